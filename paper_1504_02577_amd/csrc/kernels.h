@@ -68,7 +68,7 @@ void launch_scan_u32_to_u64(const uint32_t* in, uint64_t* out, int64_t n, void* 
 void launch_walk64(int stride, const VRec* vrec, const uint64_t* pfx, const int32_t* col,
                    const int32_t* vstart, int32_t nstart, int32_t T, uint64_t R, uint64_t seed,
                    int32_t* paths, hipStream_t s);
-void launch_walk32(int stride, const VRec* vrec, const uint2* edge, const uint4* fat,
+void launch_walk32(int stride, const VRec* vrec, const uint2* edge, const uint4* fat, int64_t m,
                    const int4* start_rec, int32_t nstart, int32_t T, uint64_t R, uint64_t seed,
                    int32_t* paths, hipStream_t s);
 

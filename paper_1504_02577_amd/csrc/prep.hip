@@ -244,11 +244,11 @@ k_guide_big(const VRec* __restrict__ vrec, const uint32_t* __restrict__ pfx,
     guide[rec.start + b] = guide_entry(pfx, rec.start, rec.deg, W, b);
 }
 
-// Fat guide record of bucket b (64 bytes, 16 words): the first three
-// candidate edges from the guide entry e0 onward, each as {inclusive
-// prefix, column, target's row start, target's degree, target's W}, and e0
-// itself in word 15.  Candidates past the row end repeat the last edge, whose
-// prefix W_v exceeds every draw, so they are never preferred.
+// Fat guide record of bucket b (four 16-byte chunks): the inclusive prefixes
+// of the first three candidate edges from the guide entry e0 onward and e0
+// itself, then each candidate's {column, target's row start, target's
+// degree, target's W}.  Candidates past the row end repeat the last edge,
+// whose prefix W_v exceeds every draw, so they are never preferred.
 __device__ __forceinline__ void fat_record(const VRec* __restrict__ vrec,
                                            const uint32_t* __restrict__ pfx,
                                            const int32_t* __restrict__ col, int32_t start,
@@ -260,13 +260,13 @@ __device__ __forceinline__ void fat_record(const VRec* __restrict__ vrec,
     if (e > start + deg - 1) e = start + deg - 1;
     const int32_t t = col[e];
     const VRec r = vrec[t];
-    w[5 * j + 0] = pfx[e];
-    w[5 * j + 1] = (uint32_t)t;
-    w[5 * j + 2] = (uint32_t)r.start;
-    w[5 * j + 3] = (uint32_t)r.deg;
-    w[5 * j + 4] = r.w_lo;
+    w[j] = pfx[e];
+    w[4 * j + 4] = (uint32_t)t;
+    w[4 * j + 5] = (uint32_t)r.start;
+    w[4 * j + 6] = (uint32_t)r.deg;
+    w[4 * j + 7] = r.w_lo;
   }
-  w[15] = (uint32_t)e0;
+  w[3] = (uint32_t)e0;
 #pragma unroll
   for (int q = 0; q < 4; ++q) out[q] = make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
 }

@@ -468,7 +468,8 @@ extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const in
     TRY(ctx_alloc(c, &p, sizeof(int32_t) * (size_t)m, "guide table"));
     tmp.add(p);
     int32_t* guide = static_cast<int32_t*>(p);
-    TRY(ctx_alloc(c, &p, 4 * sizeof(uint4) * (size_t)m, "guide records"));
+    // (at least one record: the walk reads record 0 at weightless vertices)
+    TRY(ctx_alloc(c, &p, 4 * sizeof(uint4) * (size_t)std::max<int64_t>(m, 1), "guide records"));
     c->d_fat = static_cast<uint4*>(p);
     launch_pack_edges(static_cast<const uint32_t*>(c->d_pfx), d_col, m, c->d_edge, s);
     launch_guide(c->d_vrec, static_cast<const uint32_t*>(c->d_pfx), n, big, n_big, guide, s);
@@ -575,7 +576,7 @@ extern "C" int panther_sample_paths(panther_ctx* c, int32_t T, int64_t R, uint64
     launch_walk64(stride, c->d_vrec, static_cast<const uint64_t*>(c->d_pfx), c->d_col,
                   c->d_vstart, c->nstart, T, (uint64_t)R, seed, c->d_paths, c->stream);
   else
-    launch_walk32(stride, c->d_vrec, c->d_edge, c->d_fat, c->d_start_rec, c->nstart, T,
+    launch_walk32(stride, c->d_vrec, c->d_edge, c->d_fat, c->m, c->d_start_rec, c->nstart, T,
                   (uint64_t)R, seed, c->d_paths, c->stream);
   stage_end(c, 0, c->stream);
   st = ctx_hip(c, hipGetLastError(), "walk");

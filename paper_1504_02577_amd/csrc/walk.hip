@@ -8,10 +8,10 @@
 //
 // Rows whose weight sums fit 32 bits use a guide table: bucket
 // b = floor(r_t * deg / 2^64) names the first edge e0 any draw of that bucket
-// can select.  Its 64-byte record (one aligned line) holds the edges e0,
-// e0+1, e0+2 with their inclusive prefixes, targets and the targets' own
-// {row start, degree, W}, so the usual step reads one line and already has
-// the next vertex's record; only when the draw lies beyond e0+2 does the
+// can select.  Its 64-byte record (one aligned line) holds e0 and the
+// prefixes of the edges e0, e0+1, e0+2, and their targets with the targets'
+// own {row start, degree, W}, so the usual step reads one line and already
+// has the next vertex's record; only when the draw lies beyond e0+2 does the
 // step scan packed {prefix, column} records and load the vertex record.
 // The chosen edge is always the first whose prefix exceeds u, as in a
 // bisection.
@@ -26,6 +26,13 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kScanMax = 8;  // forward steps before falling back to bisection
+// Guide tables past this size are read with non-temporal loads: such a walk
+// finds hardly a line twice (R = 6 to 12 n paths), and leaving the lines out of
+// L2 took the R-MAT 24 walk (33 GB) from 14.0 to 13.4 ms and R-MAT 23 (16 GB)
+// from 6.78 to 6.71; at R-MAT 22 (8 GB) and below both are alike (6.72 / 6.73,
+// R-MAT 20 1.36 / 1.35), and tables that caches hold lose (0.046 against
+// 0.058 ms for 10^5 paths).
+constexpr uint64_t kStreamBytes = (uint64_t)8 << 30;
 
 template <int S>
 __device__ __forceinline__ void store_row(int32_t* __restrict__ paths, uint64_t pid,
@@ -36,13 +43,71 @@ __device__ __forceinline__ void store_row(int32_t* __restrict__ paths, uint64_t 
     out[i] = make_int4(row[4 * i], row[4 * i + 1], row[4 * i + 2], row[4 * i + 3]);
 }
 
-template <int S>
+template <int CTRL>
+__device__ __forceinline__ uint32_t quad_move(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xF, 0xF, true);
+}
+
+// Transpose of a 4 x 4 matrix of words held by a quad of lanes: word j of
+// lane p becomes word p of lane j (lane exchanges at distance 1, then 2).
+__device__ __forceinline__ void quad_transpose(uint32_t& a, uint32_t& b, uint32_t& c, uint32_t& d,
+                                               bool odd, bool upper) {
+  constexpr int kXor1 = 0xB1, kXor2 = 0x4E;  // quad_perm [1,0,3,2] and [2,3,0,1]
+  uint32_t x = quad_move<kXor1>(odd ? a : b);
+  (odd ? a : b) = x;
+  x = quad_move<kXor1>(odd ? c : d);
+  (odd ? c : d) = x;
+  x = quad_move<kXor2>(upper ? a : c);
+  (upper ? a : c) = x;
+  x = quad_move<kXor2>(upper ? b : d);
+  (upper ? b : d) = x;
+}
+
+template <bool NT>
+__device__ __forceinline__ uint4 load_chunk(const uint4* p) {
+  if constexpr (NT) {
+    typedef uint32_t words __attribute__((ext_vector_type(4)));
+    const words v = __builtin_nontemporal_load(reinterpret_cast<const words*>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+  } else {
+    return *p;
+  }
+}
+
+// The 64-byte records of the four lanes of a quad: load j reads the record
+// of lane j, 16 bytes per lane, so that a record is one request of 64
+// consecutive bytes, and the transpose hands every lane the four chunks of
+// its own.  (One lane reading its record with four 16-byte loads looks the
+// line up four times, and with 2,048 lanes of a CU in flight the line could
+// leave the caches in between: the walk read 194 bytes per record from HBM.)
+// What bounds it now is the rate of scattered line requests, about 45 per
+// nanosecond (a table of 128 MB, which the Infinity Cache holds, goes no
+// faster): R-MAT 24, 10^8 paths of 5 steps, 17.4 -> 13.4 ms; R-MAT 20, 10^7
+// paths, 1.89 -> 1.36 ms.  Every lane of the quad must be active.
+template <bool NT>
+__device__ __forceinline__ void quad_records(const uint4* __restrict__ fat, uint32_t bucket,
+                                             uint4 (&g)[4]) {
+  const int p = threadIdx.x & 3;
+  const uint32_t b0 = quad_move<0x00>(bucket), b1 = quad_move<0x55>(bucket),
+                 b2 = quad_move<0xAA>(bucket), b3 = quad_move<0xFF>(bucket);
+  g[0] = load_chunk<NT>(fat + 4 * (uint64_t)b0 + p);
+  g[1] = load_chunk<NT>(fat + 4 * (uint64_t)b1 + p);
+  g[2] = load_chunk<NT>(fat + 4 * (uint64_t)b2 + p);
+  g[3] = load_chunk<NT>(fat + 4 * (uint64_t)b3 + p);
+  const bool odd = p & 1, upper = p & 2;
+  quad_transpose(g[0].x, g[1].x, g[2].x, g[3].x, odd, upper);
+  quad_transpose(g[0].y, g[1].y, g[2].y, g[3].y, odd, upper);
+  quad_transpose(g[0].z, g[1].z, g[2].z, g[3].z, odd, upper);
+  quad_transpose(g[0].w, g[1].w, g[2].w, g[3].w, odd, upper);
+}
+
+template <int S, bool NT>
 __global__ void __launch_bounds__(kBlock)
 k_walk32(const VRec* __restrict__ vrec, const uint2* __restrict__ edge,
          const uint4* __restrict__ fat, const int4* __restrict__ start_rec, int32_t nstart,
          int32_t T, uint64_t R, PhiloxKey key, int32_t* __restrict__ paths) {
+  // threads past R walk too (their quads need every lane) and write nothing
   const uint64_t pid = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (pid >= R) return;
   int32_t row[S];
   const int4 s0 = start_rec[scale64(draw(key, pid, 0u), (uint64_t)nstart)];
   int32_t v = s0.x;
@@ -53,23 +118,20 @@ k_walk32(const VRec* __restrict__ vrec, const uint2* __restrict__ edge,
     if (t <= T) {
       const uint64_t r = draw(key, pid, (uint32_t)t);
       const uint32_t W = cur.w_lo;  // w_hi == 0 on this path
+      const uint32_t u = (uint32_t)scale64(r, (uint64_t)W);
+      // a weightless row (no bucket of its own) reads record 0 and stays
+      uint4 g[4];
+      quad_records<NT>(
+          fat, W ? (uint32_t)(cur.start + (int32_t)scale64(r, (uint64_t)cur.deg)) : 0u, g);
       if (W != 0u) {
-        const uint32_t u = (uint32_t)scale64(r, (uint64_t)W);
-        const uint4* g = fat + 4 * (int64_t)(cur.start + (int32_t)scale64(r, (uint64_t)cur.deg));
-        const uint4 g0 = g[0], g1 = g[1], g2 = g[2], g3 = g[3];
-        // words: [pfx0 col0 st0 dg0] [W0 pfx1 col1 st1] [dg1 W1 pfx2 col2] [st2 dg2 W2 e0]
-        if (u < g0.x) {
-          v = (int32_t)g0.y;
-          cur = VRec{(int32_t)g0.z, (int32_t)g0.w, g1.x, 0u};
-        } else if (u < g1.y) {
-          v = (int32_t)g1.z;
-          cur = VRec{(int32_t)g1.w, (int32_t)g2.x, g2.y, 0u};
-        } else if (u < g2.z) {
-          v = (int32_t)g2.w;
-          cur = VRec{(int32_t)g3.x, (int32_t)g3.y, g3.z, 0u};
+        // chunks: [pfx0 pfx1 pfx2 e0] [col st dg W] of e0, e0+1, e0+2
+        if (u < g[0].z) {
+          const uint4 x = u < g[0].x ? g[1] : (u < g[0].y ? g[2] : g[3]);
+          v = (int32_t)x.x;
+          cur = VRec{(int32_t)x.y, (int32_t)x.z, x.w, 0u};
         } else {
           // rare: scan on from the fourth candidate, bisection after kScanMax
-          int32_t e = (int32_t)g3.w + 3;
+          int32_t e = (int32_t)g[0].w + 3;
           uint2 x = edge[e];
           int steps = 0;
           while (x.x <= u && steps < kScanMax) {
@@ -97,7 +159,7 @@ k_walk32(const VRec* __restrict__ vrec, const uint2* __restrict__ edge,
       row[t] = -1;
     }
   }
-  store_row<S>(paths, pid, row);
+  if (pid < R) store_row<S>(paths, pid, row);
 }
 
 template <int S>
@@ -158,15 +220,22 @@ void launch_walk64(int stride, const VRec* vrec, const uint64_t* pfx, const int3
 #undef PANTHER_W64
 }
 
-void launch_walk32(int stride, const VRec* vrec, const uint2* edge, const uint4* fat,
+void launch_walk32(int stride, const VRec* vrec, const uint2* edge, const uint4* fat, int64_t m,
                    const int4* start_rec, int32_t nstart, int32_t T, uint64_t R, uint64_t seed,
                    int32_t* paths, hipStream_t s) {
   const PhiloxKey key{(uint32_t)seed, (uint32_t)(seed >> 32)};
   const unsigned grid = (unsigned)((R + kBlock - 1) / kBlock);
+  if ((uint64_t)m * 64 > kStreamBytes) {
 #define PANTHER_W32(SS) \
-  k_walk32<SS><<<grid, kBlock, 0, s>>>(vrec, edge, fat, start_rec, nstart, T, R, key, paths)
-  PANTHER_STRIDES(PANTHER_W32)
+  k_walk32<SS, true><<<grid, kBlock, 0, s>>>(vrec, edge, fat, start_rec, nstart, T, R, key, paths)
+    PANTHER_STRIDES(PANTHER_W32)
 #undef PANTHER_W32
+  } else {
+#define PANTHER_W32(SS) \
+  k_walk32<SS, false><<<grid, kBlock, 0, s>>>(vrec, edge, fat, start_rec, nstart, T, R, key, paths)
+    PANTHER_STRIDES(PANTHER_W32)
+#undef PANTHER_W32
+  }
 }
 
 }  // namespace panther
