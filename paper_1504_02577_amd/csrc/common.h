@@ -80,6 +80,36 @@ __device__ __forceinline__ void dedup_row(int32_t (&v)[S]) {
 }
 
 // ---------------------------------------------------------------------------
+// Exchange inside a quad of lanes (all four active): element j of lane p
+// becomes element p of lane j, by lane moves at distance 1, then 2.
+// ---------------------------------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ uint32_t quad_move(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xF, 0xF, true);
+}
+
+__device__ __forceinline__ void quad_transpose(uint32_t& a, uint32_t& b, uint32_t& c,
+                                               uint32_t& d) {
+  constexpr int kXor1 = 0xB1, kXor2 = 0x4E;  // quad_perm [1,0,3,2] and [2,3,0,1]
+  const bool odd = threadIdx.x & 1, upper = threadIdx.x & 2;
+  uint32_t x = quad_move<kXor1>(odd ? a : b);
+  (odd ? a : b) = x;
+  x = quad_move<kXor1>(odd ? c : d);
+  (odd ? c : d) = x;
+  x = quad_move<kXor2>(upper ? a : c);
+  (upper ? a : c) = x;
+  x = quad_move<kXor2>(upper ? b : d);
+  (upper ? b : d) = x;
+}
+
+__device__ __forceinline__ void quad_exchange(uint4 (&g)[4]) {
+  quad_transpose(g[0].x, g[1].x, g[2].x, g[3].x);
+  quad_transpose(g[0].y, g[1].y, g[2].y, g[3].y);
+  quad_transpose(g[0].z, g[1].z, g[2].z, g[3].z);
+  quad_transpose(g[0].w, g[1].w, g[2].w, g[3].w);
+}
+
+// ---------------------------------------------------------------------------
 // Wave / block scans.
 // ---------------------------------------------------------------------------
 template <typename T>

@@ -25,37 +25,29 @@ void launch_validate(const int32_t* row_ptr, const int32_t* col, int32_t n, int6
 // compared).  sorted: n bytes of scratch.
 void launch_check_symmetric(const int32_t* row_ptr, const int32_t* col, const uint32_t* w,
                             int32_t n, uint8_t* sorted, uint32_t* err, hipStream_t s);
-// Row sums into vrec; rows longer than 256 entries go to big_rows.
-void launch_rowsum(const int32_t* row_ptr, const uint32_t* w, int32_t n, VRec* vrec,
-                   uint64_t* max_w, int32_t* big_rows, uint32_t* n_big, hipStream_t s);
-void launch_rowsum_big(const int32_t* big_rows, uint32_t n_big, const uint32_t* w, VRec* vrec,
-                       uint64_t* max_w, hipStream_t s);
-// Start-set flags (1 where W_v > 0, or everywhere when start_all).
-void launch_start_flags(const VRec* vrec, int32_t n, int start_all, uint32_t* flags,
-                        hipStream_t s);
-void launch_start_scatter(const uint32_t* flags, const uint64_t* pos, int32_t n, int32_t* vstart,
-                          hipStream_t s);
-// Inclusive per-row weight prefixes (uint32 when every W_v < 2^32).
-void launch_prefix32(const VRec* vrec, const uint32_t* w, int32_t n, const int32_t* big_rows,
-                     uint32_t n_big, uint32_t* pfx, hipStream_t s);
-void launch_prefix64(const VRec* vrec, const uint32_t* w, int32_t n, const int32_t* big_rows,
-                     uint32_t n_big, uint64_t* pfx, hipStream_t s);
-
-// Walk acceleration for 32-bit prefixes: edge[e] = {prefix, column} and the
-// per-row guide table (entry b = first edge any draw of bucket b can pick).
-void launch_pack_edges(const uint32_t* pfx, const int32_t* col, int64_t m, uint2* edge,
-                       hipStream_t s);
-void launch_guide(const VRec* vrec, const uint32_t* pfx, int32_t n, const int32_t* big_rows,
-                  uint32_t n_big, int32_t* guide, hipStream_t s);
-
-// 64-byte fat guide records (4 x uint4 per bucket), see prep.hip.
-void launch_fat_guide(const VRec* vrec, const uint32_t* pfx, const int32_t* col,
-                      const int32_t* guide, int32_t n, const int32_t* big_rows, uint32_t n_big,
-                      uint4* fat, hipStream_t s);
-
-// {vertex, row start, degree, W} per start-set entry (32-bit weight sums).
-void launch_start_records(const int32_t* vstart, int32_t nstart, const VRec* vrec, int4* out,
-                          hipStream_t s);
+// Tiles of the per-entry kernels below, which find an entry's row from
+// tile_row[t], the row of the first entry of tile t.
+int64_t edge_tiles(int64_t m);
+// Row records, the weights before each row (base), start-set flags (1 where
+// W_v > 0, or everywhere when start_all), tile_row and the largest W_v from
+// the exclusive scan `sum` of the weights.
+void launch_rows(const int32_t* row_ptr, const uint64_t* sum, int32_t n, int start_all, VRec* vrec,
+                 uint64_t* base, uint32_t* flags, int32_t* tile_row, uint64_t* max_w,
+                 hipStream_t s);
+// Start set in vertex order; rec (32-bit weight sums, else null) gets {vertex,
+// row start, degree, W}.
+void launch_start_scatter(const uint32_t* flags, const uint64_t* pos, const VRec* vrec, int32_t n,
+                          int32_t* vstart, int4* rec, hipStream_t s);
+// Every W_v < 2^32: packed {inclusive row prefix, column} entries and the
+// 64-byte guide records (4 x uint4 per bucket), see prep.hip.
+void launch_edges32(const int32_t* row_ptr, const int32_t* tile_row, const uint64_t* sum,
+                    const uint64_t* base, const int32_t* col, int32_t n, int64_t m, uint2* edge,
+                    hipStream_t s);
+void launch_guide32(const int32_t* row_ptr, const int32_t* tile_row, const VRec* vrec,
+                    const uint2* edge, int32_t n, int64_t m, uint4* fat, hipStream_t s);
+// Wider sums: inclusive row prefixes (pfx may be sum + 1: in place).
+void launch_prefix64(const int32_t* row_ptr, const int32_t* tile_row, const uint64_t* sum,
+                     const uint64_t* base, int32_t n, int64_t m, uint64_t* pfx, hipStream_t s);
 
 // ---- device-wide exclusive scan: out[i] = sum in[0..i), out[n] = total ----
 size_t scan_temp_bytes(int64_t n);

@@ -1,6 +1,7 @@
 // Graph preparation (Eq. 3's transition step): CSR validation, per-row
-// weight sums W_v, the start set {v : W_v > 0}, and per-row inclusive weight
-// prefixes, plus the device-wide exclusive scan used here and by the index.
+// weight sums W_v, the start set {v : W_v > 0}, per-row inclusive weight
+// prefixes and guide records, plus the device-wide exclusive scan used here
+// and by the index.
 #include "common.h"
 #include "kernels.h"
 
@@ -93,103 +94,103 @@ k_check_symmetric(const int32_t* __restrict__ row_ptr, const int32_t* __restrict
   if (__ballot(bad) != 0ull && lane == 0) atomicOr(err, 4u);
 }
 
+// ---- per-row sums, prefixes and guide records, all from one device-wide
+// scan of the weights: sum[e] = the weights of the entries before e (below
+// 2^63: fewer than 2^31 entries of 32 bits), so W_v and every row prefix are
+// differences of two of its values and no kernel depends on row lengths.
+// (One thread per short row and one wave per long row took 23.0 ms of an
+// R-MAT 22 load, 128 million entries, most of it waiting for the longest
+// rows; these kernels and the scan take 6.7 ms, of which the records, 8.2 GB
+// written, 4.6.)
+
+// Entries per work-group of the per-entry kernels; row_of finds an entry's
+// row between those of the first entries of its tile and the next.
+constexpr int kEdgePer = 16;
+constexpr int kEdgeTile = kBlock * kEdgePer;
+
 __global__ void __launch_bounds__(kBlock)
-k_rowsum(const int32_t* __restrict__ row_ptr, const uint32_t* __restrict__ w, int32_t n,
-         VRec* __restrict__ vrec, unsigned long long* max_w, int32_t* big_rows,
-         uint32_t* n_big) {
+k_rows(const int32_t* __restrict__ row_ptr, const uint64_t* __restrict__ sum, int32_t n,
+       int start_all, VRec* __restrict__ vrec, uint64_t* __restrict__ base,
+       uint32_t* __restrict__ flags, int32_t* __restrict__ tile_row, unsigned long long* max_w) {
   const int32_t v = blockIdx.x * kBlock + threadIdx.x;
-  uint64_t s = 0;
+  uint64_t W = 0;
   if (v < n) {
     const int32_t a = row_ptr[v], b = row_ptr[v + 1];
-    if (b - a > 256) {
-      big_rows[atomicAdd(n_big, 1u)] = v;
-      vrec[v] = VRec{a, b - a, 0u, 0u};
-    } else {
-      for (int32_t e = a; e < b; ++e) s += w[e];
-      vrec[v] = VRec{a, b - a, (uint32_t)s, (uint32_t)(s >> 32)};
-    }
+    const uint64_t s = sum[a];
+    W = sum[b] - s;
+    vrec[v] = VRec{a, b - a, (uint32_t)W, (uint32_t)(W >> 32)};
+    base[v] = s;
+    flags[v] = (start_all || W) ? 1u : 0u;
+    // the tiles whose first entry is in this row
+    for (int64_t t = ((int64_t)a + kEdgeTile - 1) / kEdgeTile; t * kEdgeTile < b; ++t)
+      tile_row[t] = v;
   }
-  s = wave_max(s);
-  if ((threadIdx.x & (kWave - 1)) == 0 && s) atomicMax(max_w, (unsigned long long)s);
+  W = wave_max(W);
+  if ((threadIdx.x & (kWave - 1)) == 0 && W) atomicMax(max_w, (unsigned long long)W);
 }
 
-// one wave per long row
-__global__ void __launch_bounds__(kBlock)
-k_rowsum_big(const int32_t* __restrict__ big_rows, uint32_t n_big, const uint32_t* __restrict__ w,
-             VRec* __restrict__ vrec, unsigned long long* max_w) {
-  const uint32_t r = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
-  if (r >= n_big) return;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int32_t v = big_rows[r];
-  const VRec rec = vrec[v];
-  uint64_t s = 0;
-  for (int32_t e = rec.start + lane; e < rec.start + rec.deg; e += kWave) s += w[e];
-  s = wave_sum(s);
-  if (lane == 0) {
-    vrec[v].w_lo = (uint32_t)s;
-    vrec[v].w_hi = (uint32_t)(s >> 32);
-    atomicMax(max_w, (unsigned long long)s);
+// The row holding entry e: the last v in [lo, hi] with row_ptr[v] <= e (its
+// row is not empty, since row_ptr[v + 1] > e).
+__device__ __forceinline__ int32_t row_of(const int32_t* __restrict__ row_ptr, int32_t lo,
+                                          int32_t hi, int32_t e) {
+  while (lo < hi) {
+    const int32_t mid = lo + ((hi - lo + 1) >> 1);
+    if (row_ptr[mid] <= e)
+      lo = mid;
+    else
+      hi = mid - 1;
   }
+  return lo;
 }
 
-__global__ void __launch_bounds__(kBlock)
-k_start_flags(const VRec* __restrict__ vrec, int32_t n, int start_all, uint32_t* flags) {
-  const int32_t v = blockIdx.x * kBlock + threadIdx.x;
-  if (v >= n) return;
-  const VRec r = vrec[v];
-  flags[v] = (start_all || (r.w_lo | r.w_hi)) ? 1u : 0u;
-}
-
-__global__ void __launch_bounds__(kBlock)
-k_start_scatter(const uint32_t* __restrict__ flags, const uint64_t* __restrict__ pos, int32_t n,
-                int32_t* __restrict__ vstart) {
-  const int32_t v = blockIdx.x * kBlock + threadIdx.x;
-  if (v < n && flags[v]) vstart[pos[v]] = v;
-}
-
-// Short rows: one thread per row.  Long rows: one wave per row with a
-// running carry across 64-entry chunks.
-template <typename P>
-__global__ void __launch_bounds__(kBlock)
-k_prefix_small(const VRec* __restrict__ vrec, const uint32_t* __restrict__ w, int32_t n,
-               P* __restrict__ pfx) {
-  const int32_t v = blockIdx.x * kBlock + threadIdx.x;
-  if (v >= n) return;
-  const VRec r = vrec[v];
-  if (r.deg > 256) return;
-  uint64_t s = 0;
-  for (int32_t e = r.start; e < r.start + r.deg; ++e) {
-    s += w[e];
-    pfx[e] = (P)s;
-  }
-}
-
-template <typename P>
-__global__ void __launch_bounds__(kBlock)
-k_prefix_big(const VRec* __restrict__ vrec, const uint32_t* __restrict__ w,
-             const int32_t* __restrict__ big_rows, uint32_t n_big, P* __restrict__ pfx) {
-  const uint32_t r = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
-  if (r >= n_big) return;
-  const int lane = threadIdx.x & (kWave - 1);
-  const VRec rec = vrec[big_rows[r]];
-  uint64_t carry = 0;
-  for (int32_t base = rec.start; base < rec.start + rec.deg; base += kWave) {
-    const int32_t e = base + lane;
-    const uint64_t x = e < rec.start + rec.deg ? (uint64_t)w[e] : 0ull;
-    const uint64_t inc = wave_inclusive_sum(x);
-    if (e < rec.start + rec.deg) pfx[e] = (P)(carry + inc);
-    carry += __shfl(inc, kWave - 1, kWave);
-  }
-}
-
-// ---- walk acceleration (32-bit prefixes): packed edges and guide table ----
 // edge[e] = {inclusive weight prefix, column}: one 8-byte load gives both.
 __global__ void __launch_bounds__(kBlock)
-k_pack_edges(const uint32_t* __restrict__ pfx, const int32_t* __restrict__ col, int64_t m,
-             uint2* __restrict__ edge) {
-  const int64_t gsz = (int64_t)gridDim.x * kBlock;
-  for (int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x; e < m; e += gsz)
-    edge[e] = make_uint2(pfx[e], (uint32_t)col[e]);
+k_edges32(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ tile_row,
+          const uint64_t* __restrict__ sum, const uint64_t* __restrict__ base,
+          const int32_t* __restrict__ col, int32_t n, int64_t m, uint2* __restrict__ edge) {
+  const int32_t lo = tile_row[blockIdx.x];
+  const int32_t hi = blockIdx.x + 1 < gridDim.x ? tile_row[blockIdx.x + 1] : n - 1;
+  const int64_t e0 = (int64_t)blockIdx.x * kEdgeTile + threadIdx.x;
+#pragma unroll 4
+  for (int i = 0; i < kEdgePer; ++i) {
+    const int64_t e = e0 + i * kBlock;
+    if (e >= m) break;
+    const int32_t v = row_of(row_ptr, lo, hi, (int32_t)e);
+    edge[e] = make_uint2((uint32_t)(sum[e + 1] - base[v]), (uint32_t)col[e]);
+  }
+}
+
+// 64-bit prefixes; in place when pfx == sum + 1 (each entry's own slot).
+__global__ void __launch_bounds__(kBlock)
+k_prefix64(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ tile_row,
+           const uint64_t* sum, const uint64_t* __restrict__ base, int32_t n, int64_t m,
+           uint64_t* pfx) {
+  const int32_t lo = tile_row[blockIdx.x];
+  const int32_t hi = blockIdx.x + 1 < gridDim.x ? tile_row[blockIdx.x + 1] : n - 1;
+  const int64_t e0 = (int64_t)blockIdx.x * kEdgeTile + threadIdx.x;
+#pragma unroll 4
+  for (int i = 0; i < kEdgePer; ++i) {
+    const int64_t e = e0 + i * kBlock;
+    if (e >= m) break;
+    const int32_t v = row_of(row_ptr, lo, hi, (int32_t)e);
+    pfx[e] = sum[e + 1] - base[v];
+  }
+}
+
+// Start set: vertex ids and, for the walk's first step, {vertex, row start,
+// degree, W} records (one 16-byte load instead of two lines).
+__global__ void __launch_bounds__(kBlock)
+k_start_scatter(const uint32_t* __restrict__ flags, const uint64_t* __restrict__ pos,
+                const VRec* __restrict__ vrec, int32_t n, int32_t* __restrict__ vstart,
+                int4* __restrict__ rec) {
+  const int32_t v = blockIdx.x * kBlock + threadIdx.x;
+  if (v >= n || !flags[v]) return;
+  const uint64_t i = pos[v];
+  vstart[i] = v;
+  if (rec) {
+    const VRec r = vrec[v];
+    rec[i] = make_int4(v, r.start, r.deg, (int32_t)r.w_lo);
+  }
 }
 
 // Guide entry b of a row of degree d: the draws r with floor(r d / 2^64) = b
@@ -198,8 +199,9 @@ k_pack_edges(const uint32_t* __restrict__ pfx, const int32_t* __restrict__ col, 
 // > that u is where the selection for any draw of the bucket can start.
 // ceil(b 2^64 / d) = b Q + ceil(b Rm / d) with Q = floor(2^64 / d) and
 // Rm = 2^64 mod d, all in 64-bit integers.
-__device__ __forceinline__ int32_t guide_entry(const uint32_t* __restrict__ pfx, int32_t start,
-                                               int32_t deg, uint64_t W, uint64_t b) {
+template <typename PrefixFn>
+__device__ __forceinline__ int32_t guide_entry(PrefixFn pfx, int32_t start, int32_t deg,
+                                               uint64_t W, uint64_t b) {
   const uint64_t d = (uint64_t)deg;
   uint64_t Q = ~0ull / d;
   uint64_t Rm = ~0ull - Q * d + 1ull;
@@ -212,7 +214,7 @@ __device__ __forceinline__ int32_t guide_entry(const uint32_t* __restrict__ pfx,
   int32_t lo = start, hi = start + deg - 1;
   while (lo < hi) {
     const int32_t mid = lo + ((hi - lo) >> 1);
-    if ((uint64_t)pfx[mid] > u)
+    if ((uint64_t)pfx(mid) > u)
       hi = mid;
     else
       lo = mid + 1;
@@ -220,92 +222,52 @@ __device__ __forceinline__ int32_t guide_entry(const uint32_t* __restrict__ pfx,
   return lo;
 }
 
-__global__ void __launch_bounds__(kBlock)
-k_guide_small(const VRec* __restrict__ vrec, const uint32_t* __restrict__ pfx, int32_t n,
-              int32_t* __restrict__ guide) {
-  const int32_t v = blockIdx.x * kBlock + threadIdx.x;
-  if (v >= n) return;
-  const VRec r = vrec[v];
-  const uint64_t W = (uint64_t)r.w_lo | ((uint64_t)r.w_hi << 32);
-  if (r.deg > 256 || r.deg == 0 || W == 0) return;
-  for (int32_t b = 0; b < r.deg; ++b) guide[r.start + b] = guide_entry(pfx, r.start, r.deg, W, b);
-}
-
-__global__ void __launch_bounds__(kBlock)
-k_guide_big(const VRec* __restrict__ vrec, const uint32_t* __restrict__ pfx,
-            const int32_t* __restrict__ big_rows, uint32_t n_big, int32_t* __restrict__ guide) {
-  const uint32_t r = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
-  if (r >= n_big) return;
-  const int lane = threadIdx.x & (kWave - 1);
-  const VRec rec = vrec[big_rows[r]];
-  const uint64_t W = (uint64_t)rec.w_lo | ((uint64_t)rec.w_hi << 32);
-  if (W == 0) return;
-  for (int32_t b = lane; b < rec.deg; b += kWave)
-    guide[rec.start + b] = guide_entry(pfx, rec.start, rec.deg, W, b);
-}
-
 // Fat guide record of bucket b (four 16-byte chunks): the inclusive prefixes
 // of the first three candidate edges from the guide entry e0 onward and e0
 // itself, then each candidate's {column, target's row start, target's
 // degree, target's W}.  Candidates past the row end repeat the last edge,
 // whose prefix W_v exceeds every draw, so they are never preferred.
-__device__ __forceinline__ void fat_record(const VRec* __restrict__ vrec,
-                                           const uint32_t* __restrict__ pfx,
-                                           const int32_t* __restrict__ col, int32_t start,
-                                           int32_t deg, int32_t e0, uint4* __restrict__ out) {
-  uint32_t w[16];
+// One thread per bucket: neighbouring buckets of a row bisect and gather
+// nearly the same entries, so those loads meet in L1, and the lanes of a
+// quad exchange chunks so that a record leaves as one 64-byte store.
+__global__ void __launch_bounds__(kBlock)
+k_guide32(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ tile_row,
+          const VRec* __restrict__ vrec, const uint2* __restrict__ edge, int32_t n, int64_t m,
+          uint4* __restrict__ fat) {
+  const int32_t lo = tile_row[blockIdx.x];
+  const int32_t hi = blockIdx.x + 1 < gridDim.x ? tile_row[blockIdx.x + 1] : n - 1;
+  const int64_t t0 = (int64_t)blockIdx.x * kEdgeTile + threadIdx.x;
+  const int p = threadIdx.x & 3;
+#pragma unroll 1
+  for (int i = 0; i < kEdgePer; ++i) {
+    const int64_t at = t0 + i * kBlock;
+    // lanes past the last bucket repeat it: their quad needs every lane
+    const int32_t e = (int32_t)(at < m ? at : m - 1);
+    const int32_t v = row_of(row_ptr, lo, hi, e);
+    const VRec r = vrec[v];
+    uint4 g[4] = {};
+    if (r.w_lo) {  // a weightless row has no record
+      const int32_t last = r.start + r.deg - 1;
+      const int32_t c0 = guide_entry([&](int32_t x) { return edge[x].x; }, r.start, r.deg,
+                                     (uint64_t)r.w_lo, (uint64_t)(e - r.start));
+      uint2 y[3];
+      VRec t[3];
 #pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    int32_t e = e0 + j;
-    if (e > start + deg - 1) e = start + deg - 1;
-    const int32_t t = col[e];
-    const VRec r = vrec[t];
-    w[j] = pfx[e];
-    w[4 * j + 4] = (uint32_t)t;
-    w[4 * j + 5] = (uint32_t)r.start;
-    w[4 * j + 6] = (uint32_t)r.deg;
-    w[4 * j + 7] = r.w_lo;
+      for (int j = 0; j < 3; ++j) y[j] = edge[c0 + j < last ? c0 + j : last];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) t[j] = vrec[y[j].y];
+      g[0] = make_uint4(y[0].x, y[1].x, y[2].x, (uint32_t)c0);
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        g[j + 1] = make_uint4(y[j].y, (uint32_t)t[j].start, (uint32_t)t[j].deg, t[j].w_lo);
+    }
+    quad_exchange(g);
+    // chunk p of the records of the quad's four buckets
+    const int64_t q = at - p;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (q + j < m) fat[4 * (q + j) + p] = g[j];
   }
-  w[3] = (uint32_t)e0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) out[q] = make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
-}
-
-__global__ void __launch_bounds__(kBlock)
-k_fat_small(const VRec* __restrict__ vrec, const uint32_t* __restrict__ pfx,
-            const int32_t* __restrict__ col, const int32_t* __restrict__ guide, int32_t n,
-            uint4* __restrict__ fat) {
-  const int32_t v = blockIdx.x * kBlock + threadIdx.x;
-  if (v >= n) return;
-  const VRec r = vrec[v];
-  if (r.deg > 256 || r.deg == 0 || (r.w_lo | r.w_hi) == 0) return;
-  for (int32_t b = 0; b < r.deg; ++b)
-    fat_record(vrec, pfx, col, r.start, r.deg, guide[r.start + b], fat + 4 * (int64_t)(r.start + b));
-}
-
-__global__ void __launch_bounds__(kBlock)
-k_fat_big(const VRec* __restrict__ vrec, const uint32_t* __restrict__ pfx,
-          const int32_t* __restrict__ col, const int32_t* __restrict__ guide,
-          const int32_t* __restrict__ big_rows, uint32_t n_big, uint4* __restrict__ fat) {
-  const uint32_t rr = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
-  if (rr >= n_big) return;
-  const int lane = threadIdx.x & (kWave - 1);
-  const VRec r = vrec[big_rows[rr]];
-  if ((r.w_lo | r.w_hi) == 0) return;
-  for (int32_t b = lane; b < r.deg; b += kWave)
-    fat_record(vrec, pfx, col, r.start, r.deg, guide[r.start + b], fat + 4 * (int64_t)(r.start + b));
-}
-
-// Start records: {vertex, row start, degree, W} of each start-set entry, so
-// the walk's first step reads one 16-byte record instead of two lines.
-__global__ void __launch_bounds__(kBlock)
-k_start_records(const int32_t* __restrict__ vstart, int32_t nstart, const VRec* __restrict__ vrec,
-                int4* __restrict__ out) {
-  const int32_t i = blockIdx.x * kBlock + threadIdx.x;
-  if (i >= nstart) return;
-  const int32_t v = vstart[i];
-  const VRec r = vrec[v];
-  out[i] = make_int4(v, r.start, r.deg, (int32_t)r.w_lo);
 }
 
 // ---- device-wide exclusive scan (reduce tiles, scan tile sums, apply) ----
@@ -359,26 +321,62 @@ __global__ void __launch_bounds__(kBlock) k_scan_tiles(uint64_t* tile_sums, int6
   if (threadIdx.x == 0) tile_sums[ntiles] = carry;
 }
 
+// Each wave takes 1,024 consecutive items in four rounds of four per lane, so
+// that its 16-byte loads and 32-byte stores are consecutive across lanes.
 __global__ void __launch_bounds__(kBlock)
 k_scan_apply(const uint32_t* __restrict__ in, int64_t n, const uint64_t* __restrict__ tile_sums,
              uint64_t* __restrict__ out) {
-  __shared__ uint64_t s[kBlock / kWave + 1];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  uint64_t x[kScanItems];
-  uint64_t loc = 0;
+  __shared__ uint64_t wsum[kBlock / kWave];
+  constexpr int kRounds = kScanItems / 4;
+  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+  const int64_t base =
+      (int64_t)blockIdx.x * kScanTile + (int64_t)wid * (kWave * kScanItems) + 4 * lane;
+  const bool wide = ((uintptr_t)in & 15) == 0;  // the caller's array may start anywhere
+  uint32_t x[kRounds][4];
+  uint64_t run[kRounds];  // items of the wave before this lane's four of the round
+  uint64_t carry = 0;
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    const int64_t idx = base + i;
-    x[i] = idx < n ? (uint64_t)in[idx] : 0ull;
-    loc += x[i];
+  for (int r = 0; r < kRounds; ++r) {
+    const int64_t i = base + r * (4 * kWave);
+    if (wide && i + 4 <= n) {
+      const uint4 y = *reinterpret_cast<const uint4*>(in + i);
+      x[r][0] = y.x;
+      x[r][1] = y.y;
+      x[r][2] = y.z;
+      x[r][3] = y.w;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[r][j] = i + j < n ? in[i + j] : 0u;
+    }
   }
-  uint64_t tot;
-  uint64_t run = tile_sums[blockIdx.x] + block_exclusive_sum<kBlock>(loc, s, &tot);
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    const int64_t idx = base + i;
-    if (idx < n) out[idx] = run;
-    run += x[i];
+  for (int r = 0; r < kRounds; ++r) {
+    const uint64_t four = (uint64_t)x[r][0] + x[r][1] + x[r][2] + x[r][3];
+    const uint64_t inc = wave_inclusive_sum(four);
+    run[r] = carry + inc - four;
+    carry += __shfl(inc, kWave - 1, kWave);
+  }
+  if (lane == 0) wsum[wid] = carry;
+  __syncthreads();
+  uint64_t before = tile_sums[blockIdx.x];
+  for (int w = 0; w < wid; ++w) before += wsum[w];
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const int64_t i = base + r * (4 * kWave);
+    uint64_t y[4];
+    y[0] = before + run[r];
+    y[1] = y[0] + x[r][0];
+    y[2] = y[1] + x[r][1];
+    y[3] = y[2] + x[r][2];
+    if (i + 4 <= n) {
+      ulonglong2* o = reinterpret_cast<ulonglong2*>(out + i);
+      o[0] = make_ulonglong2(y[0], y[1]);
+      o[1] = make_ulonglong2(y[2], y[3]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (i + j < n) out[i + j] = y[j];
+    }
   }
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = tile_sums[gridDim.x];
 }
@@ -405,70 +403,38 @@ void launch_check_symmetric(const int32_t* row_ptr, const int32_t* col, const ui
   k_check_symmetric<<<g, kBlock, 0, s>>>(row_ptr, col, w, sorted, n, err);
 }
 
-void launch_rowsum(const int32_t* row_ptr, const uint32_t* w, int32_t n, VRec* vrec,
-                   uint64_t* max_w, int32_t* big_rows, uint32_t* n_big, hipStream_t s) {
-  k_rowsum<<<grid_for(n, kBlock), kBlock, 0, s>>>(row_ptr, w, n, vrec,
-                                                  (unsigned long long*)max_w, big_rows, n_big);
+int64_t edge_tiles(int64_t m) { return (m + kEdgeTile - 1) / kEdgeTile; }
+
+void launch_rows(const int32_t* row_ptr, const uint64_t* sum, int32_t n, int start_all, VRec* vrec,
+                 uint64_t* base, uint32_t* flags, int32_t* tile_row, uint64_t* max_w,
+                 hipStream_t s) {
+  k_rows<<<grid_for(n, kBlock), kBlock, 0, s>>>(row_ptr, sum, n, start_all, vrec, base, flags,
+                                                tile_row, (unsigned long long*)max_w);
 }
 
-void launch_rowsum_big(const int32_t* big_rows, uint32_t n_big, const uint32_t* w, VRec* vrec,
-                       uint64_t* max_w, hipStream_t s) {
-  if (!n_big) return;
-  k_rowsum_big<<<grid_for(n_big, kBlock / kWave), kBlock, 0, s>>>(
-      big_rows, n_big, w, vrec, (unsigned long long*)max_w);
+void launch_start_scatter(const uint32_t* flags, const uint64_t* pos, const VRec* vrec, int32_t n,
+                          int32_t* vstart, int4* rec, hipStream_t s) {
+  k_start_scatter<<<grid_for(n, kBlock), kBlock, 0, s>>>(flags, pos, vrec, n, vstart, rec);
 }
 
-void launch_start_flags(const VRec* vrec, int32_t n, int start_all, uint32_t* flags,
-                        hipStream_t s) {
-  k_start_flags<<<grid_for(n, kBlock), kBlock, 0, s>>>(vrec, n, start_all, flags);
+void launch_edges32(const int32_t* row_ptr, const int32_t* tile_row, const uint64_t* sum,
+                    const uint64_t* base, const int32_t* col, int32_t n, int64_t m, uint2* edge,
+                    hipStream_t s) {
+  if (m)
+    k_edges32<<<(unsigned)edge_tiles(m), kBlock, 0, s>>>(row_ptr, tile_row, sum, base, col, n, m,
+                                                         edge);
 }
 
-void launch_start_scatter(const uint32_t* flags, const uint64_t* pos, int32_t n, int32_t* vstart,
-                          hipStream_t s) {
-  k_start_scatter<<<grid_for(n, kBlock), kBlock, 0, s>>>(flags, pos, n, vstart);
+void launch_prefix64(const int32_t* row_ptr, const int32_t* tile_row, const uint64_t* sum,
+                     const uint64_t* base, int32_t n, int64_t m, uint64_t* pfx, hipStream_t s) {
+  if (m)
+    k_prefix64<<<(unsigned)edge_tiles(m), kBlock, 0, s>>>(row_ptr, tile_row, sum, base, n, m, pfx);
 }
 
-void launch_prefix32(const VRec* vrec, const uint32_t* w, int32_t n, const int32_t* big_rows,
-                     uint32_t n_big, uint32_t* pfx, hipStream_t s) {
-  k_prefix_small<uint32_t><<<grid_for(n, kBlock), kBlock, 0, s>>>(vrec, w, n, pfx);
-  if (n_big)
-    k_prefix_big<uint32_t><<<grid_for(n_big, kBlock / kWave), kBlock, 0, s>>>(vrec, w, big_rows,
-                                                                            n_big, pfx);
-}
-
-void launch_prefix64(const VRec* vrec, const uint32_t* w, int32_t n, const int32_t* big_rows,
-                     uint32_t n_big, uint64_t* pfx, hipStream_t s) {
-  k_prefix_small<uint64_t><<<grid_for(n, kBlock), kBlock, 0, s>>>(vrec, w, n, pfx);
-  if (n_big)
-    k_prefix_big<uint64_t><<<grid_for(n_big, kBlock / kWave), kBlock, 0, s>>>(vrec, w, big_rows,
-                                                                            n_big, pfx);
-}
-
-void launch_pack_edges(const uint32_t* pfx, const int32_t* col, int64_t m, uint2* edge,
-                       hipStream_t s) {
-  if (m) k_pack_edges<<<grid_for(m, kBlock * 8, 65536), kBlock, 0, s>>>(pfx, col, m, edge);
-}
-
-void launch_guide(const VRec* vrec, const uint32_t* pfx, int32_t n, const int32_t* big_rows,
-                  uint32_t n_big, int32_t* guide, hipStream_t s) {
-  k_guide_small<<<grid_for(n, kBlock), kBlock, 0, s>>>(vrec, pfx, n, guide);
-  if (n_big)
-    k_guide_big<<<grid_for(n_big, kBlock / kWave), kBlock, 0, s>>>(vrec, pfx, big_rows, n_big,
-                                                                  guide);
-}
-
-void launch_fat_guide(const VRec* vrec, const uint32_t* pfx, const int32_t* col,
-                      const int32_t* guide, int32_t n, const int32_t* big_rows, uint32_t n_big,
-                      uint4* fat, hipStream_t s) {
-  k_fat_small<<<grid_for(n, kBlock), kBlock, 0, s>>>(vrec, pfx, col, guide, n, fat);
-  if (n_big)
-    k_fat_big<<<grid_for(n_big, kBlock / kWave), kBlock, 0, s>>>(vrec, pfx, col, guide, big_rows,
-                                                                n_big, fat);
-}
-
-void launch_start_records(const int32_t* vstart, int32_t nstart, const VRec* vrec, int4* out,
-                          hipStream_t s) {
-  k_start_records<<<grid_for(nstart, kBlock), kBlock, 0, s>>>(vstart, nstart, vrec, out);
+void launch_guide32(const int32_t* row_ptr, const int32_t* tile_row, const VRec* vrec,
+                    const uint2* edge, int32_t n, int64_t m, uint4* fat, hipStream_t s) {
+  if (m)
+    k_guide32<<<(unsigned)edge_tiles(m), kBlock, 0, s>>>(row_ptr, tile_row, vrec, edge, n, m, fat);
 }
 
 size_t scan_temp_bytes(int64_t n) {

@@ -74,7 +74,7 @@ struct panther_ctx {
   int64_t m = 0;
   int32_t* d_col = nullptr;
   panther::VRec* d_vrec = nullptr;
-  void* d_pfx = nullptr;
+  void* d_pfx = nullptr;      // 64-bit row prefixes, from entry 1 on
   bool pfx64 = false;
   uint2* d_edge = nullptr;    // {prefix, column} when every W_v < 2^32
   uint4* d_fat = nullptr;     // 64-byte guide records, same case

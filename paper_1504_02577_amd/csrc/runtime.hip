@@ -380,7 +380,7 @@ extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const in
     HIPTRY(hipMemcpyAsync(d_col, col, sizeof(int32_t) * (size_t)m, hipMemcpyDeviceToDevice, s),
            "column copy");
   }
-  // small control block: [0] error bits, [1] n_big, [2..3] max W (u64)
+  // small control block: [0] error bits, [2..3] max W (u64)
   TRY(ctx_alloc(c, &p, 64, "control"));
   tmp.add(p);
   uint32_t* ctl = static_cast<uint32_t*>(p);
@@ -414,24 +414,21 @@ extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const in
   }
   TRY(ctx_alloc(c, &p, sizeof(VRec) * (size_t)n, "vertex records"));
   c->d_vrec = static_cast<VRec*>(p);
-  TRY(ctx_alloc(c, &p, sizeof(int32_t) * (size_t)n, "long-row list"));
-  tmp.add(p);
-  int32_t* big = static_cast<int32_t*>(p);
-  launch_rowsum(d_rp, d_w, n, c->d_vrec, reinterpret_cast<uint64_t*>(ctl + 2), big, ctl + 1, s);
-  HIPTRY(hipGetLastError(), "rowsum");
-  HIPTRY(hipMemcpyAsync(hctl, ctl, 16, hipMemcpyDeviceToHost, s), "rowsum");
-  HIPTRY(hipStreamSynchronize(s), "rowsum");
-  const uint32_t n_big = hctl[1];
-  launch_rowsum_big(big, n_big, d_w, c->d_vrec, reinterpret_cast<uint64_t*>(ctl + 2), s);
-  HIPTRY(hipGetLastError(), "rowsum_big");
-  HIPTRY(hipMemcpyAsync(hctl, ctl, 16, hipMemcpyDeviceToHost, s), "rowsum");
-  HIPTRY(hipStreamSynchronize(s), "rowsum");
-  const uint64_t max_w = (uint64_t)hctl[2] | ((uint64_t)hctl[3] << 32);
-  if (max_w >= (uint64_t(1) << 63)) {
-    free_graph(c);
-    return ctx_fail(c, PANTHER_EINVAL, "row weight sum exceeds 2^63");
+  // The scan of the weights goes where the guide records will be (written
+  // last), or, when those do not fit, where the 64-bit prefixes of a graph
+  // with wide row sums will be (shifted by one entry, in place).
+  // (At least one record: the walk reads record 0 at weightless vertices.)
+  uint64_t* sum = nullptr;
+  const int fat_st = ctx_alloc(c, &p, 4 * sizeof(uint4) * (size_t)std::max<int64_t>(m, 1),
+                               "guide records");
+  if (fat_st == PANTHER_OK) {
+    c->d_fat = static_cast<uint4*>(p);
+    sum = reinterpret_cast<uint64_t*>(p);
+  } else {
+    TRY(ctx_alloc(c, &p, sizeof(uint64_t) * (size_t)(m + 1), "weight prefixes"));
+    c->d_pfx = p;
+    sum = static_cast<uint64_t*>(p);
   }
-  // start set
   const int start_all = (flags & PANTHER_START_ALL_VERTICES) ? 1 : 0;
   TRY(ctx_alloc(c, &p, sizeof(uint32_t) * (size_t)n, "start flags"));
   tmp.add(p);
@@ -439,45 +436,56 @@ extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const in
   TRY(ctx_alloc(c, &p, sizeof(uint64_t) * (size_t)(n + 1), "start positions"));
   tmp.add(p);
   uint64_t* spos = static_cast<uint64_t*>(p);
-  TRY(ctx_alloc(c, &p, scan_temp_bytes(n), "scan temp"));
+  TRY(ctx_alloc(c, &p, sizeof(uint64_t) * (size_t)n, "row offsets"));
+  tmp.add(p);
+  uint64_t* base = static_cast<uint64_t*>(p);
+  TRY(ctx_alloc(c, &p, sizeof(int32_t) * (size_t)(edge_tiles(m) + 1), "tile rows"));
+  tmp.add(p);
+  int32_t* tile_row = static_cast<int32_t*>(p);
+  TRY(ctx_alloc(c, &p, scan_temp_bytes(std::max<int64_t>(n, m)), "scan temp"));
   tmp.add(p);
   void* stemp = p;
-  launch_start_flags(c->d_vrec, n, start_all, sflags, s);
+  launch_scan_u32_to_u64(d_w, sum, m, stemp, s);
+  launch_rows(d_rp, sum, n, start_all, c->d_vrec, base, sflags, tile_row,
+              reinterpret_cast<uint64_t*>(ctl + 2), s);
   launch_scan_u32_to_u64(sflags, spos, n, stemp, s);
-  HIPTRY(hipGetLastError(), "start set");
+  HIPTRY(hipGetLastError(), "row sums");
   uint64_t nstart = 0;
+  HIPTRY(hipMemcpyAsync(hctl, ctl, 16, hipMemcpyDeviceToHost, s), "row sums");
   HIPTRY(hipMemcpyAsync(&nstart, spos + n, 8, hipMemcpyDeviceToHost, s), "start set");
-  HIPTRY(hipStreamSynchronize(s), "start set");
+  HIPTRY(hipStreamSynchronize(s), "row sums");
+  const uint64_t max_w = (uint64_t)hctl[2] | ((uint64_t)hctl[3] << 32);
+  if (max_w >= (uint64_t(1) << 63)) {
+    free_graph(c);
+    return ctx_fail(c, PANTHER_EINVAL, "row weight sum exceeds 2^63");
+  }
   if (nstart == 0) {
     free_graph(c);
     return ctx_fail(c, PANTHER_EINVAL, "no vertex has an edge of positive weight");
   }
+  c->pfx64 = max_w >= (uint64_t(1) << 32);
+  if (!c->pfx64 && fat_st) return fat_st;
   TRY(ctx_alloc(c, &p, sizeof(int32_t) * (size_t)nstart, "start set"));
   c->d_vstart = static_cast<int32_t*>(p);
-  launch_start_scatter(sflags, spos, n, c->d_vstart, s);
-  // prefixes
-  c->pfx64 = max_w >= (uint64_t(1) << 32);
-  TRY(ctx_alloc(c, &p, (c->pfx64 ? 8 : 4) * (size_t)m, "weight prefixes"));
-  c->d_pfx = p;
-  if (c->pfx64) {
-    launch_prefix64(c->d_vrec, d_w, n, big, n_big, static_cast<uint64_t*>(c->d_pfx), s);
-  } else {
-    launch_prefix32(c->d_vrec, d_w, n, big, n_big, static_cast<uint32_t*>(c->d_pfx), s);
-    TRY(ctx_alloc(c, &p, sizeof(uint2) * (size_t)m, "packed edges"));
-    c->d_edge = static_cast<uint2*>(p);
-    TRY(ctx_alloc(c, &p, sizeof(int32_t) * (size_t)m, "guide table"));
-    tmp.add(p);
-    int32_t* guide = static_cast<int32_t*>(p);
-    // (at least one record: the walk reads record 0 at weightless vertices)
-    TRY(ctx_alloc(c, &p, 4 * sizeof(uint4) * (size_t)std::max<int64_t>(m, 1), "guide records"));
-    c->d_fat = static_cast<uint4*>(p);
-    launch_pack_edges(static_cast<const uint32_t*>(c->d_pfx), d_col, m, c->d_edge, s);
-    launch_guide(c->d_vrec, static_cast<const uint32_t*>(c->d_pfx), n, big, n_big, guide, s);
-    launch_fat_guide(c->d_vrec, static_cast<const uint32_t*>(c->d_pfx), d_col, guide, n, big,
-                     n_big, c->d_fat, s);
+  if (!c->pfx64) {
     TRY(ctx_alloc(c, &p, sizeof(int4) * (size_t)nstart, "start records"));
     c->d_start_rec = static_cast<int4*>(p);
-    launch_start_records(c->d_vstart, (int32_t)nstart, c->d_vrec, c->d_start_rec, s);
+  }
+  launch_start_scatter(sflags, spos, c->d_vrec, n, c->d_vstart, c->d_start_rec, s);
+  if (c->pfx64) {
+    if (!c->d_pfx) {
+      TRY(ctx_alloc(c, &p, sizeof(uint64_t) * (size_t)(m + 1), "weight prefixes"));
+      c->d_pfx = p;
+    }
+    launch_prefix64(d_rp, tile_row, sum, base, n, m, static_cast<uint64_t*>(c->d_pfx) + 1, s);
+    HIPTRY(hipStreamSynchronize(s), "prefix");
+    ctx_free(c->d_fat);
+    c->d_fat = nullptr;
+  } else {
+    TRY(ctx_alloc(c, &p, sizeof(uint2) * (size_t)m, "packed edges"));
+    c->d_edge = static_cast<uint2*>(p);
+    launch_edges32(d_rp, tile_row, sum, base, d_col, n, m, c->d_edge, s);
+    launch_guide32(d_rp, tile_row, c->d_vrec, c->d_edge, n, m, c->d_fat, s);
   }
   HIPTRY(hipGetLastError(), "prefix");
   HIPTRY(hipStreamSynchronize(s), "load_graph");
@@ -573,7 +581,7 @@ extern "C" int panther_sample_paths(panther_ctx* c, int32_t T, int64_t R, uint64
   c->d_paths = static_cast<int32_t*>(c->b_paths.p);
   stage_begin(c, 0, c->stream);
   if (c->pfx64)
-    launch_walk64(stride, c->d_vrec, static_cast<const uint64_t*>(c->d_pfx), c->d_col,
+    launch_walk64(stride, c->d_vrec, static_cast<const uint64_t*>(c->d_pfx) + 1, c->d_col,
                   c->d_vstart, c->nstart, T, (uint64_t)R, seed, c->d_paths, c->stream);
   else
     launch_walk32(stride, c->d_vrec, c->d_edge, c->d_fat, c->m, c->d_start_rec, c->nstart, T,

@@ -43,26 +43,6 @@ __device__ __forceinline__ void store_row(int32_t* __restrict__ paths, uint64_t 
     out[i] = make_int4(row[4 * i], row[4 * i + 1], row[4 * i + 2], row[4 * i + 3]);
 }
 
-template <int CTRL>
-__device__ __forceinline__ uint32_t quad_move(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xF, 0xF, true);
-}
-
-// Transpose of a 4 x 4 matrix of words held by a quad of lanes: word j of
-// lane p becomes word p of lane j (lane exchanges at distance 1, then 2).
-__device__ __forceinline__ void quad_transpose(uint32_t& a, uint32_t& b, uint32_t& c, uint32_t& d,
-                                               bool odd, bool upper) {
-  constexpr int kXor1 = 0xB1, kXor2 = 0x4E;  // quad_perm [1,0,3,2] and [2,3,0,1]
-  uint32_t x = quad_move<kXor1>(odd ? a : b);
-  (odd ? a : b) = x;
-  x = quad_move<kXor1>(odd ? c : d);
-  (odd ? c : d) = x;
-  x = quad_move<kXor2>(upper ? a : c);
-  (upper ? a : c) = x;
-  x = quad_move<kXor2>(upper ? b : d);
-  (upper ? b : d) = x;
-}
-
 template <bool NT>
 __device__ __forceinline__ uint4 load_chunk(const uint4* p) {
   if constexpr (NT) {
@@ -94,11 +74,7 @@ __device__ __forceinline__ void quad_records(const uint4* __restrict__ fat, uint
   g[1] = load_chunk<NT>(fat + 4 * (uint64_t)b1 + p);
   g[2] = load_chunk<NT>(fat + 4 * (uint64_t)b2 + p);
   g[3] = load_chunk<NT>(fat + 4 * (uint64_t)b3 + p);
-  const bool odd = p & 1, upper = p & 2;
-  quad_transpose(g[0].x, g[1].x, g[2].x, g[3].x, odd, upper);
-  quad_transpose(g[0].y, g[1].y, g[2].y, g[3].y, odd, upper);
-  quad_transpose(g[0].z, g[1].z, g[2].z, g[3].z, odd, upper);
-  quad_transpose(g[0].w, g[1].w, g[2].w, g[3].w, odd, upper);
+  quad_exchange(g);
 }
 
 template <int S, bool NT>
