@@ -74,7 +74,7 @@ struct panther_ctx {
   int64_t m = 0;
   int32_t* d_col = nullptr;
   panther::VRec* d_vrec = nullptr;
-  void* d_pfx = nullptr;      // 64-bit row prefixes, from entry 1 on
+  uint64_t* d_pfx = nullptr;  // row prefixes from entry 1 on, when some W_v >= 2^32
   bool pfx64 = false;
   uint2* d_edge = nullptr;    // {prefix, column} when every W_v < 2^32
   uint4* d_fat = nullptr;     // 64-byte guide records, same case
@@ -82,6 +82,9 @@ struct panther_ctx {
   int32_t* d_vstart = nullptr;
   int32_t nstart = 0;
   uint64_t max_w = 0;
+  // storage of the above and of its preparation, kept across load_graph calls
+  DevBuf g_col, g_vrec, g_pfx, g_vstart, g_edge, g_fat, g_srec;
+  DevBuf g_flags, g_spos, g_base, g_tiles, g_scan, g_ctl;
   // paths + index
   bool has_paths = false;
   int32_t T = 0;

@@ -136,15 +136,18 @@ static void free_paths(panther_ctx* c, bool release) {
   }
 }
 
-static void free_graph(panther_ctx* c) {
+// Storage of the graph and of its preparation, kept for the next load_graph
+// (an R-MAT 22 load allocates 10 GB, which took up to 0.3 s of it).
+static DevBuf panther_ctx::*const kGraphBuffers[] = {
+    &panther_ctx::g_col,  &panther_ctx::g_vrec, &panther_ctx::g_pfx,  &panther_ctx::g_vstart,
+    &panther_ctx::g_edge, &panther_ctx::g_fat,  &panther_ctx::g_srec, &panther_ctx::g_flags,
+    &panther_ctx::g_spos, &panther_ctx::g_base, &panther_ctx::g_tiles, &panther_ctx::g_scan,
+    &panther_ctx::g_ctl};
+
+// Drops the graph and everything sampled from it; `release` gives the
+// graph's storage back too.
+static void free_graph(panther_ctx* c, bool release) {
   free_paths(c, true);
-  ctx_free(c->d_col);
-  ctx_free(c->d_vrec);
-  ctx_free(c->d_pfx);
-  ctx_free(c->d_vstart);
-  ctx_free(c->d_edge);
-  ctx_free(c->d_fat);
-  ctx_free(c->d_start_rec);
   c->d_edge = nullptr;
   c->d_fat = nullptr;
   c->d_start_rec = nullptr;
@@ -153,6 +156,19 @@ static void free_graph(panther_ctx* c) {
   c->d_pfx = nullptr;
   c->d_vstart = nullptr;
   c->has_graph = false;
+  if (release)
+    for (DevBuf panther_ctx::*b : kGraphBuffers) ctx_release(c->*b);
+}
+
+// A graph buffer of at least `bytes`: the kept one unless it is too small, or
+// past 64 MiB more than four times too large (a small graph after a large
+// one gives the large one's memory back).
+template <typename T>
+static int graph_alloc(panther_ctx* c, DevBuf& b, size_t bytes, const char* what, T** out) {
+  if (b.cap > ((size_t)64 << 20) && b.cap / 4 > bytes) ctx_release(b);
+  const int st = ctx_ensure(c, b, std::max<size_t>(bytes, 16), what);
+  *out = st ? nullptr : static_cast<T*>(b.p);
+  return st;
 }
 
 // RAII holder for temporaries of a call
@@ -254,7 +270,7 @@ extern "C" void panther_destroy(panther_ctx* c) {
   if (!c) return;
   (void)hipSetDevice(c->device);
   (void)hipStreamSynchronize(c->stream);
-  free_graph(c);
+  free_graph(c, true);
   for (int i = 0; i < 10; ++i)
     if (c->ev[i]) (void)hipEventDestroy(c->ev[i]);
   if (c->order_ev) (void)hipEventDestroy(c->order_ev);
@@ -324,11 +340,8 @@ extern "C" int panther_synchronize(panther_ctx* c) {
 // ---------------------------------------------------------------------------
 // load_graph (a1): validate, W_v, start set, per-row prefixes
 // ---------------------------------------------------------------------------
-extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const int32_t* row_ptr,
-                                  const int32_t* col, const uint32_t* w, int mem,
-                                  uint32_t flags) {
-  if (!c) return PANTHER_EINVAL;
-  c->err.clear();
+static int load_graph(panther_ctx* c, int32_t n, int64_t m, const int32_t* row_ptr,
+                      const int32_t* col, const uint32_t* w, int mem, uint32_t flags) {
   if (hipSetDevice(c->device) != hipSuccess) return ctx_fail(c, PANTHER_EDEVICE, "hipSetDevice");
   if (n < 1) return ctx_fail(c, PANTHER_EINVAL, "n must be >= 1");
   if (m < 0 || m >= (int64_t(1) << 31))
@@ -352,15 +365,13 @@ extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const in
   if (ends[0] != 0 || (int64_t)ends[1] != m)
     return ctx_fail(c, PANTHER_EINVAL, "row_ptr must start at 0 and end at m");
 
-  free_graph(c);
+  free_graph(c, false);
   Temp tmp;
   const int32_t* d_rp = row_ptr;
   const uint32_t* d_w = w;
-  int32_t* d_col = nullptr;
   void* p;
-  TRY(ctx_alloc(c, &p, sizeof(int32_t) * (size_t)m, "graph columns"));
-  d_col = static_cast<int32_t*>(p);
-  c->d_col = d_col;
+  TRY(graph_alloc(c, c->g_col, sizeof(int32_t) * (size_t)m, "graph columns", &c->d_col));
+  int32_t* d_col = c->d_col;
   if (mem == PANTHER_MEM_HOST) {
     TRY(ctx_alloc(c, &p, sizeof(int32_t) * (size_t)(n + 1), "row_ptr staging"));
     tmp.add(p);
@@ -381,9 +392,8 @@ extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const in
            "column copy");
   }
   // small control block: [0] error bits, [2..3] max W (u64)
-  TRY(ctx_alloc(c, &p, 64, "control"));
-  tmp.add(p);
-  uint32_t* ctl = static_cast<uint32_t*>(p);
+  uint32_t* ctl;
+  TRY(graph_alloc(c, c->g_ctl, 64, "control", &ctl));
   HIPTRY(hipMemsetAsync(ctl, 0, 64, s), "control clear");
   launch_validate(d_rp, d_col, n, m, ctl, s);
   HIPTRY(hipGetLastError(), "validate");
@@ -391,11 +401,11 @@ extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const in
   HIPTRY(hipMemcpyAsync(hctl, ctl, 16, hipMemcpyDeviceToHost, s), "validate");
   HIPTRY(hipStreamSynchronize(s), "validate");
   if (hctl[0] & 1u) {
-    free_graph(c);
+    free_graph(c, false);
     return ctx_fail(c, PANTHER_EINVAL, "row_ptr decreases");
   }
   if (hctl[0] & 2u) {
-    free_graph(c);
+    free_graph(c, false);
     return ctx_fail(c, PANTHER_EINVAL, "column id out of range");
   }
   if (flags & PANTHER_CHECK_SYMMETRIC) {
@@ -406,45 +416,37 @@ extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const in
     HIPTRY(hipMemcpyAsync(hctl, ctl, 16, hipMemcpyDeviceToHost, s), "symmetry check");
     HIPTRY(hipStreamSynchronize(s), "symmetry check");
     if (hctl[0] & 4u) {
-      free_graph(c);
+      free_graph(c, false);
       return ctx_fail(c, PANTHER_EINVAL,
                       "CSR is not symmetric: an entry v->u of weight w lacks a matching u->v "
                       "of weight w");
     }
   }
-  TRY(ctx_alloc(c, &p, sizeof(VRec) * (size_t)n, "vertex records"));
-  c->d_vrec = static_cast<VRec*>(p);
+  TRY(graph_alloc(c, c->g_vrec, sizeof(VRec) * (size_t)n, "vertex records", &c->d_vrec));
   // The scan of the weights goes where the guide records will be (written
   // last), or, when those do not fit, where the 64-bit prefixes of a graph
   // with wide row sums will be (shifted by one entry, in place).
   // (At least one record: the walk reads record 0 at weightless vertices.)
   uint64_t* sum = nullptr;
-  const int fat_st = ctx_alloc(c, &p, 4 * sizeof(uint4) * (size_t)std::max<int64_t>(m, 1),
-                               "guide records");
+  const int fat_st = graph_alloc(c, c->g_fat, 4 * sizeof(uint4) * (size_t)std::max<int64_t>(m, 1),
+                                 "guide records", &c->d_fat);
   if (fat_st == PANTHER_OK) {
-    c->d_fat = static_cast<uint4*>(p);
-    sum = reinterpret_cast<uint64_t*>(p);
+    sum = reinterpret_cast<uint64_t*>(c->d_fat);
   } else {
-    TRY(ctx_alloc(c, &p, sizeof(uint64_t) * (size_t)(m + 1), "weight prefixes"));
-    c->d_pfx = p;
-    sum = static_cast<uint64_t*>(p);
+    TRY(graph_alloc(c, c->g_pfx, sizeof(uint64_t) * (size_t)(m + 1), "weight prefixes", &sum));
+    c->d_pfx = sum;
   }
   const int start_all = (flags & PANTHER_START_ALL_VERTICES) ? 1 : 0;
-  TRY(ctx_alloc(c, &p, sizeof(uint32_t) * (size_t)n, "start flags"));
-  tmp.add(p);
-  uint32_t* sflags = static_cast<uint32_t*>(p);
-  TRY(ctx_alloc(c, &p, sizeof(uint64_t) * (size_t)(n + 1), "start positions"));
-  tmp.add(p);
-  uint64_t* spos = static_cast<uint64_t*>(p);
-  TRY(ctx_alloc(c, &p, sizeof(uint64_t) * (size_t)n, "row offsets"));
-  tmp.add(p);
-  uint64_t* base = static_cast<uint64_t*>(p);
-  TRY(ctx_alloc(c, &p, sizeof(int32_t) * (size_t)(edge_tiles(m) + 1), "tile rows"));
-  tmp.add(p);
-  int32_t* tile_row = static_cast<int32_t*>(p);
-  TRY(ctx_alloc(c, &p, scan_temp_bytes(std::max<int64_t>(n, m)), "scan temp"));
-  tmp.add(p);
-  void* stemp = p;
+  uint32_t* sflags;
+  uint64_t *spos, *base;
+  int32_t* tile_row;
+  char* stemp;
+  TRY(graph_alloc(c, c->g_flags, sizeof(uint32_t) * (size_t)n, "start flags", &sflags));
+  TRY(graph_alloc(c, c->g_spos, sizeof(uint64_t) * (size_t)(n + 1), "start positions", &spos));
+  TRY(graph_alloc(c, c->g_base, sizeof(uint64_t) * (size_t)n, "row offsets", &base));
+  TRY(graph_alloc(c, c->g_tiles, sizeof(int32_t) * (size_t)(edge_tiles(m) + 1), "tile rows",
+                  &tile_row));
+  TRY(graph_alloc(c, c->g_scan, scan_temp_bytes(std::max<int64_t>(n, m)), "scan temp", &stemp));
   launch_scan_u32_to_u64(d_w, sum, m, stemp, s);
   launch_rows(d_rp, sum, n, start_all, c->d_vrec, base, sflags, tile_row,
               reinterpret_cast<uint64_t*>(ctl + 2), s);
@@ -456,34 +458,33 @@ extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const in
   HIPTRY(hipStreamSynchronize(s), "row sums");
   const uint64_t max_w = (uint64_t)hctl[2] | ((uint64_t)hctl[3] << 32);
   if (max_w >= (uint64_t(1) << 63)) {
-    free_graph(c);
+    free_graph(c, false);
     return ctx_fail(c, PANTHER_EINVAL, "row weight sum exceeds 2^63");
   }
   if (nstart == 0) {
-    free_graph(c);
+    free_graph(c, false);
     return ctx_fail(c, PANTHER_EINVAL, "no vertex has an edge of positive weight");
   }
   c->pfx64 = max_w >= (uint64_t(1) << 32);
   if (!c->pfx64 && fat_st) return fat_st;
-  TRY(ctx_alloc(c, &p, sizeof(int32_t) * (size_t)nstart, "start set"));
-  c->d_vstart = static_cast<int32_t*>(p);
-  if (!c->pfx64) {
-    TRY(ctx_alloc(c, &p, sizeof(int4) * (size_t)nstart, "start records"));
-    c->d_start_rec = static_cast<int4*>(p);
-  }
+  TRY(graph_alloc(c, c->g_vstart, sizeof(int32_t) * (size_t)nstart, "start set", &c->d_vstart));
+  if (!c->pfx64)
+    TRY(graph_alloc(c, c->g_srec, sizeof(int4) * (size_t)nstart, "start records",
+                    &c->d_start_rec));
   launch_start_scatter(sflags, spos, c->d_vrec, n, c->d_vstart, c->d_start_rec, s);
   if (c->pfx64) {
-    if (!c->d_pfx) {
-      TRY(ctx_alloc(c, &p, sizeof(uint64_t) * (size_t)(m + 1), "weight prefixes"));
-      c->d_pfx = p;
-    }
-    launch_prefix64(d_rp, tile_row, sum, base, n, m, static_cast<uint64_t*>(c->d_pfx) + 1, s);
+    ctx_release(c->g_edge);  // storage of a graph with narrow row sums
+    ctx_release(c->g_srec);
+    if (!c->d_pfx)
+      TRY(graph_alloc(c, c->g_pfx, sizeof(uint64_t) * (size_t)(m + 1), "weight prefixes",
+                      &c->d_pfx));
+    launch_prefix64(d_rp, tile_row, sum, base, n, m, c->d_pfx + 1, s);
     HIPTRY(hipStreamSynchronize(s), "prefix");
-    ctx_free(c->d_fat);
+    ctx_release(c->g_fat);
     c->d_fat = nullptr;
   } else {
-    TRY(ctx_alloc(c, &p, sizeof(uint2) * (size_t)m, "packed edges"));
-    c->d_edge = static_cast<uint2*>(p);
+    ctx_release(c->g_pfx);
+    TRY(graph_alloc(c, c->g_edge, sizeof(uint2) * (size_t)m, "packed edges", &c->d_edge));
     launch_edges32(d_rp, tile_row, sum, base, d_col, n, m, c->d_edge, s);
     launch_guide32(d_rp, tile_row, c->d_vrec, c->d_edge, n, m, c->d_fat, s);
   }
@@ -495,6 +496,24 @@ extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const in
   c->max_w = max_w;
   c->has_graph = true;
   return PANTHER_OK;
+}
+
+extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const int32_t* row_ptr,
+                                  const int32_t* col, const uint32_t* w, int mem,
+                                  uint32_t flags) {
+  if (!c) return PANTHER_EINVAL;
+  c->err.clear();
+  bool kept = false;
+  for (DevBuf panther_ctx::*b : kGraphBuffers) kept = kept || (c->*b).p;
+  int st = load_graph(c, n, m, row_ptr, col, w, mem, flags);
+  if (st == PANTHER_ENOMEM && kept) {
+    // what the previous graph's storage holds may be what is missing
+    (void)hipStreamSynchronize(c->stream);
+    free_graph(c, true);
+    c->err.clear();
+    st = load_graph(c, n, m, row_ptr, col, w, mem, flags);
+  }
+  return st;
 }
 
 // ---------------------------------------------------------------------------
@@ -581,7 +600,7 @@ extern "C" int panther_sample_paths(panther_ctx* c, int32_t T, int64_t R, uint64
   c->d_paths = static_cast<int32_t*>(c->b_paths.p);
   stage_begin(c, 0, c->stream);
   if (c->pfx64)
-    launch_walk64(stride, c->d_vrec, static_cast<const uint64_t*>(c->d_pfx) + 1, c->d_col,
+    launch_walk64(stride, c->d_vrec, c->d_pfx + 1, c->d_col,
                   c->d_vstart, c->nstart, T, (uint64_t)R, seed, c->d_paths, c->stream);
   else
     launch_walk32(stride, c->d_vrec, c->d_edge, c->d_fat, c->m, c->d_start_rec, c->nstart, T,
