@@ -104,6 +104,13 @@ void launch_zero_u32(uint32_t* p, uint64_t n, hipStream_t s);
 void launch_query_lengths(const uint64_t* inv_ptr, const int32_t* queries, int64_t nq,
                           uint64_t* out, hipStream_t s);
 
+// FP64 brute force (knn.hip): workspace bytes of a call, and the call.
+size_t knn_fp64_bytes(int64_t nq, int32_t n, int32_t D, int32_t k, int num_cus);
+int launch_knn_fp64(const float* theta, int32_t n, int32_t D, const float* qtheta,
+                    bool exclude_self, const int32_t* queries, const int32_t* rows, int64_t nq,
+                    int32_t k, int num_cus, void* work, size_t work_bytes, int32_t* out_ids,
+                    double* out_dist, hipStream_t s);
+
 // A norm-ordered copy of a kNN database: rows p < rows in ascending order
 // of their stored squared norm norm_s[p] (units scaled by scale), vertex
 // sid[p]; err bounds the distance between a stored row and scale * theta_v.

@@ -10,13 +10,12 @@
 // The cross-graph form takes the query rows from another graph's features
 // and ranks every row of this one (no row is the query itself).
 //
-// A work-group takes QT queries (their rows in LDS as doubles) and streams
-// all n rows, one row per thread per round.  Each query keeps a candidate
-// buffer in LDS with a threshold (the kp-th best (d2, id) kept so far):
-// candidates below it are appended; at the end of a round any buffer with
-// more than kp entries is bitonic-sorted by one wavefront and cut back to
-// kp, which tightens the threshold.  A round adds at most 256 entries, so a
-// 512-entry buffer never overflows for kp <= 256.
+// A work-group takes 16 queries and a slice of the rows, two rows per thread
+// per round.  Each query keeps a candidate buffer in LDS with a threshold (the
+// kp-th best (d2, id) kept so far): candidates below it are appended, and a
+// buffer with more than kp entries is bitonic-sorted by one wavefront and cut
+// back to kp, which tightens the threshold.  The slices' kp best pairs are
+// merged per query: the order is total, so any split gives the same k.
 #include <algorithm>
 #include <cmath>
 
@@ -28,7 +27,10 @@ namespace panther {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kBuf = 512;
+constexpr int kQT = 16;     // queries of a work-group's tile
+constexpr int kRows = 2;    // database rows per thread and round
+constexpr int kCols = 16;   // coordinates staged per step
+static_assert(kQT * kRows <= 32, "one pending bit per (query, row)");
 
 __device__ __forceinline__ void wave_sync_knn() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -69,86 +71,208 @@ __device__ void wave_sort_pairs(double* d, int32_t* v, int cnt) {
   }
 }
 
-template <int QT>
+// Query rows as doubles, coordinate-major inside each tile of kQT queries
+// (zeros past the last query): one coordinate of a tile is 128 consecutive
+// bytes, which the scan reads through the scalar cache.
 __global__ void __launch_bounds__(kBlock)
-k_knn_fp64(const float* __restrict__ theta, int32_t n, int32_t D,
-           const float* __restrict__ qtheta, int32_t exclude_self,
-           const int32_t* __restrict__ queries, const int32_t* __restrict__ rows, int64_t nq,
-           int32_t k, int32_t kp,
-           int32_t* __restrict__ out_ids, double* __restrict__ out_dist) {
+k_knn_query_rows(const float* __restrict__ qtheta, int32_t D, const int32_t* __restrict__ queries,
+                 const int32_t* __restrict__ rows, int64_t nq, int64_t total,
+                 double* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= total) return;
+  const int64_t tile = i / ((int64_t)D * kQT);
+  const int32_t d = (int32_t)(i / kQT % D);
+  const int64_t q = tile * kQT + i % kQT;
+  out[i] = q < nq ? (double)qtheta[(int64_t)queries[rows ? rows[q] : q] * D + d] : 0.0;
+}
+
+// LDS of k_knn_fp64: kQT candidate buffers of `cap` pairs, the row stage.
+constexpr int kStagePitch = kCols + 1;
+__host__ __device__ constexpr size_t knn_scan_lds(int cap) {
+  return (sizeof(double) + sizeof(int32_t)) * (size_t)kQT * cap +
+         sizeof(float) * (size_t)kBlock * kRows * kStagePitch;
+}
+// Pairs a buffer holds: at least kp free places after every cut.
+__host__ __device__ constexpr int knn_scan_cap(int kp) { return kp < 64 ? 128 : 2 * kp; }
+
+// Bound: FP64 VALU, one subtraction and one fma per (query, row, coordinate),
+// at 16 lanes per clock and SIMD.  Each coordinate of the 16 queries comes as
+// scalars, each of the thread's two rows from LDS (the rows are staged 16
+// coordinates at a time by coalesced loads), so 64 FP64 instructions follow
+// two LDS reads.  The rows are split over grid.y so that few queries fill the
+// chip too: 301 queries x 262,144 rows of 100 coordinates took 43.1 ms on 19
+// work-groups that each scanned every row.
+__global__ void __launch_bounds__(kBlock)
+k_knn_fp64(const float* __restrict__ theta, int32_t n, int32_t D, const double* __restrict__ qrows,
+           int32_t exclude_self, const int32_t* __restrict__ queries,
+           const int32_t* __restrict__ rows, int64_t nq, int32_t kp, int32_t cap,
+           double* __restrict__ part_d, int32_t* __restrict__ part_v) {
   extern __shared__ __align__(16) char lds[];
-  double* qv = reinterpret_cast<double*>(lds);      // [QT][D]
-  double* bd = qv + QT * D;                          // [QT][kBuf]
-  int32_t* bv = reinterpret_cast<int32_t*>(bd + QT * kBuf);
-  uint32_t* cnt = reinterpret_cast<uint32_t*>(bv + QT * kBuf);
-  double* tau_d = reinterpret_cast<double*>(cnt + QT + (QT & 1));
-  int32_t* tau_v = reinterpret_cast<int32_t*>(tau_d + QT);
-  int32_t* qid = tau_v + QT;
+  double* bd = reinterpret_cast<double*>(lds);            // [kQT][cap]
+  int32_t* bv = reinterpret_cast<int32_t*>(bd + kQT * cap);  // [kQT][cap]
+  float* stage = reinterpret_cast<float*>(bv + kQT * cap);   // [kRows * kBlock][kStagePitch]
+  __shared__ uint32_t cnt[kQT];
+  __shared__ double tau_d[kQT];
+  __shared__ int32_t tau_v[kQT];
+  __shared__ int32_t qid[kQT];
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  const int64_t q0 = (int64_t)blockIdx.x * QT;
-  for (int i = threadIdx.x; i < QT; i += kBlock) {
+  const int64_t q0 = (int64_t)blockIdx.x * kQT;
+  if (threadIdx.x < kQT) {
+    const int i = threadIdx.x;
     qid[i] = (q0 + i < nq) ? queries[rows ? rows[q0 + i] : q0 + i] : -1;
     cnt[i] = 0u;
     tau_d[i] = INFINITY;
     tau_v[i] = 0x7FFFFFFF;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < QT * D; i += kBlock) {
-    const int32_t q = qid[i / D];
-    qv[i] = q >= 0 ? (double)qtheta[(int64_t)q * D + (i % D)] : 0.0;
-  }
-  __syncthreads();
-  for (int64_t base = 0; base < n; base += kBlock) {
-    const int64_t v = base + threadIdx.x;
-    double acc[QT];
+  typedef const __attribute__((address_space(4))) double* scalar_rows;
+  const scalar_rows qv = (scalar_rows)(uintptr_t)(qrows + q0 * D);
+  // this slice's rounds of kRows * kBlock rows, interleaved over the slices
+  constexpr int kRound = kRows * kBlock;
+  const int64_t step = (int64_t)gridDim.y * kRound;
+  for (int64_t base = (int64_t)blockIdx.y * kRound; base < n; base += step) {
+    double acc[kRows][kQT];
 #pragma unroll
-    for (int q = 0; q < QT; ++q) acc[q] = 0.0;
-    if (v < n) {
-      const float* row = theta + v * D;
-      for (int d = 0; d < D; ++d) {
-        const double x = (double)row[d];
+    for (int r = 0; r < kRows; ++r)
 #pragma unroll
-        for (int q = 0; q < QT; ++q) {
-          const double delta = qv[q * D + d] - x;
-          acc[q] = fma(delta, delta, acc[q]);
+      for (int q = 0; q < kQT; ++q) acc[r][q] = 0.0;
+    for (int d0 = 0; d0 < D; d0 += kCols) {
+      const int nc = D - d0 < kCols ? D - d0 : kCols;
+      // kCols lanes take the consecutive coordinates of one row
+      const int c = threadIdx.x % kCols;
+#pragma unroll 8
+      for (int i = 0; i < kRound * kCols / kBlock; ++i) {
+        const int r = i * (kBlock / kCols) + (int)threadIdx.x / kCols;
+        const int64_t v = base + r;
+        stage[r * kStagePitch + c] = v < n && c < nc ? theta[v * D + d0 + c] : 0.f;
+      }
+      __syncthreads();
+#pragma unroll 2
+      for (int d = 0; d < nc; ++d) {
+        double x[kRows];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+          x[r] = (double)stage[(r * kBlock + threadIdx.x) * kStagePitch + d];
+#pragma unroll
+        for (int q = 0; q < kQT; ++q) {
+          const double qx = qv[(d0 + d) * kQT + q];
+#pragma unroll
+          for (int r = 0; r < kRows; ++r) {
+            const double delta = qx - x[r];
+            acc[r][q] = fma(delta, delta, acc[r][q]);
+          }
+        }
+      }
+      __syncthreads();
+    }
+    // candidates below their query's threshold; those that find no room wait
+    // for the buffer's cut and are tested again
+    uint32_t pend = 0u;
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      const int64_t v = base + r * kBlock + threadIdx.x;
+#pragma unroll
+      for (int q = 0; q < kQT; ++q) {
+        const int32_t me = qid[q];
+        if (v < n && me >= 0 && (!exclude_self || (int32_t)v != me) &&
+            pair_less(acc[r][q], (int32_t)v, tau_d[q], tau_v[q]))
+          pend |= 1u << (r * kQT + q);
+      }
+    }
+    while (__syncthreads_or(pend != 0u)) {
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) {
+        const int32_t v = (int32_t)(base + r * kBlock + threadIdx.x);
+#pragma unroll
+        for (int q = 0; q < kQT; ++q) {
+          const uint32_t bit = 1u << (r * kQT + q);
+          if (!(pend & bit)) continue;
+          if (!pair_less(acc[r][q], v, tau_d[q], tau_v[q])) {
+            pend &= ~bit;
+            continue;
+          }
+          const uint32_t pos = atomicAdd(&cnt[q], 1u);
+          if (pos < (uint32_t)cap) {
+            bd[q * cap + pos] = acc[r][q];
+            bv[q * cap + pos] = v;
+            pend &= ~bit;
+          }
+        }
+      }
+      __syncthreads();
+      for (int q = wid; q < kQT; q += kBlock / kWave) {
+        const int c = (int)cnt[q] < cap ? (int)cnt[q] : cap;
+        if (c > kp) {
+          wave_sort_pairs(bd + q * cap, bv + q * cap, c);
+          if (lane == 0) {
+            cnt[q] = (uint32_t)kp;
+            tau_d[q] = bd[q * cap + kp - 1];
+            tau_v[q] = bv[q * cap + kp - 1];
+          }
         }
       }
     }
-#pragma unroll
-    for (int q = 0; q < QT; ++q) {
-      const int32_t me = qid[q];
-      if (v < n && me >= 0 && (!exclude_self || (int32_t)v != me) &&
-          pair_less(acc[q], (int32_t)v, tau_d[q], tau_v[q])) {
-        const uint32_t pos = atomicAdd(&cnt[q], 1u);
-        bd[q * kBuf + pos] = acc[q];
-        bv[q * kBuf + pos] = (int32_t)v;
-      }
-    }
-    __syncthreads();
-    for (int q = wid; q < QT; q += kBlock / kWave) {
-      const int c = (int)cnt[q];
-      if (c > kp) {
-        wave_sort_pairs(bd + q * kBuf, bv + q * kBuf, c);
-        if (lane == 0) {
-          cnt[q] = (uint32_t)kp;
-          tau_d[q] = bd[q * kBuf + kp - 1];
-          tau_v[q] = bv[q * kBuf + kp - 1];
-        }
-      }
-    }
-    __syncthreads();
   }
-  for (int q = wid; q < QT; q += kBlock / kWave) {
+  for (int q = wid; q < kQT; q += kBlock / kWave) {
     if (qid[q] < 0) continue;
-    const int c = (int)cnt[q];
-    wave_sort_pairs(bd + q * kBuf, bv + q * kBuf, c);
-    const int64_t qi = rows ? (int64_t)rows[q0 + q] : q0 + q;
-    for (int j = lane; j < k; j += kWave) {
-      const bool ok = j < c;
-      out_ids[qi * k + j] = ok ? bv[q * kBuf + j] : -1;
-      out_dist[qi * k + j] = ok ? sqrt(bd[q * kBuf + j]) : INFINITY;
+    const int c = (int)cnt[q];  // <= kp
+    const int64_t o = ((q0 + q) * gridDim.y + blockIdx.y) * kp;
+    for (int j = lane; j < kp; j += kWave) {
+      part_d[o + j] = j < c ? bd[q * cap + j] : INFINITY;
+      part_v[o + j] = j < c ? bv[q * cap + j] : 0x7FFFFFFF;
     }
-    wave_sync_knn();
+  }
+}
+
+// One work-group per query: the k best of its slices' pairs (m of them, the
+// missing ones (inf, INT32_MAX)), kMergeCap at a time beside the kp best so
+// far.
+constexpr int kMergeCap = 1024;
+__global__ void __launch_bounds__(kBlock)
+k_knn_merge(const double* __restrict__ part_d, const int32_t* __restrict__ part_v, int32_t m,
+            int32_t kp, int32_t k, const int32_t* __restrict__ rows,
+            int32_t* __restrict__ out_ids, double* __restrict__ out_dist) {
+  __shared__ double sd[kMergeCap];
+  __shared__ int32_t sv[kMergeCap];
+  const int64_t q = blockIdx.x;
+  const int64_t o = q * m;
+  int kept = 0;
+  for (int at = 0; at < m;) {
+    const int take = m - at < kMergeCap - kept ? m - at : kMergeCap - kept;
+    int P = 2;
+    while (P < kept + take) P <<= 1;
+    for (int j = kept + threadIdx.x; j < P; j += kBlock) {
+      const bool ok = j < kept + take;
+      sd[j] = ok ? part_d[o + at + j - kept] : INFINITY;
+      sv[j] = ok ? part_v[o + at + j - kept] : 0x7FFFFFFF;
+    }
+    __syncthreads();
+    for (int size = 2; size <= P; size <<= 1) {
+      for (int stride = size >> 1; stride > 0; stride >>= 1) {
+        for (int j = threadIdx.x; j < (P >> 1); j += kBlock) {
+          const int lo = ((j & ~(stride - 1)) << 1) | (j & (stride - 1));  // stride: power of two
+          const int hi = lo + stride;
+          const bool asc = (lo & size) == 0;
+          const double a = sd[lo], b = sd[hi];
+          const int32_t x = sv[lo], y = sv[hi];
+          if (pair_less(b, y, a, x) == asc) {
+            sd[lo] = b;
+            sd[hi] = a;
+            sv[lo] = y;
+            sv[hi] = x;
+          }
+        }
+        __syncthreads();
+      }
+    }
+    at += take;
+    kept = kept + take < kp ? kept + take : kp;
+  }
+  const int64_t qi = rows ? (int64_t)rows[q] : q;
+  for (int j = threadIdx.x; j < k; j += kBlock) {
+    const bool ok = j < kept && sv[j] != 0x7FFFFFFF;
+    out_ids[qi * k + j] = ok ? sv[j] : -1;
+    out_dist[qi * k + j] = ok ? sqrt(sd[j]) : INFINITY;
   }
 }
 
@@ -289,10 +413,6 @@ k_knn_cand_select(const int32_t* __restrict__ rows, const double* __restrict__ c
 
 }  // namespace
 
-int launch_knn_fp64(const float* theta, int32_t n, int32_t D, const float* qtheta,
-                    bool exclude_self, const int32_t* queries, const int32_t* rows, int64_t nq,
-                    int32_t k, int32_t* out_ids, double* out_dist, hipStream_t s);
-
 size_t knn_range_bytes(int64_t nr) {
   return (sizeof(double) + sizeof(int32_t)) * (size_t)nr * kSelCap + sizeof(unsigned) * nr +
          sizeof(int32_t) * nr + 2 * sizeof(int64_t) * nr + 256;
@@ -352,35 +472,89 @@ int launch_knn_recompute(const float* theta, int32_t n, int32_t D, const float* 
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return (int)e;
   if (ov == 0) return 0;
+  // the candidate lists are done with: their place (48 KiB per listed query,
+  // more than a tile of query rows and one slice need) is the scan's
   return launch_knn_fp64(theta, n, D, qtheta, exclude_self, queries, ov_list, (int64_t)ov, k,
+                         num_cus, work, (sizeof(double) + sizeof(int32_t)) * (size_t)nr * kSelCap,
                          out_ids, out_dist, s);
 }
 
-size_t knn_fp64_lds(int D) {
-  constexpr int QT = 16;
-  return sizeof(double) * QT * D + (sizeof(double) + sizeof(int32_t)) * QT * kBuf +
-         sizeof(uint32_t) * (QT + 1) + (sizeof(double) + 2 * sizeof(int32_t)) * QT + 64;
+namespace {
+// Queries of one launch of the FP64 form, and its workspace: query rows, then
+// per query S slices of kp pairs.
+constexpr int64_t kFp64Batch = 32768;
+size_t fp64_bytes(int64_t nq, int32_t D, int64_t S, int kp) {
+  const size_t tiles = (size_t)((nq + kQT - 1) / kQT);
+  return sizeof(double) * tiles * kQT * D +
+         (sizeof(double) + sizeof(int32_t)) * (size_t)nq * S * kp;
+}
+int pow2_at_least(int k) {
+  int kp = 1;
+  while (kp < k) kp <<= 1;
+  return kp;
+}
+// Slices of the rows: four work-groups per CU where the queries' tiles alone
+// are fewer, each with at least four rounds of rows, and at most 4,096 pairs
+// per query to merge.
+int64_t fp64_slices(int64_t nq, int32_t n, int kp, int num_cus) {
+  const int64_t tiles = (nq + kQT - 1) / kQT;
+  int64_t S = (4 * (int64_t)num_cus + tiles - 1) / tiles;
+  S = std::min<int64_t>(S, (n + 4 * kRows * kBlock - 1) / (4 * kRows * kBlock));
+  S = std::min<int64_t>(S, 4096 / kp);
+  return std::max<int64_t>(S, 1);
+}
+}  // namespace
+
+size_t knn_fp64_bytes(int64_t nq, int32_t n, int32_t D, int32_t k, int num_cus) {
+  if (nq <= 0) return 0;
+  const int kp = pow2_at_least(k);
+  nq = std::min(nq, kFp64Batch);
+  return fp64_bytes(nq, D, fp64_slices(nq, n, kp, num_cus), kp);
 }
 
 // qtheta: the queries' feature rows (theta itself for one graph, the other
 // graph's for the cross-graph form, which excludes no row).  rows (may be
 // null): the call answers queries[rows[i]] into output row rows[i] for
-// i < nq, instead of queries[i] into row i.
+// i < nq, instead of queries[i] into row i.  work: at least
+// knn_fp64_bytes(nq, ...) bytes, or less: then fewer slices or queries go at
+// a time (at least one tile and one slice must fit).
 int launch_knn_fp64(const float* theta, int32_t n, int32_t D, const float* qtheta,
                     bool exclude_self, const int32_t* queries, const int32_t* rows, int64_t nq,
-                    int32_t k, int32_t* out_ids, double* out_dist, hipStream_t s) {
-  constexpr int QT = 16;
-  int kp = 1;
-  while (kp < k) kp <<= 1;
-  const size_t lds = knn_fp64_lds(D);
-  hipError_t e = hipFuncSetAttribute((const void*)k_knn_fp64<QT>,
+                    int32_t k, int num_cus, void* work, size_t work_bytes, int32_t* out_ids,
+                    double* out_dist, hipStream_t s) {
+  const int kp = pow2_at_least(k);
+  const int cap = knn_scan_cap(kp);
+  const size_t lds = knn_scan_lds(cap);
+  hipError_t e = hipFuncSetAttribute((const void*)k_knn_fp64,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return (int)e;
-  const unsigned grid = (unsigned)((nq + QT - 1) / QT);
-  if (grid)
-    k_knn_fp64<QT><<<grid, kBlock, lds, s>>>(theta, n, D, qtheta, exclude_self ? 1 : 0, queries,
-                                              rows, nq, k, kp, out_ids, out_dist);
-  return (int)hipGetLastError();
+  int64_t most = std::min(nq, kFp64Batch);
+  while (most > 1 && fp64_bytes(most, D, 1, kp) > work_bytes) most = (most + 1) / 2;
+  if (most > 0 && fp64_bytes(most, D, 1, kp) > work_bytes) return (int)hipErrorInvalidValue;
+  for (int64_t i = 0; i < nq; i += most) {
+    const int64_t m = std::min(most, nq - i);
+    int64_t S = fp64_slices(m, n, kp, num_cus);
+    while (S > 1 && fp64_bytes(m, D, S, kp) > work_bytes) --S;
+    const int64_t tiles = (m + kQT - 1) / kQT;
+    const int64_t total = tiles * kQT * D;
+    double* qrows = static_cast<double*>(work);
+    double* part_d = qrows + total;
+    int32_t* part_v = reinterpret_cast<int32_t*>(part_d + m * S * kp);
+    // with a row list the batch is a part of the list, else of the queries
+    const int32_t* qs = rows ? queries : queries + i;
+    const int32_t* rs = rows ? rows + i : nullptr;
+    int32_t* ids = rows ? out_ids : out_ids + i * k;
+    double* dist = rows ? out_dist : out_dist + i * k;
+    k_knn_query_rows<<<(unsigned)((total + kBlock - 1) / kBlock), kBlock, 0, s>>>(
+        qtheta, D, qs, rs, m, total, qrows);
+    k_knn_fp64<<<dim3((unsigned)tiles, (unsigned)S), kBlock, lds, s>>>(
+        theta, n, D, qrows, exclude_self ? 1 : 0, qs, rs, m, kp, cap, part_d, part_v);
+    k_knn_merge<<<(unsigned)m, kBlock, 0, s>>>(part_d, part_v, (int32_t)(S * kp), kp, k, rs, ids,
+                                               dist);
+    e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+  }
+  return 0;
 }
 
 }  // namespace panther

@@ -15,10 +15,6 @@
 using namespace panther;
 
 namespace panther {
-size_t knn_fp64_lds(int D);
-int launch_knn_fp64(const float* theta, int32_t n, int32_t D, const float* qtheta,
-                    bool exclude_self, const int32_t* queries, const int32_t* rows, int64_t nq,
-                    int32_t k, int32_t* out_ids, double* out_dist, hipStream_t s);
 int run_pp_bf16(panther_ctx* c, Lane* lane, const int32_t* dq, int64_t nq, int32_t D, int32_t k,
                 int32_t* d_ids, double* d_dist, hipStream_t s, const float* qtheta);
 }  // namespace panther
@@ -145,8 +141,10 @@ extern "C" int panther_pp_topk(panther_ctx* c, const int32_t* queries, int64_t n
 int run_pp(panther_ctx* c, Lane* lane, const int32_t* dq, int64_t nq, int32_t D, int32_t k,
            int32_t* d_ids, double* d_dist, hipStream_t s) {
   if (c->pp_form == PANTHER_PP_FP64) {
-    const int e = launch_knn_fp64(c->d_theta, c->n, D, c->d_theta, true, dq, nullptr, nq, k, d_ids,
-                                  d_dist, s);
+    const size_t need = knn_fp64_bytes(nq, c->n, D, k, c->num_cus);
+    TRY(ctx_ensure(c, lane->b_fbw, need, "pp fp64 knn"));
+    const int e = launch_knn_fp64(c->d_theta, c->n, D, c->d_theta, true, dq, nullptr, nq, k,
+                                  c->num_cus, lane->b_fbw.p, lane->b_fbw.cap, d_ids, d_dist, s);
     HIPTRY((hipError_t)e, "pp fp64 knn");
     return PANTHER_OK;
   }
@@ -211,8 +209,10 @@ extern "C" int panther_pp_topk_cross(panther_ctx* qc, panther_ctx* dbc, const in
   }
   stage_begin(dbc, 4, s);
   if (dbc->pp_form == PANTHER_PP_FP64) {
+    const size_t need = knn_fp64_bytes(nq, dbc->n, D, k, dbc->num_cus);
+    TRY(ctx_ensure(dbc, lane->b_fbw, need, "pp fp64 cross knn"));
     const int e = launch_knn_fp64(dbc->d_theta, dbc->n, D, qc->d_theta, false, dq, nullptr, nq, k,
-                                  d_ids, d_dist, s);
+                                  dbc->num_cus, lane->b_fbw.p, lane->b_fbw.cap, d_ids, d_dist, s);
     HIPTRY((hipError_t)e, "pp fp64 cross knn");
   } else {
     TRY(prepare_bf16(dbc, D, s));
