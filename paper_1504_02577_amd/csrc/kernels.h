@@ -105,7 +105,7 @@ void launch_query_lengths(const uint64_t* inv_ptr, const int32_t* queries, int64
                           uint64_t* out, hipStream_t s);
 
 // FP64 brute force (knn.hip): workspace bytes of a call, and the call.
-size_t knn_fp64_bytes(int64_t nq, int32_t n, int32_t D, int32_t k, int num_cus);
+size_t knn_fp64_bytes(int64_t nq, int32_t n, int32_t k, int num_cus);
 int launch_knn_fp64(const float* theta, int32_t n, int32_t D, const float* qtheta,
                     bool exclude_self, const int32_t* queries, const int32_t* rows, int64_t nq,
                     int32_t k, int num_cus, void* work, size_t work_bytes, int32_t* out_ids,

@@ -10,7 +10,7 @@
 // The cross-graph form takes the query rows from another graph's features
 // and ranks every row of this one (no row is the query itself).
 //
-// A work-group takes 16 queries and a slice of the rows, two rows per thread
+// A work-group takes 8 queries and a slice of the rows, four rows per thread
 // per round.  Each query keeps a candidate buffer in LDS with a threshold (the
 // kp-th best (d2, id) kept so far): candidates below it are appended, and a
 // buffer with more than kp entries is bitonic-sorted by one wavefront and cut
@@ -27,9 +27,9 @@ namespace panther {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kQT = 16;     // queries of a work-group's tile
-constexpr int kRows = 2;    // database rows per thread and round
-constexpr int kCols = 16;   // coordinates staged per step
+constexpr int kQT = 8;    // queries of a work-group's tile
+constexpr int kRows = 4;  // database rows per thread and round
+constexpr int kCols = 8;  // coordinates staged per step
 static_assert(kQT * kRows <= 32, "one pending bit per (query, row)");
 
 __device__ __forceinline__ void wave_sync_knn() {
@@ -71,44 +71,36 @@ __device__ void wave_sort_pairs(double* d, int32_t* v, int cnt) {
   }
 }
 
-// Query rows as doubles, coordinate-major inside each tile of kQT queries
-// (zeros past the last query): one coordinate of a tile is 128 consecutive
-// bytes, which the scan reads through the scalar cache.
-__global__ void __launch_bounds__(kBlock)
-k_knn_query_rows(const float* __restrict__ qtheta, int32_t D, const int32_t* __restrict__ queries,
-                 const int32_t* __restrict__ rows, int64_t nq, int64_t total,
-                 double* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= total) return;
-  const int64_t tile = i / ((int64_t)D * kQT);
-  const int32_t d = (int32_t)(i / kQT % D);
-  const int64_t q = tile * kQT + i % kQT;
-  out[i] = q < nq ? (double)qtheta[(int64_t)queries[rows ? rows[q] : q] * D + d] : 0.0;
-}
-
-// LDS of k_knn_fp64: kQT candidate buffers of `cap` pairs, the row stage.
+// LDS of k_knn_fp64: the tile's query rows, kQT candidate buffers of `cap`
+// pairs, the row stage.
 constexpr int kStagePitch = kCols + 1;
-__host__ __device__ constexpr size_t knn_scan_lds(int cap) {
-  return (sizeof(double) + sizeof(int32_t)) * (size_t)kQT * cap +
+__host__ __device__ constexpr size_t knn_scan_lds(int D, int cap) {
+  return sizeof(double) * (size_t)kQT * D +
+         (sizeof(double) + sizeof(int32_t)) * (size_t)kQT * cap +
          sizeof(float) * (size_t)kBlock * kRows * kStagePitch;
 }
-// Pairs a buffer holds: at least kp free places after every cut.
+// Pairs a buffer holds (a power of two, for its sort): at least kp free
+// places after every cut.
 __host__ __device__ constexpr int knn_scan_cap(int kp) { return kp < 64 ? 128 : 2 * kp; }
 
 // Bound: FP64 VALU, one subtraction and one fma per (query, row, coordinate),
-// at 16 lanes per clock and SIMD.  Each coordinate of the 16 queries comes as
-// scalars, each of the thread's two rows from LDS (the rows are staged 16
-// coordinates at a time by coalesced loads), so 64 FP64 instructions follow
-// two LDS reads.  The rows are split over grid.y so that few queries fill the
-// chip too: 301 queries x 262,144 rows of 100 coordinates took 43.1 ms on 19
-// work-groups that each scanned every row.
-__global__ void __launch_bounds__(kBlock)
-k_knn_fp64(const float* __restrict__ theta, int32_t n, int32_t D, const double* __restrict__ qrows,
+// at 16 lanes per clock and SIMD.  A coordinate of the 8 queries is read from
+// LDS by four broadcasts, each of the thread's four rows by one word (the rows
+// are staged 8 coordinates at a time by coalesced loads), so that 64 FP64
+// instructions follow eight LDS reads.  (Query coordinates as scalars waited
+// for every load: 3.0 ms for the case below.)  The rows are split over grid.y
+// so that few queries fill the chip too: 301 queries x 262,144 rows of 100
+// coordinates took 43.1 ms on 19 work-groups that each scanned every row, and
+// take 1.35 (the arithmetic alone 0.41).  Two waves per SIMD (a few spilled
+// words) beat one with 284 registers, 1.70 ms.
+__global__ void __launch_bounds__(kBlock, 2)
+k_knn_fp64(const float* __restrict__ theta, int32_t n, int32_t D, const float* __restrict__ qtheta,
            int32_t exclude_self, const int32_t* __restrict__ queries,
            const int32_t* __restrict__ rows, int64_t nq, int32_t kp, int32_t cap,
            double* __restrict__ part_d, int32_t* __restrict__ part_v) {
   extern __shared__ __align__(16) char lds[];
-  double* bd = reinterpret_cast<double*>(lds);            // [kQT][cap]
+  double* qv = reinterpret_cast<double*>(lds);               // [D][kQT]
+  double* bd = qv + (size_t)kQT * D;                         // [kQT][cap]
   int32_t* bv = reinterpret_cast<int32_t*>(bd + kQT * cap);  // [kQT][cap]
   float* stage = reinterpret_cast<float*>(bv + kQT * cap);   // [kRows * kBlock][kStagePitch]
   __shared__ uint32_t cnt[kQT];
@@ -125,11 +117,25 @@ k_knn_fp64(const float* __restrict__ theta, int32_t n, int32_t D, const double* 
     tau_v[i] = 0x7FFFFFFF;
   }
   __syncthreads();
-  typedef const __attribute__((address_space(4))) double* scalar_rows;
-  const scalar_rows qv = (scalar_rows)(uintptr_t)(qrows + q0 * D);
+  for (int i = threadIdx.x; i < kQT * D; i += kBlock) {
+    const int32_t q = qid[i / D];
+    qv[(i % D) * kQT + i / D] = q >= 0 ? (double)qtheta[(int64_t)q * D + i % D] : 0.0;
+  }
   // this slice's rounds of kRows * kBlock rows, interleaved over the slices
   constexpr int kRound = kRows * kBlock;
   const int64_t step = (int64_t)gridDim.y * kRound;
+  // one step's coordinates: kCols lanes take the consecutive ones of one row
+  constexpr int kStageLoads = kRound * kCols / kBlock;
+  float next[kStageLoads];
+  auto load_stage = [&](int64_t base, int d0) {
+    const int c = d0 + (int)threadIdx.x % kCols;
+#pragma unroll
+    for (int i = 0; i < kStageLoads; ++i) {
+      const int64_t v = base + i * (kBlock / kCols) + (int)threadIdx.x / kCols;
+      next[i] = v < n && c < D ? theta[v * D + c] : 0.f;
+    }
+  };
+  load_stage((int64_t)blockIdx.y * kRound, 0);
   for (int64_t base = (int64_t)blockIdx.y * kRound; base < n; base += step) {
     double acc[kRows][kQT];
 #pragma unroll
@@ -138,14 +144,16 @@ k_knn_fp64(const float* __restrict__ theta, int32_t n, int32_t D, const double* 
       for (int q = 0; q < kQT; ++q) acc[r][q] = 0.0;
     for (int d0 = 0; d0 < D; d0 += kCols) {
       const int nc = D - d0 < kCols ? D - d0 : kCols;
-      // kCols lanes take the consecutive coordinates of one row
-      const int c = threadIdx.x % kCols;
-#pragma unroll 8
-      for (int i = 0; i < kRound * kCols / kBlock; ++i) {
-        const int r = i * (kBlock / kCols) + (int)threadIdx.x / kCols;
-        const int64_t v = base + r;
-        stage[r * kStagePitch + c] = v < n && c < nc ? theta[v * D + d0 + c] : 0.f;
-      }
+#pragma unroll
+      for (int i = 0; i < kStageLoads; ++i)
+        stage[(i * (kBlock / kCols) + (int)threadIdx.x / kCols) * kStagePitch +
+              (int)threadIdx.x % kCols] = next[i];
+      // the loads of the next step (of the next round after the last one)
+      // are in flight during this one's arithmetic
+      if (d0 + kCols < D)
+        load_stage(base, d0 + kCols);
+      else
+        load_stage(base + step, 0);
       __syncthreads();
 #pragma unroll 2
       for (int d = 0; d < nc; ++d) {
@@ -153,9 +161,16 @@ k_knn_fp64(const float* __restrict__ theta, int32_t n, int32_t D, const double* 
 #pragma unroll
         for (int r = 0; r < kRows; ++r)
           x[r] = (double)stage[(r * kBlock + threadIdx.x) * kStagePitch + d];
+        double qd[kQT];
+#pragma unroll
+        for (int q = 0; q < kQT; q += 2) {
+          const double2 y = *reinterpret_cast<const double2*>(qv + (d0 + d) * kQT + q);
+          qd[q] = y.x;
+          qd[q + 1] = y.y;
+        }
 #pragma unroll
         for (int q = 0; q < kQT; ++q) {
-          const double qx = qv[(d0 + d) * kQT + q];
+          const double qx = qd[q];
 #pragma unroll
           for (int r = 0; r < kRows; ++r) {
             const double delta = qx - x[r];
@@ -202,7 +217,9 @@ k_knn_fp64(const float* __restrict__ theta, int32_t n, int32_t D, const double* 
       __syncthreads();
       for (int q = wid; q < kQT; q += kBlock / kWave) {
         const int c = (int)cnt[q] < cap ? (int)cnt[q] : cap;
-        if (c > kp) {
+        // a cut waits until its buffer is three quarters full (the first one
+        // only for kp pairs): one a round cost seven times the arithmetic
+        if (c > kp && (c > cap - cap / 4 || tau_v[q] == 0x7FFFFFFF)) {
           wave_sort_pairs(bd + q * cap, bv + q * cap, c);
           if (lane == 0) {
             cnt[q] = (uint32_t)kp;
@@ -215,7 +232,9 @@ k_knn_fp64(const float* __restrict__ theta, int32_t n, int32_t D, const double* 
   }
   for (int q = wid; q < kQT; q += kBlock / kWave) {
     if (qid[q] < 0) continue;
-    const int c = (int)cnt[q];  // <= kp
+    int c = (int)cnt[q];  // <= cap
+    wave_sort_pairs(bd + q * cap, bv + q * cap, c);
+    if (c > kp) c = kp;
     const int64_t o = ((q0 + q) * gridDim.y + blockIdx.y) * kp;
     for (int j = lane; j < kp; j += kWave) {
       part_d[o + j] = j < c ? bd[q * cap + j] : INFINITY;
@@ -473,43 +492,42 @@ int launch_knn_recompute(const float* theta, int32_t n, int32_t D, const float* 
   if (e != hipSuccess) return (int)e;
   if (ov == 0) return 0;
   // the candidate lists are done with: their place (48 KiB per listed query,
-  // more than a tile of query rows and one slice need) is the scan's
+  // more than one slice needs) is the scan's
   return launch_knn_fp64(theta, n, D, qtheta, exclude_self, queries, ov_list, (int64_t)ov, k,
                          num_cus, work, (sizeof(double) + sizeof(int32_t)) * (size_t)nr * kSelCap,
                          out_ids, out_dist, s);
 }
 
 namespace {
-// Queries of one launch of the FP64 form, and its workspace: query rows, then
-// per query S slices of kp pairs.
+// Queries of one launch of the FP64 form, and its workspace: per query S
+// slices of kp pairs.
 constexpr int64_t kFp64Batch = 32768;
-size_t fp64_bytes(int64_t nq, int32_t D, int64_t S, int kp) {
-  const size_t tiles = (size_t)((nq + kQT - 1) / kQT);
-  return sizeof(double) * tiles * kQT * D +
-         (sizeof(double) + sizeof(int32_t)) * (size_t)nq * S * kp;
+size_t fp64_bytes(int64_t nq, int64_t S, int kp) {
+  return (sizeof(double) + sizeof(int32_t)) * (size_t)nq * S * kp;
 }
 int pow2_at_least(int k) {
   int kp = 1;
   while (kp < k) kp <<= 1;
   return kp;
 }
-// Slices of the rows: four work-groups per CU where the queries' tiles alone
-// are fewer, each with at least four rounds of rows, and at most 4,096 pairs
-// per query to merge.
+// Slices of the rows: as many as give the two work-groups that a CU holds
+// (about 60 KB of LDS each) without starting a third, where the queries' tiles
+// alone are fewer; each with at least four rounds of rows, and at most 4,096
+// pairs per query to merge.
 int64_t fp64_slices(int64_t nq, int32_t n, int kp, int num_cus) {
   const int64_t tiles = (nq + kQT - 1) / kQT;
-  int64_t S = (4 * (int64_t)num_cus + tiles - 1) / tiles;
+  int64_t S = 2 * (int64_t)num_cus / tiles;
   S = std::min<int64_t>(S, (n + 4 * kRows * kBlock - 1) / (4 * kRows * kBlock));
   S = std::min<int64_t>(S, 4096 / kp);
   return std::max<int64_t>(S, 1);
 }
 }  // namespace
 
-size_t knn_fp64_bytes(int64_t nq, int32_t n, int32_t D, int32_t k, int num_cus) {
+size_t knn_fp64_bytes(int64_t nq, int32_t n, int32_t k, int num_cus) {
   if (nq <= 0) return 0;
   const int kp = pow2_at_least(k);
   nq = std::min(nq, kFp64Batch);
-  return fp64_bytes(nq, D, fp64_slices(nq, n, kp, num_cus), kp);
+  return fp64_bytes(nq, fp64_slices(nq, n, kp, num_cus), kp);
 }
 
 // qtheta: the queries' feature rows (theta itself for one graph, the other
@@ -517,38 +535,34 @@ size_t knn_fp64_bytes(int64_t nq, int32_t n, int32_t D, int32_t k, int num_cus) 
 // null): the call answers queries[rows[i]] into output row rows[i] for
 // i < nq, instead of queries[i] into row i.  work: at least
 // knn_fp64_bytes(nq, ...) bytes, or less: then fewer slices or queries go at
-// a time (at least one tile and one slice must fit).
+// a time (at least one slice of one query must fit).
 int launch_knn_fp64(const float* theta, int32_t n, int32_t D, const float* qtheta,
                     bool exclude_self, const int32_t* queries, const int32_t* rows, int64_t nq,
                     int32_t k, int num_cus, void* work, size_t work_bytes, int32_t* out_ids,
                     double* out_dist, hipStream_t s) {
   const int kp = pow2_at_least(k);
   const int cap = knn_scan_cap(kp);
-  const size_t lds = knn_scan_lds(cap);
+  const size_t lds = knn_scan_lds(D, cap);
   hipError_t e = hipFuncSetAttribute((const void*)k_knn_fp64,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return (int)e;
   int64_t most = std::min(nq, kFp64Batch);
-  while (most > 1 && fp64_bytes(most, D, 1, kp) > work_bytes) most = (most + 1) / 2;
-  if (most > 0 && fp64_bytes(most, D, 1, kp) > work_bytes) return (int)hipErrorInvalidValue;
+  while (most > 1 && fp64_bytes(most, 1, kp) > work_bytes) most = (most + 1) / 2;
+  if (most > 0 && fp64_bytes(most, 1, kp) > work_bytes) return (int)hipErrorInvalidValue;
   for (int64_t i = 0; i < nq; i += most) {
     const int64_t m = std::min(most, nq - i);
     int64_t S = fp64_slices(m, n, kp, num_cus);
-    while (S > 1 && fp64_bytes(m, D, S, kp) > work_bytes) --S;
+    while (S > 1 && fp64_bytes(m, S, kp) > work_bytes) --S;
     const int64_t tiles = (m + kQT - 1) / kQT;
-    const int64_t total = tiles * kQT * D;
-    double* qrows = static_cast<double*>(work);
-    double* part_d = qrows + total;
+    double* part_d = static_cast<double*>(work);
     int32_t* part_v = reinterpret_cast<int32_t*>(part_d + m * S * kp);
     // with a row list the batch is a part of the list, else of the queries
     const int32_t* qs = rows ? queries : queries + i;
     const int32_t* rs = rows ? rows + i : nullptr;
     int32_t* ids = rows ? out_ids : out_ids + i * k;
     double* dist = rows ? out_dist : out_dist + i * k;
-    k_knn_query_rows<<<(unsigned)((total + kBlock - 1) / kBlock), kBlock, 0, s>>>(
-        qtheta, D, qs, rs, m, total, qrows);
     k_knn_fp64<<<dim3((unsigned)tiles, (unsigned)S), kBlock, lds, s>>>(
-        theta, n, D, qrows, exclude_self ? 1 : 0, qs, rs, m, kp, cap, part_d, part_v);
+        theta, n, D, qtheta, exclude_self ? 1 : 0, qs, rs, m, kp, cap, part_d, part_v);
     k_knn_merge<<<(unsigned)m, kBlock, 0, s>>>(part_d, part_v, (int32_t)(S * kp), kp, k, rs, ids,
                                                dist);
     e = hipGetLastError();

@@ -141,7 +141,7 @@ extern "C" int panther_pp_topk(panther_ctx* c, const int32_t* queries, int64_t n
 int run_pp(panther_ctx* c, Lane* lane, const int32_t* dq, int64_t nq, int32_t D, int32_t k,
            int32_t* d_ids, double* d_dist, hipStream_t s) {
   if (c->pp_form == PANTHER_PP_FP64) {
-    const size_t need = knn_fp64_bytes(nq, c->n, D, k, c->num_cus);
+    const size_t need = knn_fp64_bytes(nq, c->n, k, c->num_cus);
     TRY(ctx_ensure(c, lane->b_fbw, need, "pp fp64 knn"));
     const int e = launch_knn_fp64(c->d_theta, c->n, D, c->d_theta, true, dq, nullptr, nq, k,
                                   c->num_cus, lane->b_fbw.p, lane->b_fbw.cap, d_ids, d_dist, s);
@@ -209,7 +209,7 @@ extern "C" int panther_pp_topk_cross(panther_ctx* qc, panther_ctx* dbc, const in
   }
   stage_begin(dbc, 4, s);
   if (dbc->pp_form == PANTHER_PP_FP64) {
-    const size_t need = knn_fp64_bytes(nq, dbc->n, D, k, dbc->num_cus);
+    const size_t need = knn_fp64_bytes(nq, dbc->n, k, dbc->num_cus);
     TRY(ctx_ensure(dbc, lane->b_fbw, need, "pp fp64 cross knn"));
     const int e = launch_knn_fp64(dbc->d_theta, dbc->n, D, qc->d_theta, false, dq, nullptr, nq, k,
                                   dbc->num_cus, lane->b_fbw.p, lane->b_fbw.cap, d_ids, d_dist, s);
