@@ -25,13 +25,11 @@
 
 #include <algorithm>
 #include <array>
-#include <chrono>
 #include <cstring>
 #include <cstdio>
 #include <cstdlib>
 #include <sstream>
 #include <string>
-#include <thread>
 #include <vector>
 
 #include "../../include/panther.h"
@@ -468,14 +466,13 @@ __global__ void __launch_bounds__(kWaveBlock) k_topk_waves(BatchArgs A) {
 // ---- device planning of large batches ----
 // Digit of query i in the plan's order: tier B classes 64..0 (digits
 // 0..64), tier A classes 64..0 (65..129), then the hubs by class, 64..0
-// (130..194); a stable sort by digit gives the host planner's tier order,
-// and the hubs longest class first (the host planner orders them exactly
-// by length, so that repeated queries of one vertex run side by side; the
-// batches planned here, such as a pass over every vertex, rarely repeat
-// one).  Also writes the pair count the sort reads and the query index as
+// (130..194), then the repeated queries (195), which no tier sees; a stable
+// sort by digit gives the host planner's order.  Also writes the pair count
+// the sort reads and the query index as
 // the sort's value.
 constexpr uint32_t kHubDigit = 130;
-constexpr uint32_t kDigits = kHubDigit + 65;
+constexpr uint32_t kRepeatDigit = kHubDigit + 65;
+constexpr uint32_t kDigits = kRepeatDigit + 1;
 __global__ void k_plan_digits(const uint64_t* __restrict__ qlen, int64_t nq, uint64_t LA,
                               uint64_t LB, uint32_t* __restrict__ keys,
                               uint32_t* __restrict__ vals, uint64_t* __restrict__ nnz) {
@@ -484,7 +481,9 @@ __global__ void k_plan_digits(const uint64_t* __restrict__ qlen, int64_t nq, uin
   if (i >= nq) return;
   const uint64_t L = qlen[i];
   const uint32_t cl = L ? 64u - (uint32_t)__clzll((long long)L) : 0u;
-  keys[i] = (L > LB ? kHubDigit : (L > LA ? 0u : 65u)) + (64u - cl);
+  keys[i] = L == kRepeated
+                ? kRepeatDigit
+                : (L > LB ? kHubDigit : (L > LA ? 0u : 65u)) + (64u - cl);
   vals[i] = (uint32_t)i;
 }
 
@@ -566,6 +565,7 @@ struct Plan {
   bool run_kernel = false;
   int stride = 0;  // path row stride: selects the kernel specialisations
   std::vector<HubArgs> hub;
+  bool repeats = false;  // some queries are copies of others (not part of the launch)
   bool operator==(const Plan& o) const {
     if (run_kernel != o.run_kernel || stride != o.stride || hub.size() != o.hub.size())
       return false;
@@ -664,7 +664,6 @@ struct BatchState {
   Plan last_plan;
   int last_block = 0, last_grid = 0;
   size_t last_lds = 0;
-  std::vector<std::pair<uint64_t, int32_t>> hub_sort_tmp;  // host scratch of the hub order
   std::string tune_key;
   bool no_tune = false;  // serving lanes reuse a stored or default configuration
   bool no_fork = false;  // serving lanes: one stream each (lanes overlap one another)
@@ -997,7 +996,7 @@ static int launch_batched(panther_ctx* c, BatchState* b, const BatchConfig& cfg,
   return ctx_hip(c, enqueue(c, b, P, fn, grid, cfg.block, lay.lds, s), "batched kernel");
 }
 
-// Splits the hub queries (longest first) into chunks whose staging fits a
+// Splits the hub queries (longest class first) into chunks whose staging fits a
 // memory budget, and fills the device buffers and per-chunk arguments.
 static int plan_hubs(panther_ctx* c, BatchState* b,
                      const std::vector<std::pair<uint64_t, int32_t>>& C,
@@ -1019,8 +1018,7 @@ static int plan_hubs(panther_ctx* c, BatchState* b,
   }
   // staging bytes per occurrence slot: row order, bucket order
   const size_t budget = b->hub_budget_forced ? b->hub_budget_forced : b->hub_budget;
-  // the longest hub leads its class (exact order) or its class leads
-  // (device-planned batches): it is among the first class's entries
+  // the longest hub is in the first class
   uint64_t max_L = 0;
   {
     const auto cls = [](uint64_t L) { return 64 - __builtin_clzll(L); };
@@ -1154,69 +1152,18 @@ static int plan_hubs(panther_ctx* c, BatchState* b,
   return PANTHER_OK;
 }
 
-// Orders hub queries by list length, longest first; equal lengths keep
-// their order (ascending batch index).  A stable LSD radix sort on the
-// length's 11-bit digits, complemented so that longer lists come first:
-// linear in the number of hubs (a comparison sort of the tens of thousands
-// of hubs of an R-MAT 24 batch took milliseconds of host time).
-// Large sets split each pass over host threads: thread t takes a
-// contiguous range, and its run of digit d starts after every earlier
-// thread's run of d (positions are prefix sums in (digit, thread) order), so
-// the result is the one-thread order.
-static void sort_hubs_longest_first(std::vector<std::pair<uint64_t, int32_t>>& C,
-                                    std::vector<std::pair<uint64_t, int32_t>>& tmp) {
-  if (C.size() < 2) return;
-  uint64_t max_L = 0;
-  for (const auto& x : C) max_L = std::max(max_L, x.first);
-  const int bits = max_L ? 64 - __builtin_clzll(max_L) : 0;
-  constexpr int kDigit = 11;
-  constexpr uint64_t kMask = (1u << kDigit) - 1u;
-  tmp.resize(C.size());
-  const size_t n = C.size();
-  const int nth = n >= ((size_t)1 << 16) ? 8 : 1;
-  std::vector<std::vector<size_t>> pos(nth, std::vector<size_t>(kMask + 1));
-  auto lo_of = [&](int t) { return n * (size_t)t / (size_t)nth; };
-  auto in_threads = [&](auto&& fn) {
-    std::vector<std::thread> th;
-    for (int t = 1; t < nth; ++t) th.emplace_back(fn, t);
-    fn(0);
-    for (auto& x : th) x.join();
-  };
-  for (int sh = 0; sh < bits; sh += kDigit) {
-    in_threads([&](int t) {
-      auto& pt = pos[t];
-      std::fill(pt.begin(), pt.end(), (size_t)0);
-      for (size_t i = lo_of(t), e = lo_of(t + 1); i < e; ++i)
-        ++pt[kMask - ((C[i].first >> sh) & kMask)];
-    });
-    size_t run = 0;
-    for (uint64_t d = 0; d <= kMask; ++d)
-      for (int t = 0; t < nth; ++t) {
-        const size_t c = pos[t][d];
-        pos[t][d] = run;
-        run += c;
-      }
-    in_threads([&](int t) {
-      auto& pt = pos[t];
-      for (size_t i = lo_of(t), e = lo_of(t + 1); i < e; ++i)
-        tmp[pt[kMask - ((C[i].first >> sh) & kMask)]++] = C[i];
-    });
-    C.swap(tmp);
-  }
-}
-
 // Device planning of a large batch: the digits of k_plan_digits sorted by
 // one stable pass of the index's radix sort (8-bit digit, query index as
 // the value) straight into d_items, so the tier items need no host pass and
 // no upload.  Only the digit starts and the hubs' lengths come back.
 // Fills nB, need (tier items), cntA (tier A items per length class) and C
-// (the hubs, in batch order).
+// (the hubs, in batch order), and says whether queries are repeated.
 bool batched_plan_on_device(int64_t nq) { return nq >= ((int64_t)1 << 20); }
 
 static int plan_on_device(panther_ctx* c, BatchState* b, const uint64_t* dqlen, int64_t nq,
                           uint64_t LA, uint64_t LB, hipStream_t s, bool with_hubs, size_t* nB,
                           size_t* need, std::array<size_t, 65>& cntA,
-                          std::vector<std::pair<uint64_t, int32_t>>* C) {
+                          std::vector<std::pair<uint64_t, int32_t>>* C, bool* repeats) {
   const uint64_t n = (uint64_t)nq;
   const uint64_t ntiles = radix_tiles_pairs(n);
   const size_t nh = (size_t)256 * ntiles;
@@ -1253,7 +1200,8 @@ static int plan_on_device(panther_ctx* c, BatchState* b, const uint64_t* dqlen, 
   *nB = (size_t)sp[65];
   *need = (size_t)sp[kHubDigit];
   for (int c2 = 0; c2 <= 64; ++c2) cntA[c2] = (size_t)(sp[65 + (64 - c2) + 1] - sp[65 + (64 - c2)]);
-  const size_t nC = (size_t)(sp[kDigits] - sp[kHubDigit]);
+  const size_t nC = (size_t)(sp[kRepeatDigit] - sp[kHubDigit]);
+  *repeats = sp[kDigits] != sp[kRepeatDigit];
   C->clear();
   if (!with_hubs || !nC) return PANTHER_OK;
   const int32_t* hub_idx = b->d_items + sp[kHubDigit];
@@ -1294,15 +1242,11 @@ static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int
   if (b->tier_b_override >= 0) LB = std::min(LB, (uint64_t)b->tier_b_override);
   // the wave-tier sort buffer holds TA/2 keys and the block selection keeps
   // at most kCand keys without radix narrowing; both are covered by the
-  // load bound T * L <= table / 2.  The LDS tiers are ordered by
-  // power-of-two length class, longest first (enough for load balance):
-  // a counting sort over (tier, class) in two passes, written straight
-  // into the pinned upload buffer; hubs go exactly longest-first (so that
-  // repeated queries of one vertex run side by side and share its rows in
-  // the caches), by a stable radix sort on the length.
-  // Large batches split both passes over host threads (each thread takes a
-  // contiguous range of queries; positions are prefix sums over (tier,
-  // class, thread), so the order is the same as one thread's).
+  // load bound T * L <= table / 2.  Every tier is ordered by power-of-two
+  // length class, longest first (enough for load balance): a counting sort in
+  // two passes, the LDS tiers' items written straight into the pinned upload
+  // buffer.  (Hubs were ordered by exact length, which brought the repeats of
+  // a vertex together; they are answered once now.)
   auto cls = [](uint64_t L) { return L ? 64 - __builtin_clzll(L) : 0; };
   std::array<size_t, 65> cntA{};  // tier A items per length class
   size_t nB = 0, need = 0;
@@ -1310,56 +1254,30 @@ static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int
   int st;
   const bool on_device = qlen == nullptr;
   if (on_device) {
-    if ((st = plan_on_device(c, b, dqlen, nq, LA, LB, s, with_hubs, &nB, &need, cntA, &C)))
+    if ((st = plan_on_device(c, b, dqlen, nq, LA, LB, s, with_hubs, &nB, &need, cntA, &C,
+                             &out->repeats)))
       return st;
   } else {
-    const int nth = nq >= (int64_t)1 << 22 ? 16 : (nq >= (int64_t)1 << 20 ? 8 : 1);
-    std::vector<std::array<size_t, 131>> cnt(nth);  // [tier 0: 0..64, tier 1: 65..129, hubs: 130]
-    auto range = [&](int t, int64_t& lo, int64_t& hi) {
-      lo = nq * t / nth;
-      hi = nq * (t + 1) / nth;
-    };
-    auto count_part = [&](int t) {
-      auto& ct = cnt[t];
-      ct.fill(0);
-      int64_t lo, hi;
-      range(t, lo, hi);
-      for (int64_t i = lo; i < hi; ++i) {
-        const uint64_t L = qlen[i];
-        if (L > LB)
-          ++ct[130];
-        else
-          ++ct[(L > LA ? 0 : 65) + cls(L)];  // tier 0: work-group (B), 1: wave (A)
-      }
-    };
-    auto run_parts = [&](auto&& fn) {
-      if (nth == 1) {
-        fn(0);
-        return;
-      }
-      std::vector<std::thread> th;
-      for (int t = 1; t < nth; ++t) th.emplace_back(fn, t);
-      fn(0);
-      for (auto& x : th) x.join();
-    };
-    run_parts(count_part);
-    // start of each (bucket, thread): buckets in order tier 0 classes 64..0,
-    // tier 1 classes 64..0
-    std::vector<std::array<size_t, 130>> pos(nth);
-    size_t nC = 0;
-    for (int tier = 0; tier < 2; ++tier) {
-      for (int c2 = 64; c2 >= 0; --c2) {
-        const int bk = tier * 65 + c2;
-        for (int t = 0; t < nth; ++t) {
-          pos[t][bk] = need;
-          need += cnt[t][bk];
-        }
-      }
-      if (tier == 0) nB = need;
+    // bucket of a query: tier B classes 64..0, tier A classes 64..0, hub
+    // classes 64..0 (repeated queries have none)
+    auto bucket = [&](uint64_t L) { return (L > LB ? 130 : (L > LA ? 0 : 65)) + 64 - cls(L); };
+    std::array<size_t, 195> pos{};
+    out->repeats = false;
+    for (int64_t i = 0; i < nq; ++i) {
+      if (qlen[i] == kRepeated)
+        out->repeats = true;
+      else
+        ++pos[bucket(qlen[i])];
     }
-    for (int t = 0; t < nth; ++t) nC += cnt[t][130];
-    for (int c2 = 0; c2 <= 64; ++c2)
-      for (int t = 0; t < nth; ++t) cntA[c2] += cnt[t][65 + c2];
+    for (int c2 = 0; c2 <= 64; ++c2) cntA[c2] = pos[65 + 64 - c2];
+    size_t run = 0;
+    for (int bk = 0; bk < 195; ++bk) {
+      if (bk == 65) nB = run;
+      if (bk == 130) need = run;
+      const size_t m = pos[bk];
+      pos[bk] = run;
+      run += m;
+    }
     // the pinned staging of the previous plan must have been consumed
     if (b->upload_pending) {
       if ((st = ctx_hip(c, hipEventSynchronize(b->uploaded), "batch plan"))) return st;
@@ -1368,27 +1286,16 @@ static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int
     if (need && (st = pinned_ensure(c, b->pin_items, sizeof(int32_t) * need, "batch plan")))
       return st;
     int32_t* items = static_cast<int32_t*>(b->pin_items.p);
-    if (with_hubs) C.resize(nC);
-    std::vector<size_t> cpos(nth);
-    for (int t = 0, run = 0; t < nth; ++t) {
-      cpos[t] = run;
-      run += (int)cnt[t][130];
+    if (with_hubs) C.resize(run - need);
+    for (int64_t i = 0; i < nq; ++i) {
+      const uint64_t L = qlen[i];
+      if (L == kRepeated || (L > LB && !with_hubs)) continue;
+      const size_t at = pos[bucket(L)]++;
+      if (L > LB)
+        C[at - need] = {L, (int32_t)i};
+      else
+        items[at] = (int32_t)i;
     }
-    auto scatter_part = [&](int t) {
-      auto& pt = pos[t];
-      size_t cp = cpos[t];
-      int64_t lo, hi;
-      range(t, lo, hi);
-      for (int64_t i = lo; i < hi; ++i) {
-        const uint64_t L = qlen[i];
-        if (L > LB) {
-          if (with_hubs) C[cp++] = {L, (int32_t)i};
-        } else {
-          items[pt[(L > LA ? 0 : 65) + cls(L)]++] = (int32_t)i;
-        }
-      }
-    };
-    run_parts(scatter_part);
   }
   // tier A phases: class c (lengths below 2^c) runs in groups of G lanes
   // when T * (2^c - 1) fits half of the group's table (kWaveTA * G / 64);
@@ -1408,7 +1315,6 @@ static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int
     if ((st = ctx_hip(c, hipEventSynchronize(b->uploaded), "batch plan"))) return st;
     b->upload_pending = false;
   }
-  if (!on_device) sort_hubs_longest_first(C, b->hub_sort_tmp);
   st = plan_hubs(c, b, C, dq, k, cfg.bucket_bias, d_ids, d_counts, d_len, theta, s, &out->hub);
   if (st) return st;
   host_items->clear();
@@ -1515,7 +1421,7 @@ size_t lane_device_bytes(const Lane* lane) {
   size_t t = 0;
   for (const DevBuf* d : {&lane->b_qlen, &lane->b_pool, &lane->b_out, &lane->b_stats, &lane->b_q,
                           &lane->b_qrows, &lane->b_fb, &lane->b_fbw, &lane->b_qsort,
-                          &lane->b_qsort_tmp})
+                          &lane->b_qsort_tmp, &lane->b_rep, &lane->b_seen})
     t += d->p ? d->cap : 0;
   const BatchState* b = lane->batch;
   if (!b) return t;
@@ -1634,7 +1540,7 @@ int run_batched(panther_ctx* c, Lane* lane, const int32_t* dq, const uint64_t* q
         // already takes long)
         bool near_hubs = false;
         if (nq <= kStage2MaxQueries)  // (qlen is on the host for such batches)
-          for (int64_t i = 0; i < nq && !near_hubs; ++i) near_hubs = qlen[i] > lo;
+          for (int64_t i = 0; i < nq && !near_hubs; ++i) near_hubs = qlen[i] > lo && qlen[i] != kRepeated;
         if (near_hubs) {
           best = 1e30f;
           const BatchConfig base = best_cfg;
@@ -1665,5 +1571,10 @@ int run_batched(panther_ctx* c, Lane* lane, const int32_t* dq, const uint64_t* q
                 &args, &items);
   if (st) return st;
   // the plan's pinned staging is guarded by b->uploaded; nothing here waits
-  return launch_batched(c, b, b->cfg, args, s, true);
+  if ((st = launch_batched(c, b, b->cfg, args, s, true))) return st;
+  if (args.repeats) {
+    launch_copy_rows(static_cast<const int32_t*>(lane->b_rep.p), nq, k, d_ids, d_counts, d_len, s);
+    return ctx_hip(c, hipGetLastError(), "repeated queries");
+  }
+  return PANTHER_OK;
 }

@@ -103,6 +103,17 @@ void launch_iota(int32_t* out, int32_t n, hipStream_t s);
 void launch_zero_u32(uint32_t* p, uint64_t n, hipStream_t s);
 void launch_query_lengths(const uint64_t* inv_ptr, const int32_t* queries, int64_t nq,
                           uint64_t* out, hipStream_t s);
+// The same with repeated queries marked: one position (below 2^31) of every
+// queried vertex stands for it, rep[i] is that position, and the others get
+// length kRepeated.  seen: a word per vertex, zero at first, and call a
+// number above every earlier one (the first is 1).
+constexpr uint64_t kRepeated = ~0ull;
+void launch_query_lengths_once(const uint64_t* inv_ptr, const int32_t* queries, int64_t nq,
+                               unsigned long long* seen, uint32_t call, int32_t* rep,
+                               uint64_t* out, hipStream_t s);
+// Output rows of repeated queries copied from those of rep[i].
+void launch_copy_rows(const int32_t* rep, int64_t nq, int32_t k, int32_t* ids, uint32_t* counts,
+                      int32_t* len, hipStream_t s);
 
 // FP64 brute force (knn.hip): workspace bytes of a call, and the call.
 size_t knn_fp64_bytes(int64_t nq, int32_t n, int32_t k, int num_cus);

@@ -45,6 +45,10 @@ struct Lane {
   int64_t stat_fallback = 0;  // of them, recomputed exactly (boundary not certified)
   double stat_scanned = 0.0;  // (query, row) products of its pool pass / (queries * vertices)
   PinnedBuf h_qlen;  // path-list lengths of the last call's queries
+  // repeated queries of a batch (query_lengths with `once`): the position
+  // that stands for each query's vertex, and per vertex {call, position}
+  DevBuf b_rep, b_seen;
+  uint32_t seen_call = 0;
   bool have_stats = false;
   double max_rel_err = 0.0;
   double mean_pre_recall = 0.0;
@@ -137,8 +141,10 @@ void pinned_release(PinnedBuf& b);
 // Path-list lengths of the queries, gathered on the device into the lane's
 // b_qlen and, with to_host, copied back to its pinned buffer (*len points
 // there until the lane's next call; nullptr without to_host).
+// With once, repeated queries are marked (length kRepeated, lane->b_rep):
+// run_batched then answers each vertex once and copies the other rows.
 int query_lengths(panther_ctx* c, Lane* lane, const int32_t* dq, int64_t nq, hipStream_t s,
-                  const uint64_t** len, bool to_host = true);
+                  const uint64_t** len, bool to_host = true, bool once = false);
 void ctx_free(void* p);
 // Stage timing: stage i is bracketed by events 2i and 2i+1.
 void stage_begin(panther_ctx* c, int stage, hipStream_t s);

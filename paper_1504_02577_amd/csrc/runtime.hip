@@ -746,17 +746,39 @@ void free_lane(Lane* lane) {
   free_batch_state(lane);
   for (DevBuf* b : {&lane->b_qlen, &lane->b_pool, &lane->b_out, &lane->b_stats, &lane->b_q,
                     &lane->b_qrows, &lane->b_fb, &lane->b_fbw, &lane->b_qsort,
-                    &lane->b_qsort_tmp})
+                    &lane->b_qsort_tmp, &lane->b_rep, &lane->b_seen})
     ctx_release(*b);
   pinned_release(lane->h_qlen);
   lane->have_stats = false;
 }
 
 int query_lengths(panther_ctx* c, Lane* lane, const int32_t* dq, int64_t nq, hipStream_t s,
-                  const uint64_t** len, bool to_host) {
+                  const uint64_t** len, bool to_host, bool once) {
   const size_t bytes = sizeof(uint64_t) * (size_t)std::max<int64_t>(nq, 1);
   TRY(ctx_ensure(c, lane->b_qlen, bytes, "query lengths"));
-  launch_query_lengths(c->d_inv_ptr, dq, nq, static_cast<uint64_t*>(lane->b_qlen.p), s);
+  uint64_t* qlen = static_cast<uint64_t*>(lane->b_qlen.p);
+  // without room for the scratch every query is answered by itself
+  if (once && nq > 1 && nq < ((int64_t)1 << 31) &&
+      ctx_ensure(c, lane->b_rep, sizeof(int32_t) * (size_t)nq, "repeated queries") ==
+          PANTHER_OK) {
+    const size_t words = sizeof(uint64_t) * (size_t)c->n;
+    const bool grown = !lane->b_seen.p || lane->b_seen.cap < words;
+    if (!grown || ctx_ensure(c, lane->b_seen, words, "repeated queries") == PANTHER_OK) {
+      if (grown || lane->seen_call == ~0u) {
+        HIPTRY(hipMemsetAsync(lane->b_seen.p, 0, lane->b_seen.cap, s), "repeated queries");
+        lane->seen_call = 0;
+      }
+      ++lane->seen_call;
+      launch_query_lengths_once(c->d_inv_ptr, dq, nq,
+                                static_cast<unsigned long long*>(lane->b_seen.p),
+                                lane->seen_call, static_cast<int32_t*>(lane->b_rep.p), qlen, s);
+    } else {
+      once = false;
+    }
+  } else {
+    once = false;
+  }
+  if (!once) launch_query_lengths(c->d_inv_ptr, dq, nq, qlen, s);
   HIPTRY(hipGetLastError(), "query lengths");
   if (!to_host) {
     *len = nullptr;
@@ -867,7 +889,8 @@ extern "C" int panther_topk_similar(panther_ctx* c, const int32_t* queries, int6
   stage_begin(c, 2, s);
   const uint64_t* qlen = nullptr;
   TRY(query_lengths(c, &c->lane0, dq, nq, s, &qlen,
-                    c->topk_form == PANTHER_FORM_PLAIN || !batched_plan_on_device(nq)));
+                    c->topk_form == PANTHER_FORM_PLAIN || !batched_plan_on_device(nq),
+                    c->topk_form != PANTHER_FORM_PLAIN));
   if (c->topk_form == PANTHER_FORM_PLAIN) {
     TopkScratch sc{c->d_cnt, c->d_touched, c->d_ctl};
     for (int64_t i = 0; i < nq; ++i) {

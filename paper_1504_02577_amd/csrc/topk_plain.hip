@@ -100,14 +100,48 @@ k_topk_plain(const int32_t* __restrict__ qp, int32_t n, const uint64_t* __restri
   }
 }
 
+// Path-list lengths of the queries.  With rep, a vertex repeated in the batch
+// is answered once: one of its positions, the first to reach seen[vertex],
+// stands for it (rep[i] == i), and the others get that position and the
+// length kRepeated (the planner leaves them out, and their rows are copied).
+// seen holds {call number, position} per vertex, so it needs no clearing and
+// the lengths no launch of their own.
 __global__ void k_query_lengths(const uint64_t* __restrict__ inv_ptr,
                                 const int32_t* __restrict__ queries, int64_t nq,
-                                uint64_t* __restrict__ out) {
+                                unsigned long long* __restrict__ seen, uint32_t call,
+                                int32_t* __restrict__ rep, uint64_t* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i < nq) {
-    const int32_t q = queries[i];
-    out[i] = inv_ptr[q + 1] - inv_ptr[q];
+  if (i >= nq) return;
+  const int32_t q = queries[i];
+  const uint64_t L = inv_ptr[q + 1] - inv_ptr[q];
+  if (!rep) {
+    out[i] = L;
+    return;
   }
+  const unsigned long long mine = ((unsigned long long)call << 32) | (uint32_t)i;
+  unsigned long long old = __hip_atomic_load(&seen[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // an entry of this call stays; an older one is replaced by exactly one
+  if ((uint32_t)(old >> 32) != call) old = atomicCAS(&seen[q], old, mine);
+  const bool first = (uint32_t)(old >> 32) != call;
+  rep[i] = first ? (int32_t)i : (int32_t)(uint32_t)old;
+  out[i] = first ? L : kRepeated;
+}
+
+// Rows of repeated queries from the rows of the positions that stand for
+// them, one wavefront per query.
+__global__ void __launch_bounds__(kBlock)
+k_copy_rows(const int32_t* __restrict__ rep, int64_t nq, int32_t k, int32_t* __restrict__ ids,
+            uint32_t* __restrict__ counts, int32_t* __restrict__ len) {
+  const int64_t i = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+  if (i >= nq) return;
+  const int64_t r = rep[i];
+  if (r == i) return;
+  const int lane = threadIdx.x & (kWave - 1);
+  for (int j = lane; j < k; j += kWave) {
+    ids[i * k + j] = ids[r * k + j];
+    counts[i * k + j] = counts[r * k + j];
+  }
+  if (lane == 0) len[i] = len[r];
 }
 
 }  // namespace
@@ -139,9 +173,22 @@ void launch_zero_u32(uint32_t* p, uint64_t n, hipStream_t s) {
 
 void launch_query_lengths(const uint64_t* inv_ptr, const int32_t* queries, int64_t nq,
                           uint64_t* out, hipStream_t s) {
+  launch_query_lengths_once(inv_ptr, queries, nq, nullptr, 0u, nullptr, out, s);
+}
+
+void launch_query_lengths_once(const uint64_t* inv_ptr, const int32_t* queries, int64_t nq,
+                               unsigned long long* seen, uint32_t call, int32_t* rep,
+                               uint64_t* out, hipStream_t s) {
   if (nq > 0)
-    k_query_lengths<<<(unsigned)((nq + kBlock - 1) / kBlock), kBlock, 0, s>>>(inv_ptr, queries, nq,
-                                                                            out);
+    k_query_lengths<<<(unsigned)((nq + kBlock - 1) / kBlock), kBlock, 0, s>>>(
+        inv_ptr, queries, nq, seen, call, rep, out);
+}
+
+void launch_copy_rows(const int32_t* rep, int64_t nq, int32_t k, int32_t* ids, uint32_t* counts,
+                      int32_t* len, hipStream_t s) {
+  const int64_t per = kBlock / kWave;
+  if (nq > 0)
+    k_copy_rows<<<(unsigned)((nq + per - 1) / per), kBlock, 0, s>>>(rep, nq, k, ids, counts, len);
 }
 
 void launch_topk_plain(int stride, const int32_t* qp, int32_t n, const uint64_t* inv_ptr,
