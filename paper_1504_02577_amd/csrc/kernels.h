@@ -48,6 +48,10 @@ void launch_guide32(const int32_t* row_ptr, const int32_t* tile_row, const VRec*
 // Wider sums: inclusive row prefixes (pfx may be sum + 1: in place).
 void launch_prefix64(const int32_t* row_ptr, const int32_t* tile_row, const uint64_t* sum,
                      const uint64_t* base, int32_t n, int64_t m, uint64_t* pfx, hipStream_t s);
+// and their guide records (two candidates each).
+void launch_guide64(const int32_t* row_ptr, const int32_t* tile_row, const VRec* vrec,
+                    const uint64_t* pfx, const int32_t* col, int32_t n, int64_t m, uint4* fat,
+                    hipStream_t s);
 
 // ---- device-wide exclusive scan: out[i] = sum in[0..i), out[n] = total ----
 size_t scan_temp_bytes(int64_t n);
@@ -55,11 +59,11 @@ void launch_scan_u32_to_u64(const uint32_t* in, uint64_t* out, int64_t n, void* 
                             hipStream_t s);
 
 // ---- walk ----
-// 64-bit prefixes: bisection over pfx64 + col.  32-bit prefixes: guide
-// table + packed edge records.
+// 64-bit prefixes: guide records, or (fat null) bisection over pfx64 + col.
+// 32-bit prefixes: guide records + packed edges.
 void launch_walk64(int stride, const VRec* vrec, const uint64_t* pfx, const int32_t* col,
-                   const int32_t* vstart, int32_t nstart, int32_t T, uint64_t R, uint64_t seed,
-                   int32_t* paths, hipStream_t s);
+                   const uint4* fat, const int32_t* vstart, int32_t nstart, int32_t T, uint64_t R,
+                   uint64_t seed, int32_t* paths, hipStream_t s);
 void launch_walk32(int stride, const VRec* vrec, const uint2* edge, const uint4* fat, int64_t m,
                    const int4* start_rec, int32_t nstart, int32_t T, uint64_t R, uint64_t seed,
                    int32_t* paths, hipStream_t s);

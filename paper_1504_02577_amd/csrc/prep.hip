@@ -270,6 +270,45 @@ k_guide32(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ tile_
   }
 }
 
+// The same for 64-bit prefixes: two candidates, [pfx0 pfx1] [col st dg e0]
+// [col st dg -] [W0 W1].
+__global__ void __launch_bounds__(kBlock)
+k_guide64(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ tile_row,
+          const VRec* __restrict__ vrec, const uint64_t* __restrict__ pfx,
+          const int32_t* __restrict__ col, int32_t n, int64_t m, uint4* __restrict__ fat) {
+  const int32_t lo = tile_row[blockIdx.x];
+  const int32_t hi = blockIdx.x + 1 < gridDim.x ? tile_row[blockIdx.x + 1] : n - 1;
+  const int64_t t0 = (int64_t)blockIdx.x * kEdgeTile + threadIdx.x;
+  const int p = threadIdx.x & 3;
+#pragma unroll 1
+  for (int i = 0; i < kEdgePer; ++i) {
+    const int64_t at = t0 + i * kBlock;
+    const int32_t e = (int32_t)(at < m ? at : m - 1);
+    const int32_t v = row_of(row_ptr, lo, hi, e);
+    const VRec r = vrec[v];
+    uint4 g[4] = {};
+    if (r.w_lo | r.w_hi) {
+      const int32_t last = r.start + r.deg - 1;
+      const int32_t c0 = guide_entry([&](int32_t x) { return pfx[x]; }, r.start, r.deg,
+                                     (uint64_t)r.w_lo | ((uint64_t)r.w_hi << 32),
+                                     (uint64_t)(e - r.start));
+      const int32_t c1 = c0 < last ? c0 + 1 : last;
+      const uint64_t p0 = pfx[c0], p1 = pfx[c1];
+      const int32_t v0 = col[c0], v1 = col[c1];
+      const VRec t0r = vrec[v0], t1r = vrec[v1];
+      g[0] = make_uint4((uint32_t)p0, (uint32_t)(p0 >> 32), (uint32_t)p1, (uint32_t)(p1 >> 32));
+      g[1] = make_uint4((uint32_t)v0, (uint32_t)t0r.start, (uint32_t)t0r.deg, (uint32_t)c0);
+      g[2] = make_uint4((uint32_t)v1, (uint32_t)t1r.start, (uint32_t)t1r.deg, 0u);
+      g[3] = make_uint4(t0r.w_lo, t0r.w_hi, t1r.w_lo, t1r.w_hi);
+    }
+    quad_exchange(g);
+    const int64_t q = at - p;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (q + j < m) fat[4 * (q + j) + p] = g[j];
+  }
+}
+
 // ---- device-wide exclusive scan (reduce tiles, scan tile sums, apply) ----
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kBlock * kScanItems;
@@ -435,6 +474,14 @@ void launch_guide32(const int32_t* row_ptr, const int32_t* tile_row, const VRec*
                     const uint2* edge, int32_t n, int64_t m, uint4* fat, hipStream_t s) {
   if (m)
     k_guide32<<<(unsigned)edge_tiles(m), kBlock, 0, s>>>(row_ptr, tile_row, vrec, edge, n, m, fat);
+}
+
+void launch_guide64(const int32_t* row_ptr, const int32_t* tile_row, const VRec* vrec,
+                    const uint64_t* pfx, const int32_t* col, int32_t n, int64_t m, uint4* fat,
+                    hipStream_t s) {
+  if (m)
+    k_guide64<<<(unsigned)edge_tiles(m), kBlock, 0, s>>>(row_ptr, tile_row, vrec, pfx, col, n, m,
+                                                         fat);
 }
 
 size_t scan_temp_bytes(int64_t n) {

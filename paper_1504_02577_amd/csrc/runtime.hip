@@ -479,9 +479,16 @@ static int load_graph(panther_ctx* c, int32_t n, int64_t m, const int32_t* row_p
       TRY(graph_alloc(c, c->g_pfx, sizeof(uint64_t) * (size_t)(m + 1), "weight prefixes",
                       &c->d_pfx));
     launch_prefix64(d_rp, tile_row, sum, base, n, m, c->d_pfx + 1, s);
-    HIPTRY(hipStreamSynchronize(s), "prefix");
-    ctx_release(c->g_fat);
-    c->d_fat = nullptr;
+    // guide records only where they leave at least as much memory free as
+    // they take: such a graph has to load, and leave room for its paths, in
+    // as little memory as the bisection form needs
+    size_t free_b = 0, total_b = 0;
+    if (c->d_fat && (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b < c->g_fat.cap)) {
+      HIPTRY(hipStreamSynchronize(s), "prefix");
+      ctx_release(c->g_fat);
+      c->d_fat = nullptr;
+    }
+    if (c->d_fat) launch_guide64(d_rp, tile_row, c->d_vrec, c->d_pfx + 1, d_col, n, m, c->d_fat, s);
   } else {
     ctx_release(c->g_pfx);
     TRY(graph_alloc(c, c->g_edge, sizeof(uint2) * (size_t)m, "packed edges", &c->d_edge));
@@ -600,7 +607,7 @@ extern "C" int panther_sample_paths(panther_ctx* c, int32_t T, int64_t R, uint64
   c->d_paths = static_cast<int32_t*>(c->b_paths.p);
   stage_begin(c, 0, c->stream);
   if (c->pfx64)
-    launch_walk64(stride, c->d_vrec, c->d_pfx + 1, c->d_col,
+    launch_walk64(stride, c->d_vrec, c->d_pfx + 1, c->d_col, c->d_fat,
                   c->d_vstart, c->nstart, T, (uint64_t)R, seed, c->d_paths, c->stream);
   else
     launch_walk32(stride, c->d_vrec, c->d_edge, c->d_fat, c->m, c->d_start_rec, c->nstart, T,
