@@ -130,15 +130,57 @@ k_bf16_pad_rows(int64_t n_rows, int64_t npad, int32_t* __restrict__ sid, __bf16*
   sid[i] = 0x7FFFFFFF;
 }
 
+// What a call's other kernels find initialised: the statistics, and per
+// query (sorted index) the shared bound and the merge list's length.
+struct CallInit {
+  unsigned long long* stats;  // [8]
+  unsigned long long* gtau;   // [nq] or null
+  uint32_t* part_n;           // [nq] or null
+};
+
+__device__ __forceinline__ void init_call(const CallInit& C, int64_t i, int64_t nq) {
+  if (i < 8) C.stats[i] = 0ull;
+  if (i < nq && C.gtau) {
+    C.gtau[i] = ~0ull;
+    C.part_n[i] = 0u;
+  }
+}
+
 // sort keys for the queries: norm of each query position's operand
 __global__ void __launch_bounds__(kBlock)
 k_query_norm_keys(const float* __restrict__ norm, const int32_t* __restrict__ rank,
                   const float* __restrict__ qnorm, const int32_t* __restrict__ queries, int64_t nq,
-                  uint32_t* __restrict__ keys, int32_t* __restrict__ pos) {
+                  uint32_t* __restrict__ keys, int32_t* __restrict__ pos, CallInit C) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  init_call(C, i, nq);
   if (i >= nq) return;
   keys[i] = __float_as_uint(qnorm ? qnorm[i] : norm[rank[queries[i]]]);
   pos[i] = (int32_t)i;
+}
+
+// The order itself for up to kSmallOrder queries, by one work-group: a
+// bitonic sort of (norm bits, position) in LDS gives the same order as the
+// stable sort of the norms, in one launch instead of the 21 of four radix
+// passes (37 queries: 37 of the call's 700 us were those kernels, and as much
+// again the gaps between them).
+constexpr int kSmallOrder = 2048;
+constexpr int kOrderBlock = 1024;
+__global__ void __launch_bounds__(kOrderBlock)
+k_query_order_small(const float* __restrict__ norm, const int32_t* __restrict__ rank,
+                    const float* __restrict__ qnorm, const int32_t* __restrict__ queries,
+                    int32_t nq, int32_t* __restrict__ order, CallInit C) {
+  __shared__ uint64_t key[kSmallOrder];
+  const int P = next_pow2(nq < 2 ? 2 : nq);
+  for (int i = threadIdx.x; i < P || i < 8; i += kOrderBlock) {
+    init_call(C, i, nq);
+    if (i < P)
+      key[i] = i < nq ? ((uint64_t)__float_as_uint(qnorm ? qnorm[i] : norm[rank[queries[i]]]) << 32) |
+                            (uint32_t)i
+                      : ~0ull;
+  }
+  __syncthreads();
+  block_bitonic_asc<kOrderBlock>(key, P);
+  for (int i = threadIdx.x; i < nq; i += kOrderBlock) order[i] = (int32_t)(uint32_t)key[i];
 }
 
 // bf16 rows of the queries' own features (another graph's theta), scaled
@@ -221,14 +263,21 @@ __device__ void wave_sort_keys(uint64_t* a, int cnt) {
   }
 }
 
-// The P smallest of the c > P distinct keys a[0..c) by one wavefront: an
-// MSD radix select (8-bit digits, histogram in `hist`, 256 words) finds the
-// P-th smallest key T, then a[0..P) is compacted in place to the keys <= T
-// (in input order).  Returns T.
-__device__ uint64_t wave_select_cut(uint64_t* a, int c, int P, uint32_t* hist) {
+// Cuts the c > P distinct keys a[0..c) back by one wavefront: an MSD radix
+// select (8-bit digits, histogram in `hist`, 256 words) narrows the class of
+// the P-th smallest key until at most `most` keys (>= P) lie in it or below,
+// then a[] is compacted in place to those (in input order).  Returns the
+// largest key of the class, a bound that at least P keys reach, and through
+// *kept how many stayed; most == P keeps exactly the P smallest and returns
+// the P-th.  (Distances differ in their leading bits, so with some room two
+// of the eight digits decide: half of the time of a small batch's bound pass
+// went into the other six.)
+__device__ uint64_t wave_select_cut(uint64_t* a, int c, int P, int most, uint32_t* hist,
+                                    int* kept) {
   const int lane = threadIdx.x & (kWave - 1);
   uint64_t prefix = 0;  // digits fixed so far
   int need = P;         // rank of T within the current class (1-based)
+  uint64_t low = 0;     // the digits left open
   for (int shift = 56; shift >= 0; shift -= 8) {
 #pragma unroll
     for (int b = 0; b < 4; ++b) hist[lane * 4 + b] = 0u;
@@ -255,12 +304,13 @@ __device__ uint64_t wave_select_cut(uint64_t* a, int c, int P, uint32_t* hist) {
     }
     uint32_t below = inc - sum;
     int dsel = -1;
-    uint32_t below_sel = 0;
+    uint32_t below_sel = 0, in_sel = 0;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
       if (dsel < 0 && below < (uint32_t)need && below + h[b] >= (uint32_t)need) {
         dsel = lane * 4 + b;
         below_sel = below;
+        in_sel = h[b];
       }
       below += h[b];
     }
@@ -270,8 +320,13 @@ __device__ uint64_t wave_select_cut(uint64_t* a, int c, int P, uint32_t* hist) {
     need -= (int)__shfl(below_sel, src, kWave);
     prefix |= (uint64_t)d << shift;
     wsync();
+    // (not before the second digit: the first holds little but the exponent)
+    if (shift <= 48 && P - need + (int)__shfl(in_sel, src, kWave) <= most) {
+      low = (1ull << shift) - 1ull;
+      break;
+    }
   }
-  const uint64_t T = prefix;
+  const uint64_t T = prefix | low;
   // in-place compaction: a position is written only after it was read
   int base = 0;
   for (int i0 = 0; i0 < c; i0 += kWave) {
@@ -283,6 +338,7 @@ __device__ uint64_t wave_select_cut(uint64_t* a, int c, int P, uint32_t* hist) {
     base += __popcll(bm);
     wsync();
   }
+  *kept = base;
   return T;
 }
 
@@ -301,7 +357,8 @@ struct PoolArgs {
   int32_t slices;        // work-groups per query tile (grid.y), interleaved over chunks
   int32_t sort_cap;      // per-wave buffer entries (>= cap, and >= the sort's P)
   uint64_t* buf;         // [nq][slices][cap] pool buffers, by sorted index
-  uint64_t* part;        // [nq][slices][P] slice pools (slices > 1), by sorted index
+  uint64_t* part;        // [nq][slices * P] the slices' keys (slices > 1), by sorted index
+  uint32_t* part_n;      // [nq] their number
   int32_t* pool_ids;     // [nq][P] result by query position, ascending key order, -1 padded
   float* pool_d2;        // [nq][P]
   // query operands: the database's own rows (row rank[q]), or (cross
@@ -595,16 +652,17 @@ k_pp_pool(PoolArgs A) {
       for (int i = lane; i < c; i += kWave)
         sb[i] = __hip_atomic_load(&g[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       wsync();
-      const uint64_t T = wave_select_cut(sb, c, P, s_hist[wid]);
-      for (int i = lane; i < P; i += kWave) g[i] = sb[i];
+      int m;
+      const uint64_t T = wave_select_cut(sb, c, P, P + P / 4, s_hist[wid], &m);
+      for (int i = lane; i < m; i += kWave) g[i] = sb[i];
       if (lane == 0) {
-        cnt[ql] = (uint32_t)P;
+        cnt[ql] = (uint32_t)m;
         if (T < tau[ql]) {
           tau[ql] = T;
           tauf_s[ql] = __uint_as_float((uint32_t)(T >> 32));
         }
-        // (a slice keeps its P keys <= tau, so the others may drop keys >=
-        // tau; the bound pass keeps nothing and publishes only at its end)
+        // (a slice keeps at least P keys <= T, T itself among them if it is a
+        // key, so the others may drop keys >= T; the bound pass keeps nothing and publishes only at its end)
         if (A.gtau && !A.bound_only && qid[ql] >= 0)
           atomicMin(&A.gtau[q0 + ql], (unsigned long long)tau[ql]);
       }
@@ -659,8 +717,10 @@ k_pp_pool(PoolArgs A) {
         sb[i] = __hip_atomic_load(&g[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       wsync();
       // this pass keeps no pool, so the slices must keep keys equal to T
-      // too: publish the next key, T + 1 (ids stay below 2^31)
-      const uint64_t T = wave_select_cut(sb, c, P, s_hist[wid]);
+      // too: publish the next key, T + 1 (ids stay below 2^31, so T + 1 only
+      // carries into the float part where no key has T's)
+      int m;
+      const uint64_t T = wave_select_cut(sb, c, P, P + P / 4, s_hist[wid], &m);
       if (lane == 0) atomicMin(&A.gtau[q0 + ql], (unsigned long long)(T + 1ull));
       wsync();
     }
@@ -675,13 +735,12 @@ k_pp_pool(PoolArgs A) {
     for (int i = lane; i < c; i += kWave)
       sb[i] = __hip_atomic_load(&g[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     wsync();
-    // one slice: the pool in ascending key order; several: the slice's P
-    // best in any order (the merge selects across slices).  The P best are
-    // cut first, so the sort needs P (a power of two) entries of buffer.
-    if (c > P) (void)wave_select_cut(sb, c, P, s_hist[wid]);
-    if (S == 1) wave_sort_keys(sb, c < P ? c : P);
-    const int m = c < P ? c : P;
+    int m = c;
     if (S == 1) {
+      // the pool in ascending key order: the P best are cut first, so the
+      // sort needs P (a power of two) entries of buffer
+      if (c > P) (void)wave_select_cut(sb, c, P, P, s_hist[wid], &m);
+      wave_sort_keys(sb, m);
       const int64_t pos = qpos[ql];
       for (int i = lane; i < P; i += kWave) {
         const bool ok = i < m;
@@ -689,29 +748,47 @@ k_pp_pool(PoolArgs A) {
         A.pool_d2[pos * P + i] = ok ? __uint_as_float((uint32_t)(sb[i] >> 32)) : INFINITY;
       }
     } else {
-      // fixed-length slice pools (unordered), padded with the largest key
-      uint64_t* o = A.part + ((q0 + ql) * S + slice) * P;
-      for (int i = lane; i < P; i += kWave) o[i] = i < m ? sb[i] : ~0ull;
+      // the slice's keys that no bound excludes yet (in the end few more than
+      // P over all slices), at most P of them, in any order; a key >= the
+      // shared bound has P smaller or equal ones in the publishing slice
+      const unsigned long long gb =
+          __hip_atomic_load(&A.gtau[q0 + ql], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint64_t top = tau[ql] < gb ? tau[ql] : gb;
+      int at = 0;
+      for (int i0 = 0; i0 < c; i0 += kWave) {
+        const int i = i0 + lane;
+        const uint64_t x = i < c ? sb[i] : ~0ull;
+        const bool keep = i < c && x <= top;
+        const uint64_t bm = __ballot(keep);
+        if (keep) sb[at + __popcll(bm & ((1ull << lane) - 1ull))] = x;
+        at += __popcll(bm);
+        wsync();
+      }
+      m = at;
+      if (at > P) (void)wave_select_cut(sb, at, P, P, s_hist[wid], &m);
+      uint32_t base = 0u;
+      if (lane == 0 && m) base = atomicAdd(&A.part_n[q0 + ql], (uint32_t)m);
+      base = __shfl(base, 0);
+      uint64_t* o = A.part + (q0 + ql) * (int64_t)S * P + base;
+      for (int i = lane; i < m; i += kWave) o[i] = sb[i];
     }
     wsync();
   }
 }
 
-// One work-group per query (sorted index): the P smallest keys over all
-// slice pools, written to the query's position.
-// Slice pools are P keys long, padded with ~0, which complement to 0: a
-// selected 0 is padding.
+// One work-group per query (sorted index): the P smallest of the slices'
+// keys, written to the query's position.
 __global__ void __launch_bounds__(kBlock)
 k_pp_merge(PoolArgs A) {
   __shared__ SelectSmem sm;
   const int64_t j = blockIdx.x;  // sorted index; the output row is its position
   const int64_t qi = A.q_order[j];
-  const int S = A.slices, P = A.P;
-  const uint64_t* base = A.part + j * (int64_t)S * P;
+  const int P = A.P;
+  const uint64_t* base = A.part + j * (int64_t)A.slices * P;
   auto key = [&](int i) { return ~base[i]; };  // larger = better
-  const int m = block_select_topk<kBlock>(key, S * P, P, sm);
+  const int m = block_select_topk<kBlock>(key, (int)A.part_n[j], P, sm);
   for (int i = threadIdx.x; i < P; i += kBlock) {
-    const bool ok = i < m && sm.out[i] != 0ull;
+    const bool ok = i < m;
     const uint64_t k2 = ok ? ~sm.out[i] : 0ull;
     A.pool_ids[qi * P + i] = ok ? (int32_t)(uint32_t)k2 : -1;
     A.pool_d2[qi * P + i] = ok ? __uint_as_float((uint32_t)(k2 >> 32)) : INFINITY;
@@ -1102,7 +1179,8 @@ static int run_pp_bf16_geom(panther_ctx* c, Lane* lane, const int32_t* dq, int64
   const size_t buf_bytes = sizeof(uint64_t) * (size_t)nq * S * cap;
   const size_t part_bytes = S > 1 ? sizeof(uint64_t) * (size_t)nq * S * P : 0;
   const size_t ids_bytes = (sizeof(int32_t) + sizeof(float)) * (size_t)nq * P;
-  const size_t gtau_bytes = S > 1 ? sizeof(uint64_t) * (size_t)nq : 0;
+  // the shared bounds and the merge lists' lengths
+  const size_t gtau_bytes = S > 1 ? 2 * sizeof(uint64_t) * (size_t)nq : 0;
   TRY(ctx_ensure(c, lane->b_pool, buf_bytes + part_bytes + gtau_bytes + ids_bytes + 256,
                  "pools"));
   TRY(ctx_ensure(c, lane->b_stats, 64, "pp stats"));
@@ -1113,7 +1191,6 @@ static int run_pp_bf16_geom(panther_ctx* c, Lane* lane, const int32_t* dq, int64
       S > 1 ? reinterpret_cast<unsigned long long*>(base + buf_bytes + part_bytes) : nullptr;
   int32_t* pool_ids = reinterpret_cast<int32_t*>(base + buf_bytes + part_bytes + gtau_bytes);
   float* pool_d2 = reinterpret_cast<float*>(pool_ids + (size_t)nq * P);
-  HIPTRY(hipMemsetAsync(lane->b_stats.p, 0, 64, s), "pp stats");
   const int sort_cap = std::max(cap, P);
   const int64_t rows = pp->bf16_rows;
   const int64_t nchunks = (rows + kTrip * kChunk - 1) / (kTrip * kChunk) * kTrip;
@@ -1132,16 +1209,13 @@ static int run_pp_bf16_geom(panther_ctx* c, Lane* lane, const int32_t* dq, int64
   pa.sort_cap = sort_cap;
   pa.buf = buf;
   pa.part = part;
+  pa.part_n = gtau ? reinterpret_cast<uint32_t*>(gtau + nq) : nullptr;
   pa.pool_ids = pool_ids;
   pa.pool_d2 = pool_d2;
   pa.q_by_pos = 0;
   pa.exclude_self = 1;
   pa.gtau = gtau;
   pa.stat_products = static_cast<unsigned long long*>(lane->b_stats.p) + 5;
-  if (gtau) {
-    k_fill_u64<<<(unsigned)((nq + kBlock - 1) / kBlock), kBlock, 0, s>>>(gtau, nq, ~0ull);
-    HIPTRY(hipGetLastError(), "pool bounds");
-  }
   if (qtheta) {
     TRY(ctx_ensure(c, lane->b_qrows, (sizeof(__bf16) * kDP + sizeof(float)) * (size_t)nq,
                    "query bf16 rows"));
@@ -1165,10 +1239,17 @@ static int run_pp_bf16_geom(panther_ctx* c, Lane* lane, const int32_t* dq, int64
     uint32_t* kout = kin + half;
     int32_t* vin = reinterpret_cast<int32_t*>(kout + half);
     int32_t* vout = vin + half;
-    k_query_norm_keys<<<(unsigned)((nq + kBlock - 1) / kBlock), kBlock, 0, s>>>(
-        pa.norm, pa.rank, pa.qnorm, dq, nq, kin, vin);
-    HIPTRY(hipGetLastError(), "query order");
-    TRY(sort_pairs(c, lane->b_qsort_tmp, kin, kout, vin, vout, nq, s));
+    const CallInit init{static_cast<unsigned long long*>(lane->b_stats.p), pa.gtau, pa.part_n};
+    if (nq <= kSmallOrder) {
+      k_query_order_small<<<1, kOrderBlock, 0, s>>>(pa.norm, pa.rank, pa.qnorm, dq, (int32_t)nq,
+                                                    vout, init);
+      HIPTRY(hipGetLastError(), "query order");
+    } else {
+      k_query_norm_keys<<<(unsigned)((nq + kBlock - 1) / kBlock), kBlock, 0, s>>>(
+          pa.norm, pa.rank, pa.qnorm, dq, nq, kin, vin, init);
+      HIPTRY(hipGetLastError(), "query order");
+      TRY(sort_pairs(c, lane->b_qsort_tmp, kin, kout, vin, vout, nq, s));
+    }
     pa.q_order = vout;
   }
   const size_t sort_lds = sizeof(uint64_t) * (size_t)sort_cap * (kBlock / kWave);
@@ -1359,7 +1440,7 @@ size_t pp_lane_bytes(const panther_ctx* c, int64_t nq, int32_t k) {
   size_t b = 0;
   for (int w : {16, 32, 64}) {
     const panther::PoolGeom G = panther::pool_geom(c, nq, k, w);
-    b = std::max(b, sizeof(uint64_t) * n * G.S * G.cap + sizeof(uint64_t) * n +
+    b = std::max(b, sizeof(uint64_t) * n * G.S * G.cap + 2 * sizeof(uint64_t) * n +
                         (G.S > 1 ? sizeof(uint64_t) * n * G.S * G.P : 0) +
                         (sizeof(int32_t) + sizeof(float)) * n * G.P + 256);
   }
