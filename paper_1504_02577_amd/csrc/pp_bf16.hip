@@ -48,7 +48,7 @@ constexpr int kDP = 64;        // padded feature width in bfloat16
 constexpr int kChunk = 64;     // database rows per chunk (16 per wavefront)
 constexpr int kTrip = 4;        // chunks per loop trip (register ring of operands)
 constexpr int kCheckEvery = 16;  // chunks between pool compaction checks (whole trips)
-constexpr int kBoundChunks = 32;  // chunks of the bound pass before a sliced scan
+constexpr int kBoundChunks = 32;  // most chunks of a query's bound
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -134,13 +134,13 @@ k_bf16_pad_rows(int64_t n_rows, int64_t npad, int32_t* __restrict__ sid, __bf16*
 // query (sorted index) the shared bound and the merge list's length.
 struct CallInit {
   unsigned long long* stats;  // [8]
-  unsigned long long* gtau;   // [nq] or null
-  uint32_t* part_n;           // [nq] or null
+  unsigned long long* gtau;   // [nq]
+  uint32_t* part_n;           // [nq]
 };
 
 __device__ __forceinline__ void init_call(const CallInit& C, int64_t i, int64_t nq) {
   if (i < 8) C.stats[i] = 0ull;
-  if (i < nq && C.gtau) {
+  if (i < nq) {
     C.gtau[i] = ~0ull;
     C.part_n[i] = 0u;
   }
@@ -367,16 +367,12 @@ struct PoolArgs {
   const float* qnorm;
   int32_t q_by_pos;
   int32_t exclude_self;  // single graph: the query's own row is no candidate
-  // slices > 1: per query (sorted index), the smallest P-th best key any
-  // slice has reached so far -- an upper bound on the query's P-th best key
-  // overall, so every slice may drop keys at or above it
+  // per query (sorted index), an upper bound on the query's P-th best key: the
+  // bound pass's, then (slices > 1) the smallest that any slice has reached,
+  // so every slice may drop keys at or above it
   unsigned long long* gtau;
+  int32_t bound_chunks;  // chunks of a query's bound, nearest its norm
   unsigned long long* stat_products;  // += (query, row) products computed
-  // bound pass: stop after max_chunks chunks and publish, for each full
-  // pool, the key after its P-th to gtau instead of writing pools (at
-  // least P rows have keys below it: a valid exclusive bound)
-  int32_t max_chunks;    // 0: no limit
-  int32_t bound_only;
 };
 
 // Norm band of one query for the current float threshold t (squared
@@ -402,7 +398,121 @@ __device__ __forceinline__ void norm_band(float qn, float t, float& lo2, float& 
   lo2 = lo > 0.f ? lo * lo * (1.f - 2.44140625e-4f) : 0.f;
 }
 
-// grid (query tiles of QW, slices)
+// First row of the norm order with norm >= target, by the whole work-group (a
+// 256-way search: rows below lo are below it, and row hi is n or not below).
+__device__ int64_t first_row_at(const float* __restrict__ norm, int64_t n, float target) {
+  int64_t lo = 0, hi = n;
+  while (lo < hi) {
+    const int64_t step = (hi - lo + kBlock - 1) / kBlock;
+    const int64_t idx = lo + (int64_t)threadIdx.x * step;
+    const int below = idx < hi && norm[idx] < target;
+    const int nb = __syncthreads_count(below);  // the probes below form a prefix
+    if (nb == 0) {
+      hi = lo;
+    } else {
+      const int64_t last = lo + (int64_t)(nb - 1) * step;  // last probe below
+      lo = last + 1;
+      hi = last + step < hi ? last + step : hi;
+    }
+  }
+  return lo;
+}
+
+// Bound pass: one work-group per query (sorted index) takes the P-th smallest
+// key among the A.bound_chunks chunks around the first row of the query's own
+// norm and publishes the next key (an exclusive bound: at least P rows are
+// below it).  The chunks start below that row and go on above it, so where
+// many rows equal the query's, which come in id order from that row on, the
+// bound is their P-th: tiles whose queries shared one start kept up to P
+// equal rows in each of 158 slices.  The products are the scan's own (the
+// query is every column of the MFMA tile), so the keys are the same.  Each
+// thread keeps its eight keys in registers, and the P-th is found by
+// bisection on the key: a count is eight compares and ballots a wave, and the
+// search ends as soon as exactly P keys lie below the middle.
+__global__ void __launch_bounds__(kBlock)
+k_pp_bound(PoolArgs A) {
+  constexpr int kPer = kBoundChunks * kChunk / kBlock;  // keys per thread
+  __shared__ uint32_t s_cnt[2][kBlock / kWave];
+  __shared__ uint64_t s_keys[kBoundChunks * kChunk];
+  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+  const int64_t j = blockIdx.x;
+  const int32_t pos = A.q_order[j];
+  const int32_t q = A.queries[pos];
+  const float qn = A.q_by_pos ? A.qnorm[pos] : A.norm[A.rank[q]];
+  const __bf16* qr = A.q_by_pos ? A.qrows + (int64_t)pos * kDP : A.rows + (int64_t)A.rank[q] * kDP;
+  bf16x8 a[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+    a[ks] = *reinterpret_cast<const bf16x8*>(qr + ks * 32 + 8 * (lane >> 4));
+  const int64_t row0 = first_row_at(A.norm, A.n, qn);
+  const int nb = A.bound_chunks;
+  int64_t c0 = row0 / kChunk - nb * 3 / 8;
+  if (c0 > A.nchunks - nb) c0 = A.nchunks - nb;
+  if (c0 < 0) c0 = 0;
+  const int nc = (int)(A.nchunks - c0 < nb ? A.nchunks - c0 : nb);
+  for (int i = nc * kChunk + threadIdx.x; i < kBoundChunks * kChunk; i += kBlock) s_keys[i] = ~0ull;
+  // 16 rows per wavefront and chunk, as in the scan: lane l holds the products
+  // with rows 4*(l/16) .. +3 (one query in every column), and writes the key
+  // of row l % 4 of those when l % 16 < 4
+#pragma unroll 4
+  for (int c = 0; c < nc; ++c) {
+    const int64_t v0 = (c0 + c) * kChunk + wid * 16;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    bf16x8 b[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+      b[ks] = *reinterpret_cast<const bf16x8*>(A.rows + (v0 + (lane & 15)) * kDP + ks * 32 +
+                                               8 * (lane >> 4));
+    const int r = lane & 3;
+    const int at = 4 * (lane >> 4) + r;
+    const float nv = A.norm[v0 + at];
+    const int32_t v = A.sid[v0 + at];
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[0], a[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[1], a[1], acc, 0, 0, 0);
+    const float dot = r == 0 ? acc[0] : (r == 1 ? acc[1] : (r == 2 ? acc[2] : acc[3]));
+    const float raw = __builtin_fmaf(-2.f, dot, nv) + qn;
+    const bool ok = raw <= INFINITY && (!A.exclude_self || v != q);  // a padding row is NaN
+    if ((lane & 15) < 4)
+      s_keys[c * kChunk + wid * 16 + at] =
+          ok ? ((uint64_t)__float_as_uint(raw > 0.f ? raw : 0.f) << 32) | (uint32_t)v : ~0ull;
+  }
+  __syncthreads();
+  uint64_t k[kPer];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) k[i] = s_keys[i * kBlock + threadIdx.x];
+  // the smallest x such that P keys are <= x lies in (lo, hi] (keys stay
+  // below 2^63); every wave runs the same search, one barrier a step
+  int turn = 0;
+  auto count = [&](uint64_t x) {
+    uint32_t n = 0u;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) n += (uint32_t)__popcll(__ballot(k[i] <= x));
+    turn ^= 1;
+    if (lane == 0) s_cnt[turn][wid] = n;
+    __syncthreads();
+    n = 0u;
+#pragma unroll
+    for (int w = 0; w < kBlock / kWave; ++w) n += s_cnt[turn][w];
+    return n;
+  };
+  const uint32_t P = (uint32_t)A.P;
+  uint64_t lo = 0ull, hi = ~0ull >> 1;
+  if (count(hi) < P) return;  // uniform: no P rows here, the query stays unbounded
+  if (count(0ull) >= P) hi = 0ull;
+  while (hi - lo > 1ull) {
+    const uint64_t mid = lo + ((hi - lo) >> 1);
+    const uint32_t n = count(mid);
+    if (n >= P) hi = mid;
+    else lo = mid;
+    if (n == P) break;
+  }
+  // (P keys are <= hi; ids stay below 2^31, so hi + 1 cannot wrap)
+  if (threadIdx.x == 0) A.gtau[j] = (unsigned long long)(hi + 1ull);
+}
+
+// grid (query tiles of QW, slices).  The tiles of the largest norms come
+// first: their queries have few near neighbours, so their bands are the
+// widest, and as the last to start they were the tail of the pass.
 template <int QW>
 __global__ void __launch_bounds__(kBlock)
 k_pp_pool(PoolArgs A) {
@@ -419,7 +529,7 @@ k_pp_pool(PoolArgs A) {
   extern __shared__ __align__(16) uint64_t sortmem[];  // [waves][cap]
   __shared__ uint32_t s_hist[kBlock / kWave][256];     // per-wave radix select
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  const int64_t q0 = (int64_t)blockIdx.x * QW;  // sorted index of the tile's first query
+  const int64_t q0 = (int64_t)(gridDim.x - 1 - blockIdx.x) * QW;  // sorted index of the tile's first query
   const int slice = blockIdx.y;
   const int S = A.slices;
   const int P = A.P, cap = A.cap;
@@ -432,10 +542,9 @@ k_pp_pool(PoolArgs A) {
     qpos[i] = pos;
     qn_s[i] = q >= 0 ? (A.q_by_pos ? A.qnorm[pos] : A.norm[A.rank[q]]) : 0.f;
     cnt[i] = 0u;
-    // start from the shared bound when there is one (a bound pass or
-    // other slices may have set it)
+    // start from the query's bound (the bound pass's, or already a slice's)
     const unsigned long long gb =
-        q >= 0 && A.gtau && !A.bound_only
+        q >= 0
             ? __hip_atomic_load(&A.gtau[q0 + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
             : ~0ull;
     tau[i] = gb;
@@ -449,24 +558,8 @@ k_pp_pool(PoolArgs A) {
   }
   __syncthreads();
   // start chunk: where the median query norm falls among the sorted rows
-  // (a 256-way search for the first row with norm >= target: rows below
-  // lo are below it, and row hi is n or not below it)
   {
-    const float target = qn_s[(nvalid - 1) / 2];
-    int64_t lo = 0, hi = A.n;
-    while (lo < hi) {
-      const int64_t step = (hi - lo + kBlock - 1) / kBlock;
-      const int64_t idx = lo + (int64_t)threadIdx.x * step;
-      const int below = idx < hi && A.norm[idx] < target;
-      const int nb = __syncthreads_count(below);  // the probes below form a prefix
-      if (nb == 0) {
-        hi = lo;
-      } else {
-        const int64_t last = lo + (int64_t)(nb - 1) * step;  // last probe below
-        lo = last + 1;
-        hi = last + step < hi ? last + step : hi;
-      }
-    }
+    const int64_t lo = first_row_at(A.norm, A.n, qn_s[(nvalid - 1) / 2]);
     if (threadIdx.x == 0) {
       int64_t c = lo / kChunk;
       if (c >= A.nchunks) c = A.nchunks - 1;
@@ -617,12 +710,12 @@ k_pp_pool(PoolArgs A) {
     chunk_no += kTrip;
     // once the sequence returns -1 it stays -1: if the oldest chunk left
     // in the ring is none, so are the two after it
-    const bool last = c_next < 0 || (A.max_chunks && chunk_no >= A.max_chunks);
+    const bool last = c_next < 0;
     if (chunk_no % check_every != 0 && !last) continue;
     __threadfence_block();
     __syncthreads();
     // adopt the other slices' bound where it is tighter (one load per query)
-    if (A.gtau && !A.bound_only) {
+    if (S > 1) {
       for (int ql = threadIdx.x; ql < QW; ql += kBlock) {
         if (qid[ql] < 0) continue;
         const unsigned long long gb =
@@ -662,8 +755,8 @@ k_pp_pool(PoolArgs A) {
           tauf_s[ql] = __uint_as_float((uint32_t)(T >> 32));
         }
         // (a slice keeps at least P keys <= T, T itself among them if it is a
-        // key, so the others may drop keys >= T; the bound pass keeps nothing and publishes only at its end)
-        if (A.gtau && !A.bound_only && qid[ql] >= 0)
+        // key, so the others may drop keys >= T)
+        if (S > 1 && qid[ql] >= 0)
           atomicMin(&A.gtau[q0 + ql], (unsigned long long)tau[ql]);
       }
       wsync();
@@ -703,29 +796,10 @@ k_pp_pool(PoolArgs A) {
     up_on = __builtin_amdgcn_readfirstlane(s_dir[0]);
     down_on = __builtin_amdgcn_readfirstlane(s_dir[1]);
     refresh();
-    if (last) break;  // the sequence ran dry (both directions closed), or the budget
+    if (last) break;  // the sequence ran dry (both directions closed)
   }
   if (threadIdx.x == 0)
     atomicAdd(A.stat_products, (unsigned long long)((nu + nd) * kChunk * nvalid));
-  if (A.bound_only) {
-    for (int ql = wid; ql < QW; ql += kBlock / kWave) {
-      const int c = (int)cnt[ql];
-      if (qid[ql] < 0 || c < P) continue;
-      uint64_t* g = A.buf + ((q0 + ql) * S + slice) * cap;
-      uint64_t* sb = sortmem + (size_t)wid * A.sort_cap;
-      for (int i = lane; i < c; i += kWave)
-        sb[i] = __hip_atomic_load(&g[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      wsync();
-      // this pass keeps no pool, so the slices must keep keys equal to T
-      // too: publish the next key, T + 1 (ids stay below 2^31, so T + 1 only
-      // carries into the float part where no key has T's)
-      int m;
-      const uint64_t T = wave_select_cut(sb, c, P, P + P / 4, s_hist[wid], &m);
-      if (lane == 0) atomicMin(&A.gtau[q0 + ql], (unsigned long long)(T + 1ull));
-      wsync();
-    }
-    return;
-  }
   // final pools of this slice
   for (int ql = wid; ql < QW; ql += kBlock / kWave) {
     if (qid[ql] < 0) continue;
@@ -1180,7 +1254,7 @@ static int run_pp_bf16_geom(panther_ctx* c, Lane* lane, const int32_t* dq, int64
   const size_t part_bytes = S > 1 ? sizeof(uint64_t) * (size_t)nq * S * P : 0;
   const size_t ids_bytes = (sizeof(int32_t) + sizeof(float)) * (size_t)nq * P;
   // the shared bounds and the merge lists' lengths
-  const size_t gtau_bytes = S > 1 ? 2 * sizeof(uint64_t) * (size_t)nq : 0;
+  const size_t gtau_bytes = 2 * sizeof(uint64_t) * (size_t)nq;
   TRY(ctx_ensure(c, lane->b_pool, buf_bytes + part_bytes + gtau_bytes + ids_bytes + 256,
                  "pools"));
   TRY(ctx_ensure(c, lane->b_stats, 64, "pp stats"));
@@ -1188,7 +1262,7 @@ static int run_pp_bf16_geom(panther_ctx* c, Lane* lane, const int32_t* dq, int64
   uint64_t* buf = reinterpret_cast<uint64_t*>(base);
   uint64_t* part = reinterpret_cast<uint64_t*>(base + buf_bytes);
   unsigned long long* gtau =
-      S > 1 ? reinterpret_cast<unsigned long long*>(base + buf_bytes + part_bytes) : nullptr;
+      reinterpret_cast<unsigned long long*>(base + buf_bytes + part_bytes);
   int32_t* pool_ids = reinterpret_cast<int32_t*>(base + buf_bytes + part_bytes + gtau_bytes);
   float* pool_d2 = reinterpret_cast<float*>(pool_ids + (size_t)nq * P);
   const int sort_cap = std::max(cap, P);
@@ -1209,7 +1283,7 @@ static int run_pp_bf16_geom(panther_ctx* c, Lane* lane, const int32_t* dq, int64
   pa.sort_cap = sort_cap;
   pa.buf = buf;
   pa.part = part;
-  pa.part_n = gtau ? reinterpret_cast<uint32_t*>(gtau + nq) : nullptr;
+  pa.part_n = reinterpret_cast<uint32_t*>(gtau + nq);
   pa.pool_ids = pool_ids;
   pa.pool_d2 = pool_d2;
   pa.q_by_pos = 0;
@@ -1266,18 +1340,11 @@ static int run_pp_bf16_geom(panther_ctx* c, Lane* lane, const int32_t* dq, int64
     else
       k_pp_pool<16><<<dim3((unsigned)tiles, gy), kBlock, sort_lds, s>>>(args);
   };
-  if (S > 1) {
-    // bound pass: one work-group per tile scans the kBoundChunks chunks
-    // nearest its median norm and publishes each query's P-th key, so that
-    // the slices start from a tight bound instead of each filling its own
-    // pool from the first rows
-    PoolArgs pb = pa;
-    pb.slices = 1;
-    pb.max_chunks = kBoundChunks;
-    pb.bound_only = 1;
-    launch_pool(pb, 1u);
-    HIPTRY(hipGetLastError(), "pp pool bound");
-  }
+  // few queries: a wide bound (2,048 rows) costs little; a large batch pays
+  // for every row of it, and three times the pool are enough
+  pa.bound_chunks = S > 1 ? kBoundChunks : std::min(kBoundChunks, 3 * P / kChunk);
+  k_pp_bound<<<(unsigned)nq, kBlock, 0, s>>>(pa);
+  HIPTRY(hipGetLastError(), "pp pool bound");
   launch_pool(pa, (unsigned)S);
   HIPTRY(hipGetLastError(), "pp pool");
   if (S > 1) {
@@ -1343,7 +1410,8 @@ static int run_pp_bf16_geom(panther_ctx* c, Lane* lane, const int32_t* dq, int64
   lane->max_rel_err = e;
   lane->stat_nq = nq;
   lane->stat_fallback = (int64_t)hs[3];
-  lane->stat_scanned = (double)hs[5] / ((double)nq * (double)c->n);
+  const double bound = (double)nq * (double)std::min<int64_t>(nchunks, pa.bound_chunks) * kChunk;
+  lane->stat_scanned = ((double)hs[5] + bound) / ((double)nq * (double)c->n);
   return PANTHER_OK;
 }
 
