@@ -3,12 +3,14 @@
 // picked by an autotuner.
 //
 // Queries are split by the length L of their path list P_q (known on the
-// host from the index offsets) into three tiers, each ordered longest
-// length class first:
+// host from the index offsets) into tiers, each ordered longest length
+// class first:
 //   A  (T*L fits half of a per-wave LDS table): one wavefront per query in
 //      k_topk_waves.  Open-addressing hash (vertex -> count) in LDS, then
 //      the occupied slots are compacted to 64-bit ranking keys and
 //      bitonic-sorted by the wave alone (no work-group barrier).
+//   M  (fits half of a 1,024- or 2,048-entry table): one wavefront per query
+//      in k_topk_mid.
 //   B  (fits half of a work-group LDS table): one work-group per query in
 //      the persistent k_topk_batched (work queue), LDS hash, then block
 //      selection of the k largest keys.
@@ -59,8 +61,9 @@ struct ItemRec {
 struct BatchArgs {
   const int32_t* queries;  // [nq]
   const ItemRec* itemsB;   // the B queries, longest class first
+  const ItemRec* itemsM;   // then the M queries: nM2 for the wide table, nM1 for the other
   const ItemRec* itemsA;
-  int32_t nB, nA;
+  int32_t nB, nM2, nM1, nA;
   // tier A runs in four phases of 64, 32, 16 and 8 lanes per query:
   // itemsA [0, nA64), [nA64, nA32), [nA32, nA16), [nA16, nA)
   int32_t nA64, nA32, nA16;
@@ -463,27 +466,163 @@ __global__ void __launch_bounds__(kWaveBlock) k_topk_waves(BatchArgs A) {
   group_items<S, 8>(A, A.nA16, A.nA, wg, W, region);
 }
 
+// ---- tier M: one wavefront per query as in tier A, with a table of TG
+// entries of its own work-group (8 bytes an entry: 20 wavefronts of 1,024
+// entries or 10 of 2,048 share a CU's LDS).  Lists of 52 to 204 paths (T = 5)
+// are too long for tier A's tables and too short for a work-group: there each
+// took 512 threads through some fifteen barriers and a 4,096-entry table, two
+// queries at a time per CU.  Up to 256 rows of a query are loaded before the
+// first is counted, and the selection runs in registers.  R-MAT 20 features
+// (98,000 such lists of a million) 7.5 -> 4.8 ms; tier B took 3.1 ms of it.
+constexpr int kMid1 = 1024, kMid2 = 2048;
+
+template <int S, int TG>
+__global__ void __launch_bounds__(kWave) k_topk_mid(BatchArgs A, const ItemRec* items, int n) {
+  constexpr int kSlots = TG / kWave;    // table slots per lane
+  constexpr int kKeys = kSlots / 2;     // ranking keys per lane (the table is at most half full)
+  __shared__ __align__(16) int32_t keys[TG];
+  __shared__ __align__(16) uint32_t vals[TG];
+  uint64_t* comp = reinterpret_cast<uint64_t*>(keys);    // TG / 2 keys over the table's
+  uint64_t* sorted = reinterpret_cast<uint64_t*>(vals);  // storage, once it is read
+  const int lane = threadIdx.x;
+  for (int ai = blockIdx.x; ai < n; ai += gridDim.x) {
+    const ItemRec it = items[ai];
+    const int L = (int)it.L;
+#pragma unroll
+    for (int i = 0; i < kSlots / 4; ++i) {
+      reinterpret_cast<int4*>(keys)[i * kWave + lane] = make_int4(-1, -1, -1, -1);
+      reinterpret_cast<uint4*>(vals)[i * kWave + lane] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    wave_sync();
+    constexpr int RB = S <= 8 ? 4 : (S == 16 ? 2 : 1);  // rows in flight per lane
+    for (int i0 = 0; i0 < L; i0 += RB * kWave) {
+      int32_t v[RB][S];
+      uint32_t pid[RB];
+#pragma unroll
+      for (int b = 0; b < RB; ++b) {
+        const int i = i0 + b * kWave + lane;
+        pid[b] = i < L ? A.inv_pid[it.a + i] : 0u;
+      }
+#pragma unroll
+      for (int b = 0; b < RB; ++b)
+        if (i0 + b * kWave + lane < L) load_row<S>(A.paths, pid[b], v[b]);
+#pragma unroll
+      for (int b = 0; b < RB; ++b) {
+        if (i0 + b * kWave + lane >= L) continue;
+        dedup_row<S>(v[b]);
+#pragma unroll
+        for (int j = 0; j < S; ++j)
+          if (v[b][j] >= 0 && v[b][j] != it.q) lds_insert(keys, vals, (uint32_t)TG - 1u, v[b][j]);
+      }
+    }
+    wave_sync();
+    // occupied slots to ranking keys
+    int32_t kk[kSlots];
+    uint32_t vv[kSlots];
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i) {
+      kk[i] = keys[i * kWave + lane];
+      vv[i] = vals[i * kWave + lane];
+    }
+    wave_sync();
+    const uint64_t below = (1ull << lane) - 1ull;
+    int nc = 0;
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i) {
+      const uint64_t bm = __ballot(kk[i] >= 0);
+      if (kk[i] >= 0) comp[nc + __popcll(bm & below)] = rank_key(vv[i], kk[i]);
+      nc += __popcll(bm);
+    }
+    wave_sync();
+    // a lower bound that k to `room` keys reach, by bisection on the key: a
+    // count is a compare and a ballot per key held (ties differ in their ids,
+    // so the search always gets there)
+    uint64_t x[kKeys];
+#pragma unroll
+    for (int i = 0; i < kKeys; ++i) x[i] = i * kWave + lane < nc ? comp[i * kWave + lane] : 0ull;
+    const int k = A.k;
+    int room = kWaveSort;
+    while (room < k) room <<= 1;
+    uint64_t lo = 1ull;  // every key
+    int m = nc;
+    uint64_t hi = (uint64_t)(L + 1) << 32;  // no key
+    while (m > room && hi - lo > 1ull) {
+      const uint64_t mid = lo + ((hi - lo) >> 1);
+      int c = 0;
+#pragma unroll
+      for (int i = 0; i < kKeys; ++i) c += __popcll(__ballot(x[i] >= mid));
+      if (c >= k) {
+        lo = mid;
+        m = c;
+      } else {
+        hi = mid;
+      }
+    }
+    m = 0;
+#pragma unroll
+    for (int i = 0; i < kKeys; ++i) {
+      const uint64_t bm = __ballot(x[i] >= lo);
+      if (x[i] >= lo) sorted[m + __popcll(bm & below)] = x[i];
+      m += __popcll(bm);
+    }
+    int P = 2;
+    while (P < m) P <<= 1;
+    for (int j = m + lane; j < P; j += kWave) sorted[j] = 0ull;
+    wave_sync();
+    for (int size = 2; size <= P; size <<= 1) {
+      for (int stride = size >> 1; stride > 0; stride >>= 1) {
+        for (int i = lane; i < (P >> 1); i += kWave) {
+          const int a = ((i & ~(stride - 1)) << 1) | (i & (stride - 1));  // stride: power of two
+          const int b = a + stride;
+          const bool desc = (a & size) == 0;
+          const uint64_t y = sorted[a], z = sorted[b];
+          if ((y < z) == desc) {
+            sorted[a] = z;
+            sorted[b] = y;
+          }
+        }
+        wave_sync();
+      }
+    }
+    write_row(A, it.qi, sorted, m < k ? m : k, lane, kWave);
+    wave_sync();
+  }
+}
+
 // ---- device planning of large batches ----
-// Digit of query i in the plan's order: tier B classes 64..0 (digits
-// 0..64), tier A classes 64..0 (65..129), then the hubs by class, 64..0
-// (130..194), then the repeated queries (195), which no tier sees; a stable
-// sort by digit gives the host planner's order.  Also writes the pair count
-// the sort reads and the query index as
-// the sort's value.
-constexpr uint32_t kHubDigit = 130;
+// The tiers' bounds on the list length (each at least the one before).
+struct TierBounds {
+  uint64_t A, M1, M2, B;
+};
+
+// Digit of a query in the plan's order: tier B classes 64..0 (digits 0..64),
+// tier M's wide and narrow tables (65, 66), tier A classes 64..0 (67..131),
+// then the hubs by class, 64..0 (132..196), then the repeated queries (197),
+// which no tier sees.  Each tier goes longest class first, stably.
+constexpr uint32_t kMidDigit = 65;
+constexpr uint32_t kWaveDigit = 67;
+constexpr uint32_t kHubDigit = kWaveDigit + 65;
 constexpr uint32_t kRepeatDigit = kHubDigit + 65;
 constexpr uint32_t kDigits = kRepeatDigit + 1;
-__global__ void k_plan_digits(const uint64_t* __restrict__ qlen, int64_t nq, uint64_t LA,
-                              uint64_t LB, uint32_t* __restrict__ keys,
-                              uint32_t* __restrict__ vals, uint64_t* __restrict__ nnz) {
+
+__host__ __device__ inline uint32_t plan_digit(uint64_t L, const TierBounds& t) {
+  if (L == kRepeated) return kRepeatDigit;
+  const uint32_t cl = L ? 64u - (uint32_t)__builtin_clzll(L) : 0u;
+  if (L > t.B) return kHubDigit + 64u - cl;
+  if (L > t.M2) return 64u - cl;
+  if (L > t.A) return kMidDigit + (L > t.M1 ? 0u : 1u);
+  return kWaveDigit + 64u - cl;
+}
+
+// Sort keys of the device planner; also writes the pair count the sort reads
+// and the query index as the sort's value.
+__global__ void k_plan_digits(const uint64_t* __restrict__ qlen, int64_t nq, TierBounds t,
+                              uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
+                              uint64_t* __restrict__ nnz) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i == 0) *nnz = (uint64_t)nq;
   if (i >= nq) return;
-  const uint64_t L = qlen[i];
-  const uint32_t cl = L ? 64u - (uint32_t)__clzll((long long)L) : 0u;
-  keys[i] = L == kRepeated
-                ? kRepeatDigit
-                : (L > LB ? kHubDigit : (L > LA ? 0u : 65u)) + (64u - cl);
+  keys[i] = plan_digit(qlen[i], t);
   vals[i] = (uint32_t)i;
 }
 
@@ -525,6 +664,19 @@ KernelFn pick_wave_kernel(int stride) {
     case 16: return k_topk_waves<16>;
     case 32: return k_topk_waves<32>;
     default: return k_topk_waves<64>;
+  }
+}
+
+using MidFn = void (*)(BatchArgs, const ItemRec*, int);
+
+template <int TG>
+MidFn pick_mid_kernel(int stride) {
+  switch (stride) {
+    case 4: return k_topk_mid<4, TG>;
+    case 8: return k_topk_mid<8, TG>;
+    case 16: return k_topk_mid<16, TG>;
+    case 32: return k_topk_mid<32, TG>;
+    default: return k_topk_mid<64, TG>;
   }
 }
 
@@ -644,6 +796,7 @@ struct BatchState {
   size_t hub_budget_forced = 0;  // option test.hub_budget (0 = automatic)
   // configuration
   bool tuned = false;
+  bool untuned = false;  // neither forced, cached nor tuned: cfg is chosen per batch
   BatchConfig cfg;
   int forced_block = 0;
   int forced_wgs = 0;
@@ -918,6 +1071,20 @@ static hipError_t enqueue(panther_ctx* c, BatchState* b, const Plan& P, KernelFn
       k_reset_queue<<<1, 64, 0, s>>>(P.args.queue);
       hipLaunchKernelGGL(fn, dim3(grid), dim3(block), lds, s, P.args);
     }
+    // one wavefront each, as many as the LDS of all CUs holds
+    auto mid_grid = [&](int n, int TG) {
+      return dim3((unsigned)std::min(n, c->num_cus * (163840 / (8 * TG))));
+    };
+    // (a few for the narrow table join the wide one's launch: they would not
+    // fill the chip either way)
+    const bool join = P.args.nM2 > 0 && P.args.nM1 <= c->num_cus;
+    const int nM2 = P.args.nM2 + (join ? P.args.nM1 : 0), nM1 = join ? 0 : P.args.nM1;
+    if (nM2 > 0)
+      hipLaunchKernelGGL(pick_mid_kernel<kMid2>(c->stride), mid_grid(nM2, kMid2), dim3(kWave), 0,
+                         s, P.args, P.args.itemsM, nM2);
+    if (nM1 > 0)
+      hipLaunchKernelGGL(pick_mid_kernel<kMid1>(c->stride), mid_grid(nM1, kMid1), dim3(kWave), 0,
+                         s, P.args, P.args.itemsM + P.args.nM2, nM1);
     if (P.args.nA > 0) {
       const int wgrid = c->num_cus * kWaveWgsPerCu;
       hipLaunchKernelGGL(pick_wave_kernel(c->stride), dim3(wgrid), dim3(kWaveBlock), 0, s,
@@ -1156,14 +1323,13 @@ static int plan_hubs(panther_ctx* c, BatchState* b,
 // one stable pass of the index's radix sort (8-bit digit, query index as
 // the value) straight into d_items, so the tier items need no host pass and
 // no upload.  Only the digit starts and the hubs' lengths come back.
-// Fills nB, need (tier items), cntA (tier A items per length class) and C
-// (the hubs, in batch order), and says whether queries are repeated.
+// Fills the digits' starts and C (the hubs).
 bool batched_plan_on_device(int64_t nq) { return nq >= ((int64_t)1 << 20); }
 
 static int plan_on_device(panther_ctx* c, BatchState* b, const uint64_t* dqlen, int64_t nq,
-                          uint64_t LA, uint64_t LB, hipStream_t s, bool with_hubs, size_t* nB,
-                          size_t* need, std::array<size_t, 65>& cntA,
-                          std::vector<std::pair<uint64_t, int32_t>>* C, bool* repeats) {
+                          const TierBounds& tb, hipStream_t s, bool with_hubs,
+                          std::array<size_t, kDigits + 1>* starts,
+                          std::vector<std::pair<uint64_t, int32_t>>* C) {
   const uint64_t n = (uint64_t)nq;
   const uint64_t ntiles = radix_tiles_pairs(n);
   const size_t nh = (size_t)256 * ntiles;
@@ -1183,8 +1349,8 @@ static int plan_on_device(panther_ctx* c, BatchState* b, const uint64_t* dqlen, 
     return st;
   uint64_t* d_nnz = b->dp_small;
   uint64_t* d_starts = b->dp_small + 1;
-  k_plan_digits<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(dqlen, nq, LA, LB, b->dp_keys,
-                                                            b->dp_vals, d_nnz);
+  k_plan_digits<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(dqlen, nq, tb, b->dp_keys, b->dp_vals,
+                                                            d_nnz);
   launch_radix_up_pairs(b->dp_keys, d_nnz, n, 0, 8, b->dp_hist, s);
   launch_scan_u32_to_u64(b->dp_hist, b->dp_offs, (int64_t)nh, b->dp_scan, s);
   launch_radix_down_pairs(b->dp_keys, b->dp_vals, d_nnz, n, 0, 8, b->dp_offs, b->dp_keys2,
@@ -1197,11 +1363,8 @@ static int plan_on_device(panther_ctx* c, BatchState* b, const uint64_t* dqlen, 
       (st = ctx_hip(c, hipStreamSynchronize(s), "batch plan")))
     return st;
   const uint64_t* sp = static_cast<const uint64_t*>(b->pin_starts.p);
-  *nB = (size_t)sp[65];
-  *need = (size_t)sp[kHubDigit];
-  for (int c2 = 0; c2 <= 64; ++c2) cntA[c2] = (size_t)(sp[65 + (64 - c2) + 1] - sp[65 + (64 - c2)]);
+  for (size_t d = 0; d < kStarts; ++d) (*starts)[d] = (size_t)sp[d];
   const size_t nC = (size_t)(sp[kRepeatDigit] - sp[kHubDigit]);
-  *repeats = sp[kDigits] != sp[kRepeatDigit];
   C->clear();
   if (!with_hubs || !nC) return PANTHER_OK;
   const int32_t* hub_idx = b->d_items + sp[kHubDigit];
@@ -1236,10 +1399,14 @@ static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int
                 Plan* out, std::vector<int32_t>* host_items) {
   const Layout lay = layout_for(c, cfg);
   const uint64_t T = (uint64_t)c->T;
-  uint64_t LA = (uint64_t)lay.TA / (2 * T);
-  uint64_t LB = (uint64_t)lay.TB / (2 * T) / (uint64_t)cfg.tier_b_div;
-  if (b->tier_a_override >= 0) LA = std::min(LA, (uint64_t)b->tier_a_override);
-  if (b->tier_b_override >= 0) LB = std::min(LB, (uint64_t)b->tier_b_override);
+  TierBounds tb{(uint64_t)lay.TA / (2 * T), kMid1 / (2 * T), kMid2 / (2 * T),
+                (uint64_t)lay.TB / (2 * T) / (uint64_t)cfg.tier_b_div};
+  if (b->tier_a_override >= 0)
+    for (uint64_t* l : {&tb.A, &tb.M1, &tb.M2}) *l = std::min(*l, (uint64_t)b->tier_a_override);
+  if (b->tier_b_override >= 0) tb.B = std::min(tb.B, (uint64_t)b->tier_b_override);
+  tb.A = std::min(tb.A, tb.B);
+  tb.M1 = std::min(std::max(tb.M1, tb.A), tb.B);
+  tb.M2 = std::min(std::max(tb.M2, tb.M1), tb.B);
   // the wave-tier sort buffer holds TA/2 keys and the block selection keeps
   // at most kCand keys without radix narrowing; both are covered by the
   // load bound T * L <= table / 2.  Every tier is ordered by power-of-two
@@ -1247,37 +1414,16 @@ static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int
   // two passes, the LDS tiers' items written straight into the pinned upload
   // buffer.  (Hubs were ordered by exact length, which brought the repeats of
   // a vertex together; they are answered once now.)
-  auto cls = [](uint64_t L) { return L ? 64 - __builtin_clzll(L) : 0; };
-  std::array<size_t, 65> cntA{};  // tier A items per length class
-  size_t nB = 0, need = 0;
+  std::array<size_t, kDigits + 1> start{};  // of each digit of plan_digit
   std::vector<std::pair<uint64_t, int32_t>> C;
   int st;
   const bool on_device = qlen == nullptr;
   if (on_device) {
-    if ((st = plan_on_device(c, b, dqlen, nq, LA, LB, s, with_hubs, &nB, &need, cntA, &C,
-                             &out->repeats)))
-      return st;
+    if ((st = plan_on_device(c, b, dqlen, nq, tb, s, with_hubs, &start, &C))) return st;
   } else {
-    // bucket of a query: tier B classes 64..0, tier A classes 64..0, hub
-    // classes 64..0 (repeated queries have none)
-    auto bucket = [&](uint64_t L) { return (L > LB ? 130 : (L > LA ? 0 : 65)) + 64 - cls(L); };
-    std::array<size_t, 195> pos{};
-    out->repeats = false;
-    for (int64_t i = 0; i < nq; ++i) {
-      if (qlen[i] == kRepeated)
-        out->repeats = true;
-      else
-        ++pos[bucket(qlen[i])];
-    }
-    for (int c2 = 0; c2 <= 64; ++c2) cntA[c2] = pos[65 + 64 - c2];
-    size_t run = 0;
-    for (int bk = 0; bk < 195; ++bk) {
-      if (bk == 65) nB = run;
-      if (bk == 130) need = run;
-      const size_t m = pos[bk];
-      pos[bk] = run;
-      run += m;
-    }
+    for (int64_t i = 0; i < nq; ++i) ++start[plan_digit(qlen[i], tb) + 1];
+    for (uint32_t d = 0; d < kDigits; ++d) start[d + 1] += start[d];
+    const size_t need = start[kHubDigit];
     // the pinned staging of the previous plan must have been consumed
     if (b->upload_pending) {
       if ((st = ctx_hip(c, hipEventSynchronize(b->uploaded), "batch plan"))) return st;
@@ -1286,17 +1432,18 @@ static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int
     if (need && (st = pinned_ensure(c, b->pin_items, sizeof(int32_t) * need, "batch plan")))
       return st;
     int32_t* items = static_cast<int32_t*>(b->pin_items.p);
-    if (with_hubs) C.resize(run - need);
+    if (with_hubs) C.resize(start[kRepeatDigit] - need);
+    std::array<size_t, kDigits + 1> pos = start;
     for (int64_t i = 0; i < nq; ++i) {
-      const uint64_t L = qlen[i];
-      if (L == kRepeated || (L > LB && !with_hubs)) continue;
-      const size_t at = pos[bucket(L)]++;
-      if (L > LB)
-        C[at - need] = {L, (int32_t)i};
-      else
-        items[at] = (int32_t)i;
+      const uint32_t d = plan_digit(qlen[i], tb);
+      if (d < kHubDigit)
+        items[pos[d]++] = (int32_t)i;
+      else if (d < kRepeatDigit && with_hubs)
+        C[pos[d]++ - need] = {qlen[i], (int32_t)i};
     }
   }
+  const size_t nB = start[kMidDigit], need = start[kHubDigit];
+  out->repeats = start[kDigits] != start[kRepeatDigit];
   // tier A phases: class c (lengths below 2^c) runs in groups of G lanes
   // when T * (2^c - 1) fits half of the group's table (kWaveTA * G / 64);
   // the classes are in descending order, so each phase is a range
@@ -1305,7 +1452,8 @@ static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int
   };
   size_t nA64 = 0, nA32 = 0, nA16 = 0;
   for (int c2 = 64; c2 >= 0; --c2) {
-    const size_t m = cntA[c2];
+    const uint32_t d = kWaveDigit + 64u - (uint32_t)c2;
+    const size_t m = start[d + 1] - start[d];
     if (!fits(c2, 32)) nA64 += m;
     if (!fits(c2, 16)) nA32 += m;
     if (!fits(c2, 8)) nA16 += m;
@@ -1350,9 +1498,12 @@ static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int
   BatchArgs a{};
   a.queries = dq;
   a.itemsB = b->d_irec;
-  a.itemsA = b->d_irec + nB;
+  a.itemsM = b->d_irec + nB;
+  a.itemsA = b->d_irec + start[kWaveDigit];
   a.nB = (int32_t)nB;
-  a.nA = (int32_t)(need - nB);
+  a.nM2 = (int32_t)(start[kMidDigit + 1] - start[kMidDigit]);
+  a.nM1 = (int32_t)(start[kWaveDigit] - start[kMidDigit + 1]);
+  a.nA = (int32_t)(need - start[kWaveDigit]);
   a.nA64 = (int32_t)nA64;
   a.nA32 = (int32_t)nA32;
   a.nA16 = (int32_t)nA16;
@@ -1386,7 +1537,8 @@ BatchSizing batched_sizing(panther_ctx* c, Lane* lane) {
   z.LB = ~0ull;
   z.bucket_bias = 0;
   // before its first call a lane may still pick any configuration
-  const std::vector<BatchConfig> cs = b->tuned ? std::vector<BatchConfig>{b->cfg} : config_space(b);
+  const std::vector<BatchConfig> cs =
+      b->tuned && !b->untuned ? std::vector<BatchConfig>{b->cfg} : config_space(b);
   for (const BatchConfig& cf : cs) {
     const Layout lay = layout_for(c, cf);
     z.LB = std::min<uint64_t>(z.LB, (uint64_t)lay.TB / (2 * z.T) / (uint64_t)cf.tier_b_div);
@@ -1462,11 +1614,13 @@ int run_batched(panther_ctx* c, Lane* lane, const int32_t* dq, const uint64_t* q
   int k_bucket = 1;
   while (k_bucket < k) k_bucket <<= 1;
   char key[256];
-  snprintf(key, sizeof key, "gfx950:n%d:T%d:R%lld:nq2^%d:k%d:cu%d:f%d", c->n, c->T,
+  snprintf(key, sizeof key, "gfx950:m:n%d:T%d:R%lld:nq2^%d:k%d:cu%d:f%d", c->n, c->T,
            (long long)c->R, nq_bucket, k_bucket, c->num_cus, theta ? 1 : 0);
   if (b->tuned && !forced && b->tune_key != key) b->tuned = false;
+  if (forced) b->untuned = false;
   if (!b->tuned) {
     b->tune_key = key;
+    b->untuned = false;
     BatchConfig cached;
     if (tune_lookup(b->tune_key, &cached)) {
       b->cfg = cached;
@@ -1565,7 +1719,19 @@ int run_batched(panther_ctx* c, Lane* lane, const int32_t* dq, const uint64_t* q
     } else {
       b->cfg = BatchConfig{};
       b->tuned = true;
+      b->untuned = true;
     }
+  }
+  if (b->untuned && qlen) {
+    // A batch too small to tune (or a serving lane's): tier B's largest table
+    // where that spares the hub pipeline; where the longest list needs the
+    // pipeline anyway, the smallest, which leaves tier B empty (61 queries of
+    // R-MAT 20, k = 200: 0.157 ms, 0.21 with the largest).
+    const BatchConfig wide{};
+    const uint64_t LB = (uint64_t)layout_for(c, wide).TB / (2 * (uint64_t)c->T);
+    bool hub = false;
+    for (int64_t i = 0; i < nq && !hub; ++i) hub = qlen[i] > LB && qlen[i] != kRepeated;
+    b->cfg = hub ? BatchConfig{512, 2, 2, 0} : wide;
   }
   int st = plan(c, b, b->cfg, dq, qlen, dqlen, nq, k, d_ids, d_counts, d_len, theta, s, true,
                 &args, &items);
