@@ -640,19 +640,24 @@ __global__ void k_plan_hub_lengths(const int32_t* __restrict__ idx, int64_t n,
   if (i < n) out[i] = qlen[idx[i]];
 }
 
-__global__ void k_expand_items(const int32_t* __restrict__ items, int64_t n,
-                               const int32_t* __restrict__ queries,
-                               const uint64_t* __restrict__ inv_ptr, ItemRec* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// What a launch starts with: the tier items expanded into records, the work
+// queue reset, and the first hub chunk's maps and counters (later chunks
+// prepare theirs, which share buffers, when the one before is done).
+__global__ void __launch_bounds__(256)
+k_begin(const int32_t* __restrict__ items, int32_t n, const int32_t* __restrict__ queries,
+        const uint64_t* __restrict__ inv_ptr, ItemRec* __restrict__ out, uint32_t* queue,
+        uint32_t item_blocks, HubArgs hub) {
+  if (blockIdx.x >= item_blocks) {
+    hub_prep_query(hub, (int)(blockIdx.x - item_blocks));
+    return;
+  }
+  if (blockIdx.x == 0 && threadIdx.x < kQueueCtl) queue[threadIdx.x] = 0u;
+  const int32_t i = (int32_t)(blockIdx.x * 256 + threadIdx.x);
   if (i >= n) return;
   const int32_t qi = items[i];
   const int32_t q = queries[qi];
   const uint64_t a = inv_ptr[q];
   out[i] = ItemRec{a, (uint32_t)(inv_ptr[q + 1] - a), qi, q, 0};
-}
-
-__global__ void k_reset_queue(uint32_t* q) {
-  if (threadIdx.x < kQueueCtl) q[threadIdx.x] = 0u;
 }
 
 using KernelFn = void (*)(BatchArgs);
@@ -714,12 +719,16 @@ constexpr int64_t kStage2MaxQueries = (int64_t)1 << 18;  // batches the second s
 // persistent kernel over tiers A and B.
 struct Plan {
   BatchArgs args{};
+  const int32_t* items = nullptr;  // tier items, tier after tier
+  ItemRec* recs = nullptr;         // and their records (args.itemsB)
+  int32_t need = 0;
   bool run_kernel = false;
   int stride = 0;  // path row stride: selects the kernel specialisations
   std::vector<HubArgs> hub;
   bool repeats = false;  // some queries are copies of others (not part of the launch)
   bool operator==(const Plan& o) const {
-    if (run_kernel != o.run_kernel || stride != o.stride || hub.size() != o.hub.size())
+    if (run_kernel != o.run_kernel || stride != o.stride || hub.size() != o.hub.size() ||
+        items != o.items || recs != o.recs || need != o.need)
       return false;
     if (std::memcmp(&args, &o.args, sizeof(args)) != 0) return false;
     for (size_t i = 0; i < hub.size(); ++i)
@@ -730,14 +739,14 @@ struct Plan {
 
 struct BatchState {
   // device plan buffers (grown as needed)
-  int32_t* d_items = nullptr;
+  char* d_plan = nullptr;  // hub plan, then (planned on the host) the tier items
+  size_t plan_cap = 0;
+  int32_t* d_items = nullptr;  // items of a batch planned on the device
   size_t items_cap = 0;
-  ItemRec* d_irec = nullptr;  // the tier items expanded (k_expand_items)
+  ItemRec* d_irec = nullptr;  // the tier items expanded (k_begin)
   size_t irec_cap = 0;
   uint32_t* d_queue = nullptr;
   // hub pipeline buffers (grown as needed)
-  HubQuery* d_hq = nullptr;
-  size_t hq_cap = 0;
   int32_t* d_stA = nullptr;
   size_t occ_cap = 0;
   int32_t* d_stB = nullptr;
@@ -769,7 +778,7 @@ struct BatchState {
   char* d_scan = nullptr;
   size_t scan_cap = 0;
   // page-locked staging of the plan; `uploaded` guards its reuse
-  PinnedBuf pin_items, pin_hq;
+  PinnedBuf pin_plan;
   // device planning of large batches: digit keys, the sort's scratch, the
   // digit starts and the hubs' lengths (and their pinned copies)
   uint32_t* dp_keys = nullptr;
@@ -859,18 +868,18 @@ void free_batch_state(Lane* lane) {
   if (b->ev_fork) (void)hipEventDestroy(b->ev_fork);
   if (b->ev_join) (void)hipEventDestroy(b->ev_join);
   if (b->side) (void)hipStreamDestroy(b->side);
-  pinned_release(b->pin_items);
-  pinned_release(b->pin_hq);
+  pinned_release(b->pin_plan);
   pinned_release(b->pin_starts);
   pinned_release(b->pin_hubL);
   pinned_release(b->pin_hubI);
   for (void* p : {(void*)b->dp_keys, (void*)b->dp_keys2, (void*)b->dp_vals, (void*)b->dp_hist,
                   (void*)b->dp_offs, (void*)b->dp_scan, (void*)b->dp_small, (void*)b->dp_hubL})
     ctx_free(p);
+  ctx_free(b->d_plan);
   ctx_free(b->d_items);
   ctx_free(b->d_irec);
   ctx_free(b->d_queue);
-  for (void* p : {(void*)b->d_hq, (void*)b->d_stA, (void*)b->d_stB, (void*)b->d_bkt_cnt,
+  for (void* p : {(void*)b->d_stA, (void*)b->d_stB, (void*)b->d_bkt_cnt,
                   (void*)b->d_bkt_fill, (void*)b->d_bkt_start, (void*)b->d_cand,
                   (void*)b->d_cand_n, (void*)b->d_scan, (void*)b->d_hx,
                   (void*)b->d_tile_owner, (void*)b->d_stile_owner, (void*)b->d_bkt_owner,
@@ -1055,6 +1064,14 @@ static int grow(panther_ctx* c, P*& ptr, size_t& cap, size_t want, size_t elem, 
 static hipError_t enqueue(panther_ctx* c, BatchState* b, const Plan& P, KernelFn fn, int grid,
                           int block, size_t lds, hipStream_t s) {
   const bool fork = !P.hub.empty() && P.run_kernel && !b->no_fork;
+  {
+    const HubArgs none{};
+    const uint32_t item_blocks = (uint32_t)std::max(1, (P.need + 255) / 256);
+    const uint32_t hubs = P.hub.empty() ? 0u : (uint32_t)P.hub[0].nq;
+    k_begin<<<item_blocks + hubs, 256, 0, s>>>(P.items, P.need, P.args.queries, P.args.inv_ptr,
+                                               P.recs, P.args.queue, item_blocks,
+                                               P.hub.empty() ? none : P.hub[0]);
+  }
   hipStream_t hs = s;
   if (fork) {
     hipError_t e = hipEventRecord(b->ev_fork, s);
@@ -1063,29 +1080,35 @@ static hipError_t enqueue(panther_ctx* c, BatchState* b, const Plan& P, KernelFn
     hs = b->side;
   }
   for (const HubArgs& h : P.hub) {
-    const hipError_t e = enqueue_hub_chunk(h, c->stride, b->d_scan, hs);
+    const hipError_t e = enqueue_hub_chunk(h, c->stride, b->d_scan, hs, &h != &P.hub[0]);
     if (e != hipSuccess) return e;
   }
   if (P.run_kernel) {
     if (P.args.nB > 0) {
-      k_reset_queue<<<1, 64, 0, s>>>(P.args.queue);
       hipLaunchKernelGGL(fn, dim3(grid), dim3(block), lds, s, P.args);
     }
     // one wavefront each, as many as the LDS of all CUs holds
     auto mid_grid = [&](int n, int TG) {
       return dim3((unsigned)std::min(n, c->num_cus * (163840 / (8 * TG))));
     };
-    // (a few for the narrow table join the wide one's launch: they would not
-    // fill the chip either way)
-    const bool join = P.args.nM2 > 0 && P.args.nM1 <= c->num_cus;
-    const int nM2 = P.args.nM2 + (join ? P.args.nM1 : 0), nM1 = join ? 0 : P.args.nM1;
+    // Few queries of the wavefront tiers go in one launch, tier M's and A's
+    // alike, with the widest table that any of them needs (they would not fill
+    // the chip in launches of their own, and each costs about 8 us).
+    int nM2 = P.args.nM2, nM1 = P.args.nM1, nA = P.args.nA;
+    if (nM2 > 0 && nM2 + nM1 + nA <= 4 * c->num_cus) {
+      nM2 += nM1 + nA;
+      nM1 = nA = 0;
+    } else if (nM1 > 0 && nM1 + nA <= 4 * c->num_cus) {
+      nM1 += nA;
+      nA = 0;
+    }
     if (nM2 > 0)
       hipLaunchKernelGGL(pick_mid_kernel<kMid2>(c->stride), mid_grid(nM2, kMid2), dim3(kWave), 0,
                          s, P.args, P.args.itemsM, nM2);
     if (nM1 > 0)
       hipLaunchKernelGGL(pick_mid_kernel<kMid1>(c->stride), mid_grid(nM1, kMid1), dim3(kWave), 0,
                          s, P.args, P.args.itemsM + P.args.nM2, nM1);
-    if (P.args.nA > 0) {
+    if (nA > 0) {
       const int wgrid = c->num_cus * kWaveWgsPerCu;
       hipLaunchKernelGGL(pick_wave_kernel(c->stride), dim3(wgrid), dim3(kWaveBlock), 0, s,
                          P.args);
@@ -1164,19 +1187,17 @@ static int launch_batched(panther_ctx* c, BatchState* b, const BatchConfig& cfg,
 }
 
 // Splits the hub queries (longest class first) into chunks whose staging fits a
-// memory budget, and fills the device buffers and per-chunk arguments.
+// memory budget, and fills the plan hq (uploaded to d_hq by the caller), the
+// device buffers and the per-chunk arguments.
 static int plan_hubs(panther_ctx* c, BatchState* b,
                      const std::vector<std::pair<uint64_t, int32_t>>& C,
-                     const int32_t* dq, int32_t k, int bias, int32_t* d_ids, uint32_t* d_counts,
-                     int32_t* d_len, float* theta, hipStream_t s, std::vector<HubArgs>* out) {
+                     HubQuery* hq, const HubQuery* d_hq, const int32_t* dq, int32_t k, int bias,
+                     int32_t* d_ids, uint32_t* d_counts, int32_t* d_len, float* theta,
+                     std::vector<HubArgs>* out) {
   out->clear();
   if (C.empty()) return PANTHER_OK;
   const uint64_t T = (uint64_t)c->T;
-  // the plan is written straight into the pinned upload buffer (the
-  // previous plan's upload has completed: plan waits for it)
   int st;
-  if ((st = pinned_ensure(c, b->pin_hq, sizeof(HubQuery) * C.size(), "hub plan"))) return st;
-  HubQuery* hq = static_cast<HubQuery*>(b->pin_hq.p);
   size_t nhq = 0;
   if (!b->hub_budget) {
     size_t free_b = 0, total_b = 0;
@@ -1249,7 +1270,6 @@ static int plan_hubs(panther_ctx* c, BatchState* b,
     cur.ths += (uint64_t)stiles * nb;
   }
   close();
-  if ((st = grow(c, b->d_hq, b->hq_cap, nhq, sizeof(HubQuery), "hub plan"))) return st;
   if ((st = grow(c, b->d_stA, b->occ_cap, max_occ, sizeof(int32_t), "hub staging"))) return st;
   if ((st = grow(c, b->d_stB, b->occB_cap, max_occ, sizeof(int32_t), "hub staging"))) return st;
   if ((st = grow(c, b->d_bkt_cnt, b->bkt_cap, max_bkt, sizeof(uint32_t), "hub buckets"))) return st;
@@ -1277,17 +1297,13 @@ static int plan_hubs(panther_ctx* c, BatchState* b,
     return st;
   if ((st = grow(c, b->d_th, b->th_cap, max_ths, sizeof(uint32_t), "hub tile counts")))
     return st;
-  st = ctx_hip(c, hipMemcpyAsync(b->d_hq, b->pin_hq.p, sizeof(HubQuery) * nhq,
-                                 hipMemcpyHostToDevice, s),
-               "hub plan upload");
-  if (st) return st;
   for (const Chunk& ch : chunks) {
     HubArgs h{};
     h.queries = dq;
     h.inv_ptr = c->d_inv_ptr;
     h.inv_pid = c->d_inv_pid;
     h.paths = c->d_paths;
-    h.hq = b->d_hq + ch.first;
+    h.hq = d_hq + ch.first;
     h.hx = b->d_hx;
     h.tile_owner = b->d_tile_owner;
     h.stile_owner = b->d_stile_owner;
@@ -1396,7 +1412,7 @@ static int plan_on_device(panther_ctx* c, BatchState* b, const uint64_t* dqlen, 
 static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int32_t* dq,
                 const uint64_t* qlen, const uint64_t* dqlen, int64_t nq, int32_t k, int32_t* d_ids,
                 uint32_t* d_counts, int32_t* d_len, float* theta, hipStream_t s, bool with_hubs,
-                Plan* out, std::vector<int32_t>* host_items) {
+                Plan* out) {
   const Layout lay = layout_for(c, cfg);
   const uint64_t T = (uint64_t)c->T;
   TierBounds tb{(uint64_t)lay.TA / (2 * T), kMid1 / (2 * T), kMid2 / (2 * T),
@@ -1424,15 +1440,25 @@ static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int
     for (int64_t i = 0; i < nq; ++i) ++start[plan_digit(qlen[i], tb) + 1];
     for (uint32_t d = 0; d < kDigits; ++d) start[d + 1] += start[d];
     const size_t need = start[kHubDigit];
-    // the pinned staging of the previous plan must have been consumed
-    if (b->upload_pending) {
-      if ((st = ctx_hip(c, hipEventSynchronize(b->uploaded), "batch plan"))) return st;
-      b->upload_pending = false;
-    }
-    if (need && (st = pinned_ensure(c, b->pin_items, sizeof(int32_t) * need, "batch plan")))
-      return st;
-    int32_t* items = static_cast<int32_t*>(b->pin_items.p);
-    if (with_hubs) C.resize(start[kRepeatDigit] - need);
+    if (with_hubs) C.resize(start[kRepeatDigit] - start[kHubDigit]);
+  }
+  const size_t nB = start[kMidDigit], need = start[kHubDigit];
+  out->repeats = start[kDigits] != start[kRepeatDigit];
+  // One upload: the hub plan, then the items of a batch planned here.  The
+  // pinned staging of the previous plan must have been consumed.
+  if (b->upload_pending) {
+    if ((st = ctx_hip(c, hipEventSynchronize(b->uploaded), "batch plan"))) return st;
+    b->upload_pending = false;
+  }
+  const size_t items_at = sizeof(HubQuery) * C.size();
+  const size_t plan_bytes = items_at + (on_device ? 0 : sizeof(int32_t) * need);
+  if ((st = pinned_ensure(c, b->pin_plan, plan_bytes, "batch plan")) ||
+      (st = grow(c, b->d_plan, b->plan_cap, std::max<size_t>(plan_bytes, 4096), 1, "batch plan")))
+    return st;
+  HubQuery* hq = static_cast<HubQuery*>(b->pin_plan.p);
+  const HubQuery* d_hq = reinterpret_cast<const HubQuery*>(b->d_plan);
+  int32_t* items = reinterpret_cast<int32_t*>(static_cast<char*>(b->pin_plan.p) + items_at);
+  if (!on_device) {
     std::array<size_t, kDigits + 1> pos = start;
     for (int64_t i = 0; i < nq; ++i) {
       const uint32_t d = plan_digit(qlen[i], tb);
@@ -1442,8 +1468,6 @@ static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int
         C[pos[d]++ - need] = {qlen[i], (int32_t)i};
     }
   }
-  const size_t nB = start[kMidDigit], need = start[kHubDigit];
-  out->repeats = start[kDigits] != start[kRepeatDigit];
   // tier A phases: class c (lengths below 2^c) runs in groups of G lanes
   // when T * (2^c - 1) fits half of the group's table (kWaveTA * G / 64);
   // the classes are in descending order, so each phase is a range
@@ -1458,36 +1482,26 @@ static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int
     if (!fits(c2, 16)) nA32 += m;
     if (!fits(c2, 8)) nA16 += m;
   }
-  // the pinned hub plan of the previous call must have been consumed too
-  if (b->upload_pending) {
-    if ((st = ctx_hip(c, hipEventSynchronize(b->uploaded), "batch plan"))) return st;
-    b->upload_pending = false;
-  }
-  st = plan_hubs(c, b, C, dq, k, cfg.bucket_bias, d_ids, d_counts, d_len, theta, s, &out->hub);
+  st = plan_hubs(c, b, C, hq, d_hq, dq, k, cfg.bucket_bias, d_ids, d_counts, d_len, theta,
+                 &out->hub);
   if (st) return st;
-  host_items->clear();
-  if (!on_device &&
-      (st = grow(c, b->d_items, b->items_cap, std::max<size_t>(need, 1024), sizeof(int32_t),
-                 "batch plan")))
-    return st;
   if (!b->d_queue) {
     void* p;
     st = ctx_alloc(c, &p, 64, "batch queue");
     if (st) return st;
     b->d_queue = static_cast<uint32_t*>(p);
   }
-  if (!on_device && need) {
-    st = ctx_hip(c, hipMemcpyAsync(b->d_items, b->pin_items.p, sizeof(int32_t) * need,
-                                   hipMemcpyHostToDevice, s),
+  if (plan_bytes) {
+    st = ctx_hip(c, hipMemcpyAsync(b->d_plan, b->pin_plan.p, plan_bytes, hipMemcpyHostToDevice, s),
                  "batch plan upload");
     if (st) return st;
   }
-  if (need) {
-    if ((st = grow(c, b->d_irec, b->irec_cap, need, sizeof(ItemRec), "batch plan"))) return st;
-    k_expand_items<<<(unsigned)((need + 255) / 256), 256, 0, s>>>(b->d_items, (int64_t)need, dq,
-                                                                   c->d_inv_ptr, b->d_irec);
-    if ((st = ctx_hip(c, hipGetLastError(), "batch plan"))) return st;
-  }
+  if ((st = grow(c, b->d_irec, b->irec_cap, std::max<size_t>(need, 1), sizeof(ItemRec),
+                 "batch plan")))
+    return st;
+  out->items = on_device ? b->d_items : reinterpret_cast<const int32_t*>(b->d_plan + items_at);
+  out->recs = b->d_irec;
+  out->need = (int32_t)need;
   if (!b->uploaded) {
     st = ctx_hip(c, hipEventCreateWithFlags(&b->uploaded, hipEventDisableTiming), "batch plan");
     if (st) return st;
@@ -1566,7 +1580,7 @@ size_t batched_query_bytes(const BatchSizing& z, uint64_t L, int32_t kmax) {
 }
 
 // Device bytes of a batched call's fixed buffers (plan minimum, queue).
-size_t batched_fixed_bytes() { return sizeof(int32_t) * 1024 + 64 + sizeof(uint32_t) * 16 + 256; }
+size_t batched_fixed_bytes() { return 4096 + sizeof(ItemRec) + 64 + sizeof(uint32_t) * 16 + 256; }
 
 // Device bytes the lane's query scratch holds now.
 size_t lane_device_bytes(const Lane* lane) {
@@ -1577,8 +1591,9 @@ size_t lane_device_bytes(const Lane* lane) {
     t += d->p ? d->cap : 0;
   const BatchState* b = lane->batch;
   if (!b) return t;
-  t += sizeof(int32_t) * b->items_cap + sizeof(ItemRec) * b->irec_cap + (b->d_queue ? 64 : 0);
-  t += sizeof(HubQuery) * b->hq_cap + sizeof(int32_t) * (b->occ_cap + b->occB_cap);
+  t += b->plan_cap + sizeof(int32_t) * b->items_cap + sizeof(ItemRec) * b->irec_cap +
+       (b->d_queue ? 64 : 0);
+  t += sizeof(int32_t) * (b->occ_cap + b->occB_cap);
   t += sizeof(uint32_t) * (b->bkt_cap + b->bkt_fill_cap + b->redo_cap + b->cand_n_cap);
   t += sizeof(uint64_t) * (b->bkt_start_cap + b->cand_cap + b->bkt_cand0_cap);
   t += sizeof(HubList) * b->hx_cap + b->scan_cap;
@@ -1593,7 +1608,6 @@ int run_batched(panther_ctx* c, Lane* lane, const int32_t* dq, const uint64_t* q
                 int32_t k, int32_t* d_ids, uint32_t* d_counts, int32_t* d_len, float* theta,
                 hipStream_t s) {
   BatchState* b = state(lane);
-  std::vector<int32_t> items;
   Plan args;
   const uint64_t* dqlen = static_cast<const uint64_t*>(lane->b_qlen.p);
   // configuration: forced, cached, autotuned, or the default
@@ -1657,7 +1671,7 @@ int run_batched(panther_ctx* c, Lane* lane, const int32_t* dq, const uint64_t* q
       }
       auto time_cfg = [&](const BatchConfig& cfg, int64_t m, bool hubs, float* ms_out) -> int {
         int r = plan(c, b, cfg, dq, hubs ? qlen : tq, dqlen, m, k, d_ids, d_counts, d_len, theta,
-                     s, hubs, &args, &items);
+                     s, hubs, &args);
         if (r) return r;
         float best_ms = 1e30f;
         for (int rep = 0; rep < 3; ++rep) {
@@ -1734,7 +1748,7 @@ int run_batched(panther_ctx* c, Lane* lane, const int32_t* dq, const uint64_t* q
     b->cfg = hub ? BatchConfig{512, 2, 2, 0} : wide;
   }
   int st = plan(c, b, b->cfg, dq, qlen, dqlen, nq, k, d_ids, d_counts, d_len, theta, s, true,
-                &args, &items);
+                &args);
   if (st) return st;
   // the plan's pinned staging is guarded by b->uploaded; nothing here waits
   if ((st = launch_batched(c, b, b->cfg, args, s, true))) return st;

@@ -73,13 +73,39 @@ struct HubArgs {
   float fR;
 };
 
+// Per query j of the chunk, by 256 threads: its list bounds, the owner maps of
+// its tiles and buckets, and zeroed bucket counters.
+__device__ __forceinline__ void hub_prep_query(const HubArgs& A, int j) {
+  const HubQuery Q = A.hq[j];
+  const bool last = j + 1 == A.nq;
+  const uint32_t t1 = last ? A.n_tiles : A.hq[j + 1].tile0;
+  const uint32_t s1 = last ? A.n_stiles : A.hq[j + 1].stile0;
+  const uint32_t nb = Q.nb;
+  if (threadIdx.x == 0) {
+    const int32_t q = A.queries[Q.qi];
+    const uint64_t a = A.inv_ptr[q];
+    A.hx[j] = HubList{a, A.inv_ptr[q + 1] - a, q, 0};
+    A.cand_n[j] = 0u;
+  }
+  for (uint32_t t = Q.tile0 + threadIdx.x; t < t1; t += 256) A.tile_owner[t] = j;
+  for (uint32_t t = Q.stile0 + threadIdx.x; t < s1; t += 256) A.stile_owner[t] = j;
+  for (uint32_t b = threadIdx.x; b < nb; b += 256) {
+    A.bkt_owner[Q.bkt0 + b] = j;
+    A.bkt_cand0[Q.bkt0 + b] = Q.cand0;
+    A.bkt_cnt[Q.bkt0 + b] = 0u;
+    A.bkt_fill[Q.bkt0 + b] = 0u;
+  }
+  if (j == 0 && threadIdx.x == 0) *A.redo_n = 0u;
+}
+
 // Buckets of a hub query with `occ` staging slots: about kBucketTarget
 // slots each, at most 2^max_bits.
 uint32_t hub_buckets(uint64_t occ, int max_bits);
 uint32_t hub_tiles(uint64_t L);
 uint32_t hub_stiles(uint64_t L);
 size_t hub_count_lds();
-hipError_t enqueue_hub_chunk(const HubArgs& A, int stride, void* scan_temp, hipStream_t s);
+hipError_t enqueue_hub_chunk(const HubArgs& A, int stride, void* scan_temp, hipStream_t s,
+                             bool prep);
 hipError_t hub_set_attributes();
 
 }  // namespace panther

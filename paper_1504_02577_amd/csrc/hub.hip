@@ -87,31 +87,7 @@ __device__ __forceinline__ void load_batch(const int32_t* __restrict__ src, uint
   }
 }
 
-// Per query of the chunk: its list bounds, the owner maps of its tiles and
-// buckets, and zeroed bucket counters.
-__global__ void __launch_bounds__(256) k_hub_prep(HubArgs A) {
-  const int j = blockIdx.x;
-  const HubQuery Q = A.hq[j];
-  const bool last = j + 1 == A.nq;
-  const uint32_t t1 = last ? A.n_tiles : A.hq[j + 1].tile0;
-  const uint32_t s1 = last ? A.n_stiles : A.hq[j + 1].stile0;
-  const uint32_t nb = Q.nb;
-  if (threadIdx.x == 0) {
-    const int32_t q = A.queries[Q.qi];
-    const uint64_t a = A.inv_ptr[q];
-    A.hx[j] = HubList{a, A.inv_ptr[q + 1] - a, q, 0};
-    A.cand_n[j] = 0u;
-  }
-  for (uint32_t t = Q.tile0 + threadIdx.x; t < t1; t += 256) A.tile_owner[t] = j;
-  for (uint32_t t = Q.stile0 + threadIdx.x; t < s1; t += 256) A.stile_owner[t] = j;
-  for (uint32_t b = threadIdx.x; b < nb; b += 256) {
-    A.bkt_owner[Q.bkt0 + b] = j;
-    A.bkt_cand0[Q.bkt0 + b] = Q.cand0;
-    A.bkt_cnt[Q.bkt0 + b] = 0u;
-    A.bkt_fill[Q.bkt0 + b] = 0u;
-  }
-  if (j == 0 && threadIdx.x == 0) *A.redo_n = 0u;
-}
+__global__ void __launch_bounds__(256) k_hub_prep(HubArgs A) { hub_prep_query(A, blockIdx.x); }
 
 template <int S>
 __global__ void __launch_bounds__(kGatherBlock) k_hub_gather(HubArgs A) {
@@ -560,11 +536,13 @@ uint32_t hub_stiles(uint64_t L) { return (uint32_t)((L + kSTileRows - 1) / kSTil
 
 size_t hub_count_lds() { return sizeof(CountSmem); }
 
-// Enqueues the four steps for one chunk.  Buffers in `A` must hold the
+// Enqueues the four steps for one chunk (prep: its maps and counters first,
+// when no earlier kernel has made them).  Buffers in `A` must hold the
 // chunk's totals; nothing here allocates or synchronises.
-hipError_t enqueue_hub_chunk(const HubArgs& A, int stride, void* scan_temp, hipStream_t s) {
+hipError_t enqueue_hub_chunk(const HubArgs& A, int stride, void* scan_temp, hipStream_t s,
+                             bool prep) {
   if (A.nq == 0) return hipSuccess;
-  k_hub_prep<<<(uint32_t)A.nq, 256, 0, s>>>(A);
+  if (prep) k_hub_prep<<<(uint32_t)A.nq, 256, 0, s>>>(A);
   switch (stride) {
     case 4: k_hub_gather<4><<<A.n_tiles, kGatherBlock, 0, s>>>(A); break;
     case 8: k_hub_gather<8><<<A.n_tiles, kGatherBlock, 0, s>>>(A); break;
