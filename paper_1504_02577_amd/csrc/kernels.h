@@ -68,6 +68,10 @@ void launch_walk32(int stride, const VRec* vrec, const uint2* edge, const uint4*
                    const int4* start_rec, int32_t nstart, int32_t T, uint64_t R, uint64_t seed,
                    int32_t* paths, hipStream_t s);
 
+// rows of w entries out of rows of `stride`, packed.
+void launch_pack_paths(const int32_t* paths, int stride, int w, int64_t rows, int32_t* out,
+                       hipStream_t s);
+
 // ---- index by stable LSD radix sort of (vertex, path id) pairs ----
 constexpr int kRadixPassBits = 8;
 uint64_t radix_tiles_paths(uint64_t R, int T);

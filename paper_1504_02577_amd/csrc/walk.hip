@@ -236,7 +236,32 @@ k_walk64(const VRec* __restrict__ vrec, const uint64_t* __restrict__ pfx,
   store_row<S>(paths, pid, row);
 }
 
+// Consecutive threads write consecutive entries of a work-group's kPackRows
+// rows.  (The runtime's strided copy moved the 24-byte rows of 10^7 paths at
+// 1.6 TB/s, read plus write.)
+constexpr int kPackRows = 1024;
+__global__ void __launch_bounds__(kBlock)
+k_pack_paths(const int32_t* __restrict__ paths, int stride, uint32_t w, int64_t rows,
+             int32_t* __restrict__ out) {
+  const int64_t r0 = (int64_t)blockIdx.x * kPackRows;
+  const uint32_t n = (uint32_t)(rows - r0 < kPackRows ? rows - r0 : kPackRows) * w;
+  const int32_t* in = paths + r0 * stride;
+  int32_t* to = out + r0 * w;
+#pragma unroll 4
+  for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
+    const uint32_t r = i / w;
+    to[i] = in[r * (uint32_t)stride + (i - r * w)];
+  }
+}
+
 }  // namespace
+
+void launch_pack_paths(const int32_t* paths, int stride, int w, int64_t rows, int32_t* out,
+                       hipStream_t s) {
+  if (rows > 0)
+    k_pack_paths<<<(unsigned)((rows + kPackRows - 1) / kPackRows), kBlock, 0, s>>>(
+        paths, stride, (uint32_t)w, rows, out);
+}
 
 #define PANTHER_STRIDES(MACRO) \
   switch (stride) {            \
