@@ -100,8 +100,8 @@ k_check_symmetric(const int32_t* __restrict__ row_ptr, const int32_t* __restrict
 // differences of two of its values and no kernel depends on row lengths.
 // (One thread per short row and one wave per long row took 23.0 ms of an
 // R-MAT 22 load, 128 million entries, most of it waiting for the longest
-// rows; these kernels and the scan take 6.7 ms, of which the records, 8.2 GB
-// written, 4.6.)
+// rows; these kernels and the scan take 5.6 ms, of which the records, 8.2 GB
+// written, 4.4.)
 
 // Entries per work-group of the per-entry kernels; row_of finds an entry's
 // row between those of the first entries of its tile and the next.
@@ -126,7 +126,11 @@ k_rows(const int32_t* __restrict__ row_ptr, const uint64_t* __restrict__ sum, in
       tile_row[t] = v;
   }
   W = wave_max(W);
-  if ((threadIdx.x & (kWave - 1)) == 0 && W) atomicMax(max_w, (unsigned long long)W);
+  // Only a wave above the maximum so far writes it: with all 65,536 waves of
+  // 4 M rows writing that one address the kernel took 0.75 ms instead of 0.13.
+  if ((threadIdx.x & (kWave - 1)) == 0 &&
+      W > __hip_atomic_load(max_w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(max_w, (unsigned long long)W);
 }
 
 // The row holding entry e: the last v in [lo, hi] with row_ptr[v] <= e (its
@@ -143,19 +147,46 @@ __device__ __forceinline__ int32_t row_of(const int32_t* __restrict__ row_ptr, i
   return lo;
 }
 
+// The rows of one tile's entries: their starts are kept in LDS when they are
+// few (every tile but those among long runs of empty rows), so that the
+// bisection of each entry (eight steps at 30 entries a row) stays there
+// (k_edges32 at 128 M entries: 1.14 -> 0.49 ms).
+constexpr int kRowCache = 2048;
+struct TileRows {
+  const int32_t* row_ptr;
+  int32_t* cache;  // [kRowCache] LDS
+  int32_t lo, hi;
+  bool cached;
+  __device__ __forceinline__ void load(const int32_t* rp, const int32_t* tile_row, int32_t n,
+                                       int32_t* lds) {
+    row_ptr = rp;
+    cache = lds;
+    lo = tile_row[blockIdx.x];
+    hi = blockIdx.x + 1 < gridDim.x ? tile_row[blockIdx.x + 1] : n - 1;
+    cached = hi - lo < kRowCache;
+    if (cached)
+      for (int32_t i = threadIdx.x; i <= hi - lo; i += kBlock) cache[i] = rp[lo + i];
+    __syncthreads();
+  }
+  __device__ __forceinline__ int32_t of(int32_t e) const {
+    return cached ? lo + row_of(cache, 0, hi - lo, e) : row_of(row_ptr, lo, hi, e);
+  }
+};
+
 // edge[e] = {inclusive weight prefix, column}: one 8-byte load gives both.
 __global__ void __launch_bounds__(kBlock)
 k_edges32(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ tile_row,
           const uint64_t* __restrict__ sum, const uint64_t* __restrict__ base,
           const int32_t* __restrict__ col, int32_t n, int64_t m, uint2* __restrict__ edge) {
-  const int32_t lo = tile_row[blockIdx.x];
-  const int32_t hi = blockIdx.x + 1 < gridDim.x ? tile_row[blockIdx.x + 1] : n - 1;
+  __shared__ int32_t s_rows[kRowCache];
+  TileRows rows;
+  rows.load(row_ptr, tile_row, n, s_rows);
   const int64_t e0 = (int64_t)blockIdx.x * kEdgeTile + threadIdx.x;
 #pragma unroll 4
   for (int i = 0; i < kEdgePer; ++i) {
     const int64_t e = e0 + i * kBlock;
     if (e >= m) break;
-    const int32_t v = row_of(row_ptr, lo, hi, (int32_t)e);
+    const int32_t v = rows.of((int32_t)e);
     edge[e] = make_uint2((uint32_t)(sum[e + 1] - base[v]), (uint32_t)col[e]);
   }
 }
@@ -165,14 +196,15 @@ __global__ void __launch_bounds__(kBlock)
 k_prefix64(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ tile_row,
            const uint64_t* sum, const uint64_t* __restrict__ base, int32_t n, int64_t m,
            uint64_t* pfx) {
-  const int32_t lo = tile_row[blockIdx.x];
-  const int32_t hi = blockIdx.x + 1 < gridDim.x ? tile_row[blockIdx.x + 1] : n - 1;
+  __shared__ int32_t s_rows[kRowCache];
+  TileRows rows;
+  rows.load(row_ptr, tile_row, n, s_rows);
   const int64_t e0 = (int64_t)blockIdx.x * kEdgeTile + threadIdx.x;
 #pragma unroll 4
   for (int i = 0; i < kEdgePer; ++i) {
     const int64_t e = e0 + i * kBlock;
     if (e >= m) break;
-    const int32_t v = row_of(row_ptr, lo, hi, (int32_t)e);
+    const int32_t v = rows.of((int32_t)e);
     pfx[e] = sum[e + 1] - base[v];
   }
 }
@@ -234,8 +266,9 @@ __global__ void __launch_bounds__(kBlock)
 k_guide32(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ tile_row,
           const VRec* __restrict__ vrec, const uint2* __restrict__ edge, int32_t n, int64_t m,
           uint4* __restrict__ fat) {
-  const int32_t lo = tile_row[blockIdx.x];
-  const int32_t hi = blockIdx.x + 1 < gridDim.x ? tile_row[blockIdx.x + 1] : n - 1;
+  __shared__ int32_t s_rows[kRowCache];
+  TileRows rows;
+  rows.load(row_ptr, tile_row, n, s_rows);
   const int64_t t0 = (int64_t)blockIdx.x * kEdgeTile + threadIdx.x;
   const int p = threadIdx.x & 3;
 #pragma unroll 1
@@ -243,7 +276,7 @@ k_guide32(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ tile_
     const int64_t at = t0 + i * kBlock;
     // lanes past the last bucket repeat it: their quad needs every lane
     const int32_t e = (int32_t)(at < m ? at : m - 1);
-    const int32_t v = row_of(row_ptr, lo, hi, e);
+    const int32_t v = rows.of(e);
     const VRec r = vrec[v];
     uint4 g[4] = {};
     if (r.w_lo) {  // a weightless row has no record
@@ -276,15 +309,16 @@ __global__ void __launch_bounds__(kBlock)
 k_guide64(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ tile_row,
           const VRec* __restrict__ vrec, const uint64_t* __restrict__ pfx,
           const int32_t* __restrict__ col, int32_t n, int64_t m, uint4* __restrict__ fat) {
-  const int32_t lo = tile_row[blockIdx.x];
-  const int32_t hi = blockIdx.x + 1 < gridDim.x ? tile_row[blockIdx.x + 1] : n - 1;
+  __shared__ int32_t s_rows[kRowCache];
+  TileRows rows;
+  rows.load(row_ptr, tile_row, n, s_rows);
   const int64_t t0 = (int64_t)blockIdx.x * kEdgeTile + threadIdx.x;
   const int p = threadIdx.x & 3;
 #pragma unroll 1
   for (int i = 0; i < kEdgePer; ++i) {
     const int64_t at = t0 + i * kBlock;
     const int32_t e = (int32_t)(at < m ? at : m - 1);
-    const int32_t v = row_of(row_ptr, lo, hi, e);
+    const int32_t v = rows.of(e);
     const VRec r = vrec[v];
     uint4 g[4] = {};
     if (r.w_lo | r.w_hi) {
