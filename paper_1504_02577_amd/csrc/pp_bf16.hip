@@ -23,9 +23,9 @@
 //    (norm +- threshold radius), it stops -- those rows could not enter
 //    any pool.  The pool is thus the P smallest keys over all rows, the
 //    same set a full scan gives, from a fraction of the rows.
-// 3. Rerank: one work-group per query recomputes the exact FP64 squared
+// 3. Rerank: one wavefront per query recomputes the exact FP64 squared
 //    distance (one fma per coordinate, coordinate order) of every pool
-//    member (one member per thread), sorts by (d2, id) and writes the
+//    member that can be among the first k, sorts by (d2, id) and writes the
 //    first k.  It also records how
 //    many of the final ids the pool order already had in its first k, and
 //    the relative error of d2~ / R^2 against d2 on the returned neighbours.
@@ -132,14 +132,22 @@ k_bf16_pad_rows(int64_t n_rows, int64_t npad, int32_t* __restrict__ sid, __bf16*
 
 // What a call's other kernels find initialised: the statistics, and per
 // query (sorted index) the shared bound and the merge list's length.
+// The call's statistics: [3] uncertified queries, [4] their overflow count,
+// [5] products, and behind these eight words kStatSlots slots of eight words
+// for the rerank's sums, {pre-rerank hits, max relative error, returned}.
+// (At one address, 65,536 queries' atomics, one after the other, took 2.06 ms
+// of the rerank's 2.36.)
+constexpr int kStatSlots = 64;
+constexpr int kStatWords = 8 + 8 * kStatSlots;
+
 struct CallInit {
-  unsigned long long* stats;  // [8]
+  unsigned long long* stats;  // [kStatWords]
   unsigned long long* gtau;   // [nq]
   uint32_t* part_n;           // [nq]
 };
 
 __device__ __forceinline__ void init_call(const CallInit& C, int64_t i, int64_t nq) {
-  if (i < 8) C.stats[i] = 0ull;
+  if (i < kStatWords) C.stats[i] = 0ull;
   if (i < nq) {
     C.gtau[i] = ~0ull;
     C.part_n[i] = 0u;
@@ -171,7 +179,7 @@ k_query_order_small(const float* __restrict__ norm, const int32_t* __restrict__ 
                     int32_t nq, int32_t* __restrict__ order, CallInit C) {
   __shared__ uint64_t key[kSmallOrder];
   const int P = next_pow2(nq < 2 ? 2 : nq);
-  for (int i = threadIdx.x; i < P || i < 8; i += kOrderBlock) {
+  for (int i = threadIdx.x; i < P || i < kStatWords; i += kOrderBlock) {
     init_call(C, i, nq);
     if (i < P)
       key[i] = i < nq ? ((uint64_t)__float_as_uint(qnorm ? qnorm[i] : norm[rank[queries[i]]]) << 32) |
@@ -851,8 +859,12 @@ k_pp_pool(PoolArgs A) {
 }
 
 // One work-group per query (sorted index): the P smallest of the slices'
-// keys, written to the query's position.
-__global__ void __launch_bounds__(kBlock)
+// keys, written to the query's position.  Few queries come here (they leave
+// the chip idle, or there would be no slices), with up to 40,000 keys each
+// that are read several times: sixteen waves of loads in flight instead of
+// four (37 queries of R-MAT 20, k = 50: 77 -> 41 us).
+constexpr int kMergeBlock = 1024;
+__global__ void __launch_bounds__(kMergeBlock)
 k_pp_merge(PoolArgs A) {
   __shared__ SelectSmem sm;
   const int64_t j = blockIdx.x;  // sorted index; the output row is its position
@@ -860,8 +872,8 @@ k_pp_merge(PoolArgs A) {
   const int P = A.P;
   const uint64_t* base = A.part + j * (int64_t)A.slices * P;
   auto key = [&](int i) { return ~base[i]; };  // larger = better
-  const int m = block_select_topk<kBlock>(key, (int)A.part_n[j], P, sm);
-  for (int i = threadIdx.x; i < P; i += kBlock) {
+  const int m = block_select_topk<kMergeBlock>(key, (int)A.part_n[j], P, sm);
+  for (int i = threadIdx.x; i < P; i += kMergeBlock) {
     const bool ok = i < m;
     const uint64_t k2 = ok ? ~sm.out[i] : 0ull;
     A.pool_ids[qi * P + i] = ok ? (int32_t)(uint32_t)k2 : -1;
@@ -869,7 +881,7 @@ k_pp_merge(PoolArgs A) {
   }
 }
 
-// per query (work-group): d, v, ap of P entries and up to 256 staged ids
+// per query: d, v, ap of P entries and up to 256 staged ids
 __host__ __device__ constexpr size_t rerank_lds(int P) {
   return (sizeof(double) + sizeof(int32_t) + sizeof(float)) * (size_t)P + sizeof(int32_t) * 256;
 }
@@ -893,88 +905,172 @@ struct RerankArgs {
   float inv_s2;          // 1 / s^2: scale of d2~ back to theta units
   int32_t* out_ids;
   double* out_dist;
-  unsigned long long* stat_hits;   // sum over queries of pre-rerank hits
-  unsigned long long* stat_err;    // max relative error (bits of a double >= 0)
-  unsigned long long* stat_ret;    // sum over queries of returned neighbours
+  // kStatSlots slots of eight words: [0] sum over queries of pre-rerank hits,
+  // [1] max relative error (bits of a double >= 0), [2] sum over queries of
+  // returned neighbours
+  unsigned long long* stat_slots;
 };
 
-// one wavefront per query
-__global__ void __launch_bounds__(kBlock)
+// One wavefront per query.  Bound: rows gathered from theta, 200 bytes each at
+// D = 50.  Only the members that can be among the k nearest are read: the
+// first ones of the pool order give an upper bound on the k-th exact
+// distance, and a later member whose d2~ puts it beyond that bound (the
+// certificate's inequality, below) is left out.  65,536 queries of R-MAT 22,
+// pool 256, k = 20: 2.53 -> 0.30 ms, with the statistics in slots; with them
+// at one address 2.36.
+constexpr int kRerankBlock = kWave;
+__global__ void __launch_bounds__(kRerankBlock)
 k_pp_rerank(RerankArgs A) {
-  // one work-group per query: d[P], v[P], ap[P], first[256]
+  // d[P], v[P], ap[P], first[256]
   extern __shared__ __align__(16) char rr_lds[];
   __shared__ double qv[kDP];
-  __shared__ unsigned int s_valid, s_hits;
+  __shared__ unsigned int s_hits;
   __shared__ unsigned long long s_err;
-  const int lane = threadIdx.x & (kWave - 1);
+  const int lane = threadIdx.x;
   const int64_t qi = blockIdx.x;
   const int32_t q = A.queries[qi];
-  const int P = A.P, D = A.D;
+  const int P = A.P, D = A.D, k = A.k;
   const float* tq = A.qtheta + (int64_t)q * D;
   double* d = reinterpret_cast<double*>(rr_lds);
   int32_t* v = reinterpret_cast<int32_t*>(d + P);
   float* ap = reinterpret_cast<float*>(v + P);
   int32_t* first = reinterpret_cast<int32_t*>(ap + P);
-  if ((int)threadIdx.x < D) qv[threadIdx.x] = (double)tq[threadIdx.x];
-  if (threadIdx.x == 0) {
-    s_valid = 0u;
+  if (lane < D) qv[lane] = (double)tq[lane];
+  if (lane == 0) {
     s_hits = 0u;
     s_err = 0ull;
   }
+  // norms of the query's row and of its rounding, and whether it is integral
+  double nq2 = 0.0, rq2 = 0.0;
+  bool q_int = true;
+  const float sf = (float)A.scale;
+  for (int j = lane; j < D; j += kWave) {
+    nq2 = fma((double)tq[j], (double)tq[j], nq2);
+    const float b = (float)(__bf16)(tq[j] * sf);
+    const double r = (double)b - (double)(tq[j] * sf);
+    rq2 = fma(r, r, rq2);
+    q_int = q_int && b == floorf(b);
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    nq2 += __shfl_xor(nq2, off, kWave);
+    rq2 += __shfl_xor(rq2, off, kWave);
+  }
+  q_int = __ballot(!q_int) == 0ull;
   __syncthreads();
-  // every member's row at once (one member per thread, all loads of a
-  // thread's row independent): the exact chain of the oracle
-  unsigned my_valid = 0;
-  for (int i = threadIdx.x; i < P; i += kBlock) {
-    const int32_t c = A.pool_ids[qi * P + i];
+  const double sc = A.scale, xq = sc * sqrt(nq2);
+  // Lower bound (scaled units) on the exact distance of a vertex of pool
+  // distance a2 that is within dk (scaled) of the query or nearer; a vertex
+  // farther than that needs none.  See the certificate below.
+  auto lower_bound = [&](double a2, double dk) {
+    const double M = sc * (double)A.db_max[0], E = (double)A.db_max[1];
+    const double reach = xq + dk;
+    const bool small = q_int && reach < 255.0;
+    const double bq = xq * (1.0 + 1.0 / 256.0);
+    const double bv = fmin(M, reach) * (1.0 + 1.0 / 256.0);
+    const bool exact = q_int && bq * bq + bv * bv < 8388608.0;
+    const double delta = exact ? 0.0 : 3.0517578125e-05 * (bq * bq + bv * bv);
+    const double rv = small ? 2.384185791015625e-07 * reach : fmin(E, reach / 128.0);
+    return sqrt(fmax(a2 - delta, 0.0)) - sqrt(rq2) * (1.0 + 1e-6) - rv - 1.2e-7 * (xq + bv);
+  };
+  // the exact chain of the oracle for pool member c into slot `to`
+  auto member = [&](int32_t c, float a, int to) {
     double sacc = INFINITY;
     if (c >= 0) {
       const float* tv = A.theta + (int64_t)c * D;
       sacc = 0.0;
-      for (int j = 0; j < D; ++j) {
+      int j = 0;
+      // sixteen values' loads in flight ahead of their chain
+      for (; j + 16 <= D; j += 16) {
+        float x[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = tv[j + i];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const double delta = qv[j + i] - (double)x[i];
+          sacc = fma(delta, delta, sacc);
+        }
+      }
+      for (; j < D; ++j) {
         const double delta = qv[j] - (double)tv[j];
         sacc = fma(delta, delta, sacc);
       }
-      ++my_valid;
     }
-    d[i] = sacc;
-    v[i] = c >= 0 ? c : 0x7FFFFFFF;
-    ap[i] = A.pool_d2[qi * P + i];
-  }
-  if (my_valid) atomicAdd(&s_valid, my_valid);
-  __syncthreads();
-  // sort (d, v) ascending; the approximate values ride along
-  for (int size = 2; size <= P; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int i = threadIdx.x; i < (P >> 1); i += kBlock) {
-        const int lo = ((i & ~(stride - 1)) << 1) | (i & (stride - 1));  // stride: power of two
-        const int hi = lo + stride;
-        const bool asc = (lo & size) == 0;
-        const double x = d[lo], y = d[hi];
-        const int32_t xv = v[lo], yv = v[hi];
-        const bool gt = x > y || (x == y && xv > yv);
-        if (gt == asc) {
-          d[lo] = y;
-          d[hi] = x;
-          v[lo] = yv;
-          v[hi] = xv;
-          const float t = ap[lo];
-          ap[lo] = ap[hi];
-          ap[hi] = t;
+    d[to] = sacc;
+    v[to] = c >= 0 ? c : 0x7FFFFFFF;
+    ap[to] = a;
+  };
+  // sort (d, v)[0, n) ascending, n a power of two; the approximate values
+  // ride along
+  auto sort = [&](int n) {
+    wsync();
+    for (int size = 2; size <= n; size <<= 1) {
+      for (int stride = size >> 1; stride > 0; stride >>= 1) {
+        for (int i = lane; i < (n >> 1); i += kWave) {
+          const int lo = ((i & ~(stride - 1)) << 1) | (i & (stride - 1));  // stride: power of two
+          const int hi = lo + stride;
+          const bool asc = (lo & size) == 0;
+          const double x = d[lo], y = d[hi];
+          const int32_t xv = v[lo], yv = v[hi];
+          const bool gt = x > y || (x == y && xv > yv);
+          if (gt == asc) {
+            d[lo] = y;
+            d[hi] = x;
+            v[lo] = yv;
+            v[hi] = xv;
+            const float t = ap[lo];
+            ap[lo] = ap[hi];
+            ap[hi] = t;
+          }
         }
+        wsync();
       }
-      __syncthreads();
+    }
+  };
+  // the first n1 members (a power of two, at least 2k where the pool allows)
+  int n1 = kWave;
+  while (n1 < 2 * k) n1 <<= 1;
+  if (n1 > P) n1 = P;
+  int valid = 0;
+  for (int i0 = 0; i0 < P; i0 += kWave) {
+    const int32_t c = i0 + lane < P ? A.pool_ids[qi * P + i0 + lane] : -1;
+    valid += __popcll(__ballot(c >= 0));
+    if (i0 + lane < n1) member(c, A.pool_d2[qi * P + i0 + lane], i0 + lane);
+  }
+  sort(n1);
+  // (k rows equal to a query whose near rows bfloat16 keeps exactly: the
+  // pool's equal rows are in id order, so the later ones rank behind these)
+  const bool equal = valid >= k && d[k - 1] == 0.0 && q_int && xq < 255.0;
+  if (n1 < P && valid > n1 && !equal) {
+    // the members after them that the k-th exact distance so far does not
+    // exclude, behind the sorted ones
+    const double dk = sc * sqrt(d[k - 1]);
+    int n = n1;
+    for (int i0 = n1; i0 < P; i0 += kWave) {
+      const int32_t c = A.pool_ids[qi * P + i0 + lane];
+      const float a = A.pool_d2[qi * P + i0 + lane];
+      const bool in = c >= 0 && !(lower_bound((double)a, dk) > dk * (1.0 + 1e-9));
+      const uint64_t bm = __ballot(in);
+      if (in) member(c, a, n + __popcll(bm & ((1ull << lane) - 1ull)));
+      n += __popcll(bm);
+    }
+    if (n > n1) {
+      int n2 = n1;
+      while (n2 < n) n2 <<= 1;
+      for (int i = n + lane; i < n2; i += kWave) {
+        d[i] = INFINITY;
+        v[i] = 0x7FFFFFFF;
+        ap[i] = INFINITY;
+      }
+      sort(n2);
     }
   }
-  const int valid = (int)s_valid;
-  const int k = A.k;
   const int m = valid < k ? valid : k;
   // the pool order's first m ids (pre-rerank top k: the pool is in key order)
-  for (int i = threadIdx.x; i < m; i += kBlock) first[i] = A.pool_ids[qi * P + i];
-  __syncthreads();
+  for (int i = lane; i < m; i += kWave) first[i] = A.pool_ids[qi * P + i];
+  wsync();
   unsigned hits = 0;
   double err = 0.0;
-  for (int j = threadIdx.x; j < k; j += kBlock) {
+  for (int j = lane; j < k; j += kWave) {
     const bool ok = j < m;
     A.out_ids[qi * k + j] = ok ? v[j] : -1;
     A.out_dist[qi * k + j] = ok ? sqrt(d[j]) : INFINITY;
@@ -989,12 +1085,12 @@ k_pp_rerank(RerankArgs A) {
   }
   if (hits) atomicAdd(&s_hits, hits);
   if (err > 0.0) atomicMax(&s_err, (unsigned long long)__double_as_longlong(err));  // err >= 0
-  __syncthreads();
-  if (threadIdx.x >= kWave) return;  // the first wavefront finishes the query
+  wsync();
   if (lane == 0) {
-    atomicAdd(A.stat_ret, (unsigned long long)m);
-    atomicAdd(A.stat_hits, (unsigned long long)s_hits);
-    atomicMax(A.stat_err, s_err);
+    unsigned long long* st = A.stat_slots + 8 * (qi & (kStatSlots - 1));
+    atomicAdd(&st[0], (unsigned long long)s_hits);
+    atomicMax(&st[1], s_err);
+    atomicAdd(&st[2], (unsigned long long)m);
   }
   // Certificate (in units of the scaled rows x = theta * s).  Every vertex
   // outside the pool has a pool key at least the pool's largest, so its
@@ -1017,47 +1113,13 @@ k_pp_rerank(RerankArgs A) {
   // are rows equal to the query's, each with d2~ = 0 in the pool in id
   // order, so it is certified too.  Otherwise the query is recomputed
   // exactly: every row within its k-th exact pair (d_k, id) is a candidate.
-  double nq2 = 0.0, rq2 = 0.0;
-  bool q_int = true;
-  const float sf = (float)A.scale;
-  for (int j = lane; j < A.D; j += kWave) {
-    nq2 = fma((double)tq[j], (double)tq[j], nq2);
-    const float b = (float)(__bf16)(tq[j] * sf);
-    const double r = (double)b - (double)(tq[j] * sf);
-    rq2 = fma(r, r, rq2);
-    q_int = q_int && b == floorf(b);
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    nq2 += __shfl_xor(nq2, off, kWave);
-    rq2 += __shfl_xor(rq2, off, kWave);
-  }
-  q_int = __ballot(!q_int) == 0ull;
   if (lane == 0) {
     const bool full = A.pool_ids[qi * P + P - 1] >= 0;
     bool ok = !full || m < k;
     if (!ok && !A.force) {
-      const double s = A.scale, dk = s * sqrt(d[k - 1]);
-      const double xq = s * sqrt(nq2), M = s * (double)A.db_max[0], E = (double)A.db_max[1];
-      const double reach = xq + dk;
-      const bool small = q_int && reach < 255.0;
-      if (small && d[k - 1] == 0.0) {
-        ok = true;
-      } else {
-        const double bq = xq * (1.0 + 1.0 / 256.0);
-        const double bv = fmin(M, reach) * (1.0 + 1.0 / 256.0);
-        // integral rows with |b_q|^2 + |b_v|^2 < 2^23: every partial sum
-        // of the evaluation (in any order) is an integer below 2^24, exact
-        // in FP32
-        const bool exact = q_int && bq * bq + bv * bv < 8388608.0;
-        const double delta = exact ? 0.0 : 3.0517578125e-05 * (bq * bq + bv * bv);
-        const double rv = small ? 2.384185791015625e-07 * reach : fmin(E, reach / 128.0);
-        const double a2 = (double)A.pool_d2[qi * P + P - 1];
-        // r was measured against the FP32 product theta * s, which is within
-        // 2^-24 of the exact scaled row
-        const double lower = sqrt(fmax(a2 - delta, 0.0)) - sqrt(rq2) * (1.0 + 1e-6) - rv -
-                             1.2e-7 * (xq + bv);
-        ok = lower > dk * (1.0 + 1e-9);
-      }
+      const double dk = sc * sqrt(d[k - 1]);
+      ok = equal ||
+           lower_bound((double)A.pool_d2[qi * P + P - 1], dk) > dk * (1.0 + 1e-9);
     }
     if (!ok) {
       const unsigned long long at = atomicAdd(A.fb_n, 1ull);
@@ -1257,7 +1319,7 @@ static int run_pp_bf16_geom(panther_ctx* c, Lane* lane, const int32_t* dq, int64
   const size_t gtau_bytes = 2 * sizeof(uint64_t) * (size_t)nq;
   TRY(ctx_ensure(c, lane->b_pool, buf_bytes + part_bytes + gtau_bytes + ids_bytes + 256,
                  "pools"));
-  TRY(ctx_ensure(c, lane->b_stats, 64, "pp stats"));
+  TRY(ctx_ensure(c, lane->b_stats, sizeof(unsigned long long) * kStatWords, "pp stats"));
   char* base = static_cast<char*>(lane->b_pool.p);
   uint64_t* buf = reinterpret_cast<uint64_t*>(base);
   uint64_t* part = reinterpret_cast<uint64_t*>(base + buf_bytes);
@@ -1348,7 +1410,7 @@ static int run_pp_bf16_geom(panther_ctx* c, Lane* lane, const int32_t* dq, int64
   launch_pool(pa, (unsigned)S);
   HIPTRY(hipGetLastError(), "pp pool");
   if (S > 1) {
-    k_pp_merge<<<(unsigned)nq, kBlock, 0, s>>>(pa);
+    k_pp_merge<<<(unsigned)nq, kMergeBlock, 0, s>>>(pa);
     HIPTRY(hipGetLastError(), "pp merge");
   }
   unsigned long long* st = static_cast<unsigned long long*>(lane->b_stats.p);
@@ -1377,16 +1439,14 @@ static int run_pp_bf16_geom(panther_ctx* c, Lane* lane, const int32_t* dq, int64
   ra.inv_s2 = 1.0f / (scale * scale);
   ra.out_ids = d_ids;
   ra.out_dist = d_dist;
-  ra.stat_hits = st;
-  ra.stat_err = st + 1;
-  ra.stat_ret = st + 2;
+  ra.stat_slots = st + 8;
   const size_t rr_lds = rerank_lds(P);
   HIPTRY(hipFuncSetAttribute((const void*)k_pp_rerank, hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)rr_lds),
          "pp rerank attribute");
-  k_pp_rerank<<<(unsigned)nq, kBlock, rr_lds, s>>>(ra);
+  k_pp_rerank<<<(unsigned)nq, kRerankBlock, rr_lds, s>>>(ra);
   HIPTRY(hipGetLastError(), "pp rerank");
-  unsigned long long hs[6];
+  unsigned long long hs[kStatWords];
   HIPTRY(hipMemcpyAsync(hs, st, sizeof hs, hipMemcpyDeviceToHost, s), "pp stats");
   HIPTRY(hipStreamSynchronize(s), "pp stats");
   // queries whose pool boundary is not certified: exact recompute
@@ -1403,10 +1463,16 @@ static int run_pp_bf16_geom(panther_ctx* c, Lane* lane, const int32_t* dq, int64
     HIPTRY((hipError_t)e, "pp exact recompute");
     HIPTRY(hipStreamSynchronize(s), "pp exact recompute");
   }
+  unsigned long long hits = 0, worst = 0, returned = 0;
+  for (int i = 0; i < kStatSlots; ++i) {
+    hits += hs[8 + 8 * i];
+    worst = std::max(worst, hs[8 + 8 * i + 1]);
+    returned += hs[8 + 8 * i + 2];
+  }
   lane->have_stats = true;
-  lane->mean_pre_recall = hs[2] ? (double)hs[0] / (double)hs[2] : 1.0;
+  lane->mean_pre_recall = returned ? (double)hits / (double)returned : 1.0;
   double e;
-  std::memcpy(&e, &hs[1], sizeof e);
+  std::memcpy(&e, &worst, sizeof e);
   lane->max_rel_err = e;
   lane->stat_nq = nq;
   lane->stat_fallback = (int64_t)hs[3];
