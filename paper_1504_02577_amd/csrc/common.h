@@ -92,14 +92,19 @@ __device__ __forceinline__ void quad_transpose(uint32_t& a, uint32_t& b, uint32_
                                                uint32_t& d) {
   constexpr int kXor1 = 0xB1, kXor2 = 0x4E;  // quad_perm [1,0,3,2] and [2,3,0,1]
   const bool odd = threadIdx.x & 1, upper = threadIdx.x & 2;
-  uint32_t x = quad_move<kXor1>(odd ? a : b);
-  (odd ? a : b) = x;
-  x = quad_move<kXor1>(odd ? c : d);
-  (odd ? c : d) = x;
+  // (selected values: an assignment through a selected reference keeps the
+  // words in LDS instead of registers)
+  uint32_t x = quad_move<kXor1>(odd ? a : b), y = quad_move<kXor1>(odd ? c : d);
+  a = odd ? x : a;
+  b = odd ? b : x;
+  c = odd ? y : c;
+  d = odd ? d : y;
   x = quad_move<kXor2>(upper ? a : c);
-  (upper ? a : c) = x;
-  x = quad_move<kXor2>(upper ? b : d);
-  (upper ? b : d) = x;
+  y = quad_move<kXor2>(upper ? b : d);
+  a = upper ? x : a;
+  c = upper ? c : x;
+  b = upper ? y : b;
+  d = upper ? d : y;
 }
 
 __device__ __forceinline__ void quad_exchange(uint4 (&g)[4]) {

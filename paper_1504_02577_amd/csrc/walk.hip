@@ -18,6 +18,8 @@
 // Graphs with 64-bit row sums have records of the first two edges of a bucket;
 // where their 64 bytes per entry do not fit in memory, each step bisects its
 // row's prefixes.  Each path's T+1 vertices are written once as 16-byte stores.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -64,7 +66,7 @@ __device__ __forceinline__ uint4 load_chunk(const uint4* p) {
 // What bounds it now is the rate of scattered line requests, about 45 per
 // nanosecond (a table of 128 MB, which the Infinity Cache holds, goes no
 // faster): R-MAT 24, 10^8 paths of 5 steps, 17.4 -> 13.4 ms; R-MAT 20, 10^7
-// paths, 1.89 -> 1.36 ms.  Every lane of the quad must be active.
+// paths, 1.89 -> 1.20 ms.  Every lane of the quad must be active.
 template <bool NT>
 __device__ __forceinline__ void quad_records(const uint4* __restrict__ fat, uint32_t bucket,
                                              uint4 (&g)[4]) {
@@ -77,6 +79,10 @@ __device__ __forceinline__ void quad_records(const uint4* __restrict__ fat, uint
   g[3] = load_chunk<NT>(fat + 4 * (uint64_t)b3 + p);
   quad_exchange(g);
 }
+
+// A choice between two values: between two chunks as a whole it would be one
+// of addresses, and the record would be kept in LDS.
+__device__ __forceinline__ uint32_t pick(bool c, uint32_t a, uint32_t b) { return c ? a : b; }
 
 template <int S, bool NT>
 __global__ void __launch_bounds__(kBlock)
@@ -103,9 +109,11 @@ k_walk32(const VRec* __restrict__ vrec, const uint2* __restrict__ edge,
       if (W != 0u) {
         // chunks: [pfx0 pfx1 pfx2 e0] [col st dg W] of e0, e0+1, e0+2
         if (u < g[0].z) {
-          const uint4 x = u < g[0].x ? g[1] : (u < g[0].y ? g[2] : g[3]);
-          v = (int32_t)x.x;
-          cur = VRec{(int32_t)x.y, (int32_t)x.z, x.w, 0u};
+          const bool c0 = u < g[0].x, c1 = u < g[0].y;
+          v = (int32_t)pick(c0, g[1].x, pick(c1, g[2].x, g[3].x));
+          cur = VRec{(int32_t)pick(c0, g[1].y, pick(c1, g[2].y, g[3].y)),
+                     (int32_t)pick(c0, g[1].z, pick(c1, g[2].z, g[3].z)),
+                     pick(c0, g[1].w, pick(c1, g[2].w, g[3].w)), 0u};
         } else {
           // rare: scan on from the fourth candidate, bisection after kScanMax
           int32_t e = (int32_t)g[0].w + 3;
@@ -169,9 +177,9 @@ k_walk64_guide(const VRec* __restrict__ vrec, const uint64_t* __restrict__ pfx,
         const uint64_t p1 = (uint64_t)g[0].z | ((uint64_t)g[0].w << 32);
         if (u < p1) {
           const bool one = u >= p0;
-          v = (int32_t)(one ? g[2].x : g[1].x);
-          cur = VRec{(int32_t)(one ? g[2].y : g[1].y), (int32_t)(one ? g[2].z : g[1].z),
-                     one ? g[3].z : g[3].x, one ? g[3].w : g[3].y};
+          v = (int32_t)pick(one, g[2].x, g[1].x);
+          cur = VRec{(int32_t)pick(one, g[2].y, g[1].y), (int32_t)pick(one, g[2].z, g[1].z),
+                     pick(one, g[3].z, g[3].x), pick(one, g[3].w, g[3].y)};
         } else {
           // scan on from the third candidate, bisection after kScanMax
           int32_t e = (int32_t)g[1].w + 2;
@@ -236,15 +244,13 @@ k_walk64(const VRec* __restrict__ vrec, const uint64_t* __restrict__ pfx,
   store_row<S>(paths, pid, row);
 }
 
-// Consecutive threads write consecutive entries of a work-group's kPackRows
-// rows.  (The runtime's strided copy moved the 24-byte rows of 10^7 paths at
-// 1.6 TB/s, read plus write.)
-constexpr int kPackRows = 1024;
+// Consecutive threads write consecutive entries of a work-group's `per` rows
+// (10^7 rows of 24 bytes: 0.35 ms by the runtime's strided copy, 0.10 here).
 __global__ void __launch_bounds__(kBlock)
-k_pack_paths(const int32_t* __restrict__ paths, int stride, uint32_t w, int64_t rows,
+k_pack_paths(const int32_t* __restrict__ paths, int stride, uint32_t w, int64_t rows, int per,
              int32_t* __restrict__ out) {
-  const int64_t r0 = (int64_t)blockIdx.x * kPackRows;
-  const uint32_t n = (uint32_t)(rows - r0 < kPackRows ? rows - r0 : kPackRows) * w;
+  const int64_t r0 = (int64_t)blockIdx.x * per;
+  const uint32_t n = (uint32_t)(rows - r0 < per ? rows - r0 : per) * w;
   const int32_t* in = paths + r0 * stride;
   int32_t* to = out + r0 * w;
 #pragma unroll 4
@@ -258,9 +264,12 @@ k_pack_paths(const int32_t* __restrict__ paths, int stride, uint32_t w, int64_t 
 
 void launch_pack_paths(const int32_t* paths, int stride, int w, int64_t rows, int32_t* out,
                        hipStream_t s) {
-  if (rows > 0)
-    k_pack_paths<<<(unsigned)((rows + kPackRows - 1) / kPackRows), kBlock, 0, s>>>(
-        paths, stride, (uint32_t)w, rows, out);
+  if (rows <= 0) return;
+  // a thousand work-groups where the rows allow (16,000 rows of 21 in 16
+  // work-groups of 1,024 rows took longer than the strided copy)
+  const int per = (int)std::min<int64_t>(1024, std::max<int64_t>(16, rows / 1024));
+  k_pack_paths<<<(unsigned)((rows + per - 1) / per), kBlock, 0, s>>>(paths, stride, (uint32_t)w,
+                                                                     rows, per, out);
 }
 
 #define PANTHER_STRIDES(MACRO) \
