@@ -1084,20 +1084,29 @@ static hipError_t enqueue(panther_ctx* c, BatchState* b, const Plan& P, KernelFn
     if (e != hipSuccess) return e;
   }
   if (P.run_kernel) {
-    if (P.args.nB > 0) {
-      hipLaunchKernelGGL(fn, dim3(grid), dim3(block), lds, s, P.args);
+    BatchArgs B = P.args;
+    int nM2 = P.args.nM2, nM1 = P.args.nM1, nA = P.args.nA;
+    // Tier M's queries ride in tier B's launch while that leaves a work-group
+    // for each (2,378 queries of 10^4 paths, 94 + 96 of tier M: 13 us for the
+    // three tiers B, M2 and M1 in one launch, 41 in three).
+    if (B.nB > 0 && B.nB + nM2 + nM1 <= grid) {
+      B.nB += nM2 + nM1;
+      nM2 = nM1 = 0;
     }
+    if (B.nB > 0) hipLaunchKernelGGL(fn, dim3(grid), dim3(block), lds, s, B);
     // one wavefront each, as many as the LDS of all CUs holds
     auto mid_grid = [&](int n, int TG) {
       return dim3((unsigned)std::min(n, c->num_cus * (163840 / (8 * TG))));
     };
-    // Few queries of the wavefront tiers go in one launch, tier M's and A's
-    // alike, with the widest table that any of them needs (they would not fill
-    // the chip in launches of their own, and each costs about 8 us).
-    int nM2 = P.args.nM2, nM1 = P.args.nM1, nA = P.args.nA;
+    // Few queries of the wavefront tiers go in one launch, all or tier M's,
+    // with the widest table that any of them needs (they would not fill the
+    // chip in launches of their own, and each costs about 8 us).
     if (nM2 > 0 && nM2 + nM1 + nA <= 4 * c->num_cus) {
       nM2 += nM1 + nA;
       nM1 = nA = 0;
+    } else if (nM2 > 0 && nM2 + nM1 <= 4 * c->num_cus) {
+      nM2 += nM1;
+      nM1 = 0;
     } else if (nM1 > 0 && nM1 + nA <= 4 * c->num_cus) {
       nM1 += nA;
       nA = 0;
@@ -1688,11 +1697,18 @@ int run_batched(panther_ctx* c, Lane* lane, const int32_t* dq, const uint64_t* q
       };
       BatchConfig best_cfg{};
       float best = 1e30f;
+      // Where tier B's largest table takes the longest list, a smaller one
+      // still sends lists to the hub pipeline: stage 1 then times the whole
+      // call, or it would credit those lists to the smaller table (2,378
+      // queries of 10^4 paths, a handful of long lists: 147 us against 122).
+      bool whole = qlen && nq <= kStage2MaxQueries;
+      const uint64_t widest = (uint64_t)layout_for(c, BatchConfig{}).TB / (2 * (uint64_t)c->T);
+      for (int64_t i = 0; i < nq && whole; ++i) whole = qlen[i] <= widest || qlen[i] == kRepeated;
       for (int blk : kBlocks)
         for (int wgs : kWgs) {
           const BatchConfig cfg{blk, wgs, 1, 0};
           float ms = 0.f;
-          if (!st) st = time_cfg(cfg, m, false, &ms);
+          if (!st) st = time_cfg(cfg, whole ? nq : m, whole, &ms);
           if (!st && ms < best) {
             best = ms;
             best_cfg = cfg;

@@ -38,3 +38,38 @@ def test_mid_tier_bounds(oracle, inputs, T):
             got = P.topk(q, k)
             assert all((a == b).all() for a, b in zip(got, want))
     P.close()
+
+
+@pytest.mark.parametrize("mid", [0, 1, 40, 255, 256, 300, 1100])
+def test_tier_b_launch_takes_few_mid_queries(oracle, inputs, mid):
+    """One query of tier B, `mid` of tier M and 1,200 of tier A: tier M's go in
+    tier B's launch up to one work-group each (256 CUs), else in their own."""
+    from paper_1504_02577_amd.panther import Panther
+
+    rng = np.random.default_rng(mid)
+    n, T, R = 4000, 5, 60_000
+    edges = np.concatenate([rng.integers(0, n, (16_000, 2)), rng.integers(0, 20, (4000, 2))])
+    w = np.where(edges.max(1) < 20, 40, np.where(edges.max(1) < 2000, 16, 1))
+    g = inputs.graph_from_edges(n, edges, w.astype(np.int64))
+    paths = oracle.walk(g, T, R, 5)
+    ptr, pid = oracle.index(g.n, paths)
+    L = np.diff(ptr)
+    wave, m2, b = 512 // (2 * T), 2048 // (2 * T), 8192 // (2 * T)
+    longest = np.flatnonzero((L > m2) & (L <= b))
+    middle = np.flatnonzero((L > wave) & (L <= m2))
+    short = np.flatnonzero(L <= wave)
+    assert len(longest) and len(middle) >= 1100 and len(short) >= 1200
+    q = np.concatenate([longest[:1], middle[:mid], short[:1200]]).astype(np.int32)
+    rng.shuffle(q)
+    P = Panther(0)
+    P.load_graph(g)
+    P.sample_paths(T, R, 5)
+    for key, v in (("batch.block", 512), ("batch.wgs_per_cu", 1), ("batch.tier_b_div", 1)):
+        P.set_option(key, v)
+    print(f"case: tier B launch, {mid} mid queries", flush=True)
+    for k in (5, 60):
+        want = oracle.topk(g.n, paths, ptr, pid, q, k)
+        for _ in range(3):  # launched, captured, replayed
+            got = P.topk(q, k)
+            assert all((a == x).all() for a, x in zip(got, want))
+    P.close()
