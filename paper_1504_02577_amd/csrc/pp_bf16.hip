@@ -1578,7 +1578,7 @@ size_t pp_lane_bytes(const panther_ctx* c, int64_t nq, int32_t k) {
                         (G.S > 1 ? sizeof(uint64_t) * n * G.S * G.P : 0) +
                         (sizeof(int32_t) + sizeof(float)) * n * G.P + 256);
   }
-  b += 64;
+  b += sizeof(unsigned long long) * kStatWords;
   b += (2 * sizeof(uint32_t) + 2 * sizeof(int32_t)) * ((n + 63) / 64 * 64);
   b += sort_pairs_bytes(nq);
   b += (2 * sizeof(int32_t) + sizeof(double)) * n;
