@@ -455,8 +455,10 @@ k_scan_apply(const uint32_t* __restrict__ in, int64_t n, const uint64_t* __restr
 }
 
 // The whole scan of a few tiles by one work-group: one launch instead of
-// three, of which each costs about 8 us between small kernels.
-constexpr int kScanSmallTiles = 4;
+// three, of which each costs about 8 us between small kernels.  Two tiles:
+// at four the tiles in turn take longer than the launches (an index of 11,282
+// paths of 20 steps, four tiles a scan: the sample 183 us so, 166 in three).
+constexpr int kScanSmallTiles = 2;
 __global__ void __launch_bounds__(kBlock)
 k_scan_small(const uint32_t* __restrict__ in, int64_t n, uint64_t* __restrict__ out) {
   __shared__ uint64_t s[kBlock / kWave + 1];
