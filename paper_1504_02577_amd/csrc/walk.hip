@@ -32,9 +32,8 @@ constexpr int kScanMax = 8;  // forward steps before falling back to bisection
 // Guide tables past this size are read with non-temporal loads: such a walk
 // finds hardly a line twice (R = 6 to 12 n paths), and leaving the lines out of
 // L2 took the R-MAT 24 walk (33 GB) from 14.0 to 13.4 ms and R-MAT 23 (16 GB)
-// from 6.78 to 6.71; at R-MAT 22 (8 GB) and below both are alike (6.72 / 6.73,
-// R-MAT 20 1.36 / 1.35), and tables that caches hold lose (0.046 against
-// 0.058 ms for 10^5 paths).
+// from 6.78 to 6.71; at R-MAT 22 (8 GB) and below both are alike (6.72 / 6.73),
+// and tables that caches hold lose (10^5 paths: a quarter more time).
 constexpr uint64_t kStreamBytes = (uint64_t)8 << 30;
 
 template <int S>
