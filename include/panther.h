@@ -177,7 +177,9 @@ int64_t panther_sample_size(double eps, double c, double delta, int32_t T);
  * 1: the BF16 form recomputes every query whose pool is full by the exact
  * path, certified or not; 2: also overflows every candidate list so that
  * the full brute force runs; for tests), "test.fail_alloc_after" (the next n device allocations
- * succeed, the one after fails with ENOMEM; -1 disables).
+ * succeed, every one after fails with ENOMEM; -1 disables),
+ * "test.mem_reserve" (device memory in bytes that the context's allocations
+ * leave free: one that would not fails with ENOMEM; default 0; for tests).
  * Errors: EINVAL (unknown key or value out of range). */
 int panther_set_option(panther_ctx *ctx, const char *key, int64_t value);
 

@@ -71,6 +71,7 @@ struct panther_ctx {
   std::map<std::string, int> pp_qw_tuned;  // tuned pool tile width per shape class
   std::mutex pp_tune_mu;
   int64_t fail_alloc_after = -1;
+  int64_t mem_reserve = 0;  // test: bytes of device memory that allocations leave free
   std::mutex alloc_mu;
   // graph
   bool has_graph = false;
@@ -133,6 +134,8 @@ struct panther_ctx {
 int ctx_fail(panther_ctx* c, int code, const char* fmt, ...);
 int ctx_hip(panther_ctx* c, hipError_t e, const char* what);
 int ctx_alloc(panther_ctx* c, void** p, size_t bytes, const char* what);  // thread-safe
+// Free device memory an allocation may still take.
+size_t device_room(panther_ctx* c);
 // Makes b hold at least `bytes`; the contents are not preserved on growth.
 int ctx_ensure(panther_ctx* c, DevBuf& b, size_t bytes, const char* what);
 void ctx_release(DevBuf& b);

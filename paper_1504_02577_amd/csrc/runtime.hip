@@ -53,13 +53,24 @@ int ctx_alloc(panther_ctx* c, void** p, size_t bytes, const char* what) {
   }
   if (inject) return ctx_fail(c, PANTHER_ENOMEM, "%s: allocation failure injected", what);
   if (bytes == 0) bytes = 16;
-  hipError_t e = hipMalloc(p, bytes);
+  const bool room = !c->mem_reserve || device_room(c) >= bytes;
+  hipError_t e = room ? hipMalloc(p, bytes) : hipErrorOutOfMemory;
   if (e != hipSuccess) {
     *p = nullptr;
     (void)hipGetLastError();
     return ctx_fail(c, PANTHER_ENOMEM, "%s: cannot allocate %zu bytes", what, bytes);
   }
   return PANTHER_OK;
+}
+
+size_t device_room(panther_ctx* c) {
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  const size_t keep = (size_t)c->mem_reserve;
+  return free_b > keep ? free_b - keep : 0;
 }
 
 void ctx_free(void* p) {
@@ -314,6 +325,9 @@ extern "C" int panther_set_option(panther_ctx* c, const char* key, int64_t value
     c->pp_recompute_all = (int)value;
   } else if (k == "test.fail_alloc_after") {
     c->fail_alloc_after = value < 0 ? -1 : value;
+  } else if (k == "test.mem_reserve") {
+    if (value < 0) return ctx_fail(c, PANTHER_EINVAL, "test.mem_reserve must be >= 0");
+    c->mem_reserve = value;
   } else if (k == "batch.tier_a" || k == "batch.tier_b" || k == "batch.block" ||
              k == "batch.wgs_per_cu" || k == "batch.hub_bits" || k == "batch.tier_b_div" ||
              k == "batch.bucket_bias" || k == "test.hub_budget") {
@@ -340,8 +354,12 @@ extern "C" int panther_synchronize(panther_ctx* c) {
 // ---------------------------------------------------------------------------
 // load_graph (a1): validate, W_v, start set, per-row prefixes
 // ---------------------------------------------------------------------------
+// records: with guide records where they fit.  Without, a graph with 64-bit
+// row sums takes no more than its bisection form needs, and one with narrow
+// sums, which is walked by records only, ends with ENOMEM.
 static int load_graph(panther_ctx* c, int32_t n, int64_t m, const int32_t* row_ptr,
-                      const int32_t* col, const uint32_t* w, int mem, uint32_t flags) {
+                      const int32_t* col, const uint32_t* w, int mem, uint32_t flags,
+                      bool records) {
   if (hipSetDevice(c->device) != hipSuccess) return ctx_fail(c, PANTHER_EDEVICE, "hipSetDevice");
   if (n < 1) return ctx_fail(c, PANTHER_EINVAL, "n must be >= 1");
   if (m < 0 || m >= (int64_t(1) << 31))
@@ -428,9 +446,8 @@ static int load_graph(panther_ctx* c, int32_t n, int64_t m, const int32_t* row_p
   // with wide row sums will be (shifted by one entry, in place).
   // (At least one record: the walk reads record 0 at weightless vertices.)
   uint64_t* sum = nullptr;
-  const int fat_st = graph_alloc(c, c->g_fat, 4 * sizeof(uint4) * (size_t)std::max<int64_t>(m, 1),
-                                 "guide records", &c->d_fat);
-  if (fat_st == PANTHER_OK) {
+  const size_t fat_bytes = 4 * sizeof(uint4) * (size_t)std::max<int64_t>(m, 1);
+  if (records && graph_alloc(c, c->g_fat, fat_bytes, "guide records", &c->d_fat) == PANTHER_OK) {
     sum = reinterpret_cast<uint64_t*>(c->d_fat);
   } else {
     TRY(graph_alloc(c, c->g_pfx, sizeof(uint64_t) * (size_t)(m + 1), "weight prefixes", &sum));
@@ -466,7 +483,8 @@ static int load_graph(panther_ctx* c, int32_t n, int64_t m, const int32_t* row_p
     return ctx_fail(c, PANTHER_EINVAL, "no vertex has an edge of positive weight");
   }
   c->pfx64 = max_w >= (uint64_t(1) << 32);
-  if (!c->pfx64 && fat_st) return fat_st;
+  if (!c->pfx64 && !c->d_fat)
+    return ctx_fail(c, PANTHER_ENOMEM, "guide records: cannot allocate %zu bytes", fat_bytes);
   TRY(graph_alloc(c, c->g_vstart, sizeof(int32_t) * (size_t)nstart, "start set", &c->d_vstart));
   if (!c->pfx64)
     TRY(graph_alloc(c, c->g_srec, sizeof(int4) * (size_t)nstart, "start records",
@@ -482,8 +500,7 @@ static int load_graph(panther_ctx* c, int32_t n, int64_t m, const int32_t* row_p
     // guide records only where they leave at least as much memory free as
     // they take: such a graph has to load, and leave room for its paths, in
     // as little memory as the bisection form needs
-    size_t free_b = 0, total_b = 0;
-    if (c->d_fat && (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b < c->g_fat.cap)) {
+    if (c->d_fat && device_room(c) < c->g_fat.cap) {
       HIPTRY(hipStreamSynchronize(s), "prefix");
       ctx_release(c->g_fat);
       c->d_fat = nullptr;
@@ -512,14 +529,17 @@ extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const in
   c->err.clear();
   bool kept = false;
   for (DevBuf panther_ctx::*b : kGraphBuffers) kept = kept || (c->*b).p;
-  int st = load_graph(c, n, m, row_ptr, col, w, mem, flags);
-  if (st == PANTHER_ENOMEM && kept) {
-    // what the previous graph's storage holds may be what is missing
+  int st = load_graph(c, n, m, row_ptr, col, w, mem, flags, true);
+  // short of memory: once more without the previous graph's storage, which
+  // may hold what is missing, then without the optional records
+  for (const bool records : {true, false}) {
+    if (st != PANTHER_ENOMEM) break;
+    if (records && !kept) continue;
     (void)hipStreamSynchronize(c->stream);
     free_graph(c, true);
-    c->err.clear();
-    st = load_graph(c, n, m, row_ptr, col, w, mem, flags);
+    st = load_graph(c, n, m, row_ptr, col, w, mem, flags, records);
   }
+  if (st == PANTHER_OK) c->err.clear();  // a failed first attempt's message
   return st;
 }
 
