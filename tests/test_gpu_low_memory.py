@@ -69,3 +69,34 @@ def test_too_little_room_for_any_form(oracle, inputs):
         P.sample_paths(5, 1000, 9)
         assert (P.paths() == oracle.walk(g, 5, 1000, 9)).all()
         P.close()
+
+
+@pytest.mark.parametrize("room", [100, 420])
+@pytest.mark.parametrize("start_all", [False, True])
+def test_bisection_walk_edges(oracle, inputs, room, start_all):
+    """The walk of a wide graph without guide records (prefixes made in place
+    of the scan at 100 MiB, records dropped after it at 420): weightless rows,
+    zero weights, a hub, isolated vertices, and partly filled work-groups."""
+    from paper_1504_02577_amd.panther import PANTHER_START_ALL_VERTICES, Panther
+
+    # 350 such vertices beside a dense part that makes the records large
+    edges = [(0, i) for i in range(1, 301)] + [(i, i + 1) for i in range(1, 340)] + [(345, 346)]
+    rng = np.random.default_rng(5)
+    w = rng.integers(1, 1000, len(edges))
+    w[:300:7] = 100_000
+    w[5:300:11] = 0
+    w[-1] = 0
+    pairs, pw = dense_graph(2000, True, first=350)
+    g = inputs.graph_from_edges(2350, np.concatenate([edges, pairs]),
+                                np.concatenate([(w * 42_000).astype(np.uint32), pw]))
+    P = Panther(0)
+    leave_room(P, room * MB)
+    P.load_graph(g, flags=PANTHER_START_ALL_VERTICES if start_all else 0)
+    leave_room(P, None)  # (the runtime takes memory for the longest rows' walk)
+    for T in (1, 3, 5, 9, 20, 63):
+        for R in (1, 2, 255, 257, 5001):
+            print(f"case: bisection walk room={room} start_all={start_all} T={T} R={R}", flush=True)
+            P.sample_paths(T, R, 40 + R)
+            want = oracle.walk(g, T, R, 40 + R, start_all=start_all)
+            assert (P.paths() == want).all(), (T, R)
+    P.close()
