@@ -73,6 +73,7 @@ struct panther_ctx {
   int64_t fail_alloc_after = -1;
   int64_t mem_reserve = 0;  // test: bytes of device memory that allocations leave free
   std::mutex alloc_mu;
+  std::mutex spare_mu;  // one allocation at a time gives memory back
   // graph
   bool has_graph = false;
   int32_t n = 0;

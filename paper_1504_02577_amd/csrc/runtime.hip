@@ -41,6 +41,28 @@ int ctx_hip(panther_ctx* c, hipError_t e, const char* what) {
   return ctx_fail(c, PANTHER_EDEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
+// Frees memory the context holds but can do without, for an allocation that
+// failed: first what only a repeat of an earlier call would use again, then
+// the guide records of a graph with 64-bit row sums, which is walked by
+// bisection from then on.  False once nothing is left to free.
+static bool give_back(panther_ctx* c) {
+  std::lock_guard<std::mutex> g(c->spare_mu);
+  bool any = false;
+  auto drop = [&](DevBuf& b) {
+    if (!b.p) return;
+    ctx_release(b);  // (hipFree waits for the kernels that use it)
+    any = true;
+  };
+  drop(c->lane0.b_seen);  // an earlier call's: query_lengths drops its own before it asks for more
+  if (!c->has_graph) return any;
+  for (DevBuf* b : {&c->g_flags, &c->g_spos, &c->g_base, &c->g_tiles, &c->g_scan}) drop(*b);
+  if (!any && c->pfx64 && c->d_fat) {
+    c->d_fat = nullptr;
+    drop(c->g_fat);
+  }
+  return any;
+}
+
 int ctx_alloc(panther_ctx* c, void** p, size_t bytes, const char* what) {
   *p = nullptr;
   bool inject = false;
@@ -53,8 +75,15 @@ int ctx_alloc(panther_ctx* c, void** p, size_t bytes, const char* what) {
   }
   if (inject) return ctx_fail(c, PANTHER_ENOMEM, "%s: allocation failure injected", what);
   if (bytes == 0) bytes = 16;
-  const bool room = !c->mem_reserve || device_room(c) >= bytes;
-  hipError_t e = room ? hipMalloc(p, bytes) : hipErrorOutOfMemory;
+  auto device_alloc = [&] {
+    const bool room = !c->mem_reserve || device_room(c) >= bytes;
+    return room ? hipMalloc(p, bytes) : hipErrorOutOfMemory;
+  };
+  hipError_t e = device_alloc();
+  while (e != hipSuccess && give_back(c)) {
+    (void)hipGetLastError();
+    e = device_alloc();
+  }
   if (e != hipSuccess) {
     *p = nullptr;
     (void)hipGetLastError();

@@ -100,3 +100,65 @@ def test_bisection_walk_edges(oracle, inputs, room, start_all):
             want = oracle.walk(g, T, R, 40 + R, start_all=start_all)
             assert (P.paths() == want).all(), (T, R)
     P.close()
+
+
+def ring_graph(inputs, n):
+    i = np.arange(n)
+    return inputs.graph_from_edges(n, np.stack([i, (i + 1) % n], 1), 1 + i % 97)
+
+
+def test_sampling_takes_what_the_load_left(oracle, inputs):
+    """2 M vertices leave 40 MiB that only a load uses, and the paths need 20
+    MiB more than there is beside it; then a query batch's outputs need what an
+    earlier batch's 16 MiB of marks hold."""
+    import torch
+    from paper_1504_02577_amd.panther import Panther
+
+    g = ring_graph(inputs, 1 << 21)
+    T, R = 5, 1_000_000
+    P = Panther(0)
+    P.load_graph(g)
+    before = torch.cuda.mem_get_info()[0]
+    P.sample_paths(T, R, 3)
+    need = before - torch.cuda.mem_get_info()[0]
+    P.close()
+    P = Panther(0)
+    P.load_graph(g)
+    print(f"case: sample in {need // MB} - 20 MiB", flush=True)
+    leave_room(P, need - 20 * MB)
+    P.sample_paths(T, R, 3)
+    leave_room(P, None)
+    paths = oracle.walk(g, T, R, 3)
+    ptr, pid = oracle.index(g.n, paths)
+    assert (P.paths() == paths).all()
+    got = P.index(g.n)
+    assert (got[0] == ptr).all() and (got[1] == pid).all()
+    P.set_option("autotune", 0)
+    q = np.arange(1500, dtype=np.int32)
+    for room in (None, 6 * MB):
+        print(f"case: batch in {room}", flush=True)
+        leave_room(P, room)
+        k = 5 if room is None else 1024
+        want = oracle.topk(g.n, paths, ptr, pid, q, k)
+        assert all((a == b).all() for a, b in zip(P.topk(q, k), want))
+    P.close()
+
+
+def test_sampling_takes_the_optional_records_memory(oracle, inputs):
+    """A wide graph loaded with room for its records, then sampled in less
+    than the paths need beside them: it is walked by bisection from there on."""
+    from paper_1504_02577_amd.panther import Panther
+
+    g = inputs.graph_from_edges(2000, *dense_graph(2000, True))
+    P = Panther(0)
+    P.load_graph(g)
+    print("case: sample of a wide graph in 40 MiB", flush=True)
+    leave_room(P, 40 * MB)
+    for T, R, seed in ((5, 500_000, 3), (5, 700_000, 4), (20, 3001, 5)):
+        P.sample_paths(T, R, seed)
+        paths = oracle.walk(g, T, R, seed)
+        assert (P.paths() == paths).all()
+        ptr, pid = oracle.index(g.n, paths)
+        got = P.index(g.n)
+        assert (got[0] == ptr).all() and (got[1] == pid).all()
+    P.close()
