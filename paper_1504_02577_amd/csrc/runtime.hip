@@ -568,7 +568,13 @@ extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const in
     free_graph(c, true);
     st = load_graph(c, n, m, row_ptr, col, w, mem, flags, records);
   }
-  if (st == PANTHER_OK) c->err.clear();  // a failed first attempt's message
+  if (st == PANTHER_OK) {
+    c->err.clear();  // a failed first attempt's message
+  } else if (!c->has_graph) {
+    // a rejected graph's storage, or the former graph's, serves nothing now
+    (void)hipStreamSynchronize(c->stream);
+    free_graph(c, true);
+  }
   return st;
 }
 

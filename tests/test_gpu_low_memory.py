@@ -162,3 +162,42 @@ def test_sampling_takes_the_optional_records_memory(oracle, inputs):
         got = P.index(g.n)
         assert (got[0] == ptr).all() and (got[1] == pid).all()
     P.close()
+
+
+def held_by(P, call):
+    """Device bytes that `call` left allocated."""
+    import torch
+
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    call()
+    torch.cuda.synchronize()
+    return before - torch.cuda.mem_get_info()[0]
+
+
+@pytest.mark.parametrize("why", ["column", "symmetry"])
+def test_rejected_graph_holds_no_memory(inputs, why):
+    from paper_1504_02577_amd.panther import PANTHER_CHECK_SYMMETRIC, Panther, PantherError
+
+    g = inputs.graph_from_edges(2000, *dense_graph(2000, False))
+    bad = inputs.Graph(n=g.n, row_ptr=g.row_ptr, col=g.col.copy(), w=g.w.copy())
+    if why == "column":
+        bad.col[-1] = g.n
+    else:
+        bad.w[-1] += 1
+    P = Panther(0)
+    P.load_graph(inputs.graph_from_edges(3, [(0, 1), (1, 2)], [5, 7]))
+    print(f"case: rejected for {why}", flush=True)
+
+    def load_and_reject():
+        P.load_graph(g)  # 300 MiB
+        with pytest.raises(PantherError):
+            P.load_graph(bad, flags=PANTHER_CHECK_SYMMETRIC)
+
+    assert held_by(P, load_and_reject) < 32 * MB
+    P.load_graph(g)
+    # a malformed argument is no rejected graph: the one loaded stays
+    with pytest.raises(PantherError):
+        P.load_graph(g, flags=1 << 7)
+    P.sample_paths(5, 100, 1)
+    P.close()
