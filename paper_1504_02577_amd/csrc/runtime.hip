@@ -573,7 +573,7 @@ extern "C" int panther_load_graph(panther_ctx* c, int32_t n, int64_t m, const in
   } else if (!c->has_graph) {
     // a rejected graph's storage, or the former graph's, serves nothing now
     (void)hipStreamSynchronize(c->stream);
-    free_graph(c, true);
+    for (DevBuf panther_ctx::*b : kGraphBuffers) ctx_release(c->*b);
   }
   return st;
 }
