@@ -201,11 +201,11 @@ static void free_graph(panther_ctx* c, bool release) {
 }
 
 // A graph buffer of at least `bytes`: the kept one unless it is too small, or
-// past 64 MiB more than four times too large (a small graph after a large
-// one gives the large one's memory back).
+// more than 64 MiB too large (what a graph holds, and whether there is room
+// for optional records, is hardly to depend on the graphs before it).
 template <typename T>
 static int graph_alloc(panther_ctx* c, DevBuf& b, size_t bytes, const char* what, T** out) {
-  if (b.cap > ((size_t)64 << 20) && b.cap / 4 > bytes) ctx_release(b);
+  if (b.cap > bytes + ((size_t)64 << 20)) ctx_release(b);
   const int st = ctx_ensure(c, b, std::max<size_t>(bytes, 16), what);
   *out = st ? nullptr : static_cast<T*>(b.p);
   return st;
@@ -529,7 +529,7 @@ static int load_graph(panther_ctx* c, int32_t n, int64_t m, const int32_t* row_p
     // guide records only where they leave at least as much memory free as
     // they take: such a graph has to load, and leave room for its paths, in
     // as little memory as the bisection form needs
-    if (c->d_fat && device_room(c) < c->g_fat.cap) {
+    if (c->d_fat && device_room(c) < fat_bytes) {
       HIPTRY(hipStreamSynchronize(s), "prefix");
       ctx_release(c->g_fat);
       c->d_fat = nullptr;
