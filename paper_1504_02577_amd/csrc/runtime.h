@@ -134,7 +134,9 @@ struct panther_ctx {
 
 int ctx_fail(panther_ctx* c, int code, const char* fmt, ...);
 int ctx_hip(panther_ctx* c, hipError_t e, const char* what);
-int ctx_alloc(panther_ctx* c, void** p, size_t bytes, const char* what);  // thread-safe
+// Device memory, from any thread; a null `what` leaves no message on failure
+// (the caller does without).
+int ctx_alloc(panther_ctx* c, void** p, size_t bytes, const char* what);
 // Free device memory an allocation may still take.
 size_t device_room(panther_ctx* c);
 // Makes b hold at least `bytes`; the contents are not preserved on growth.

@@ -73,7 +73,10 @@ int ctx_alloc(panther_ctx* c, void** p, size_t bytes, const char* what) {
     else if (c->fail_alloc_after > 0)
       --c->fail_alloc_after;
   }
-  if (inject) return ctx_fail(c, PANTHER_ENOMEM, "%s: allocation failure injected", what);
+  if (inject) {
+    if (!what) return PANTHER_ENOMEM;
+    return ctx_fail(c, PANTHER_ENOMEM, "%s: allocation failure injected", what);
+  }
   if (bytes == 0) bytes = 16;
   auto device_alloc = [&] {
     const bool room = !c->mem_reserve || device_room(c) >= bytes;
@@ -87,6 +90,7 @@ int ctx_alloc(panther_ctx* c, void** p, size_t bytes, const char* what) {
   if (e != hipSuccess) {
     *p = nullptr;
     (void)hipGetLastError();
+    if (!what) return PANTHER_ENOMEM;
     return ctx_fail(c, PANTHER_ENOMEM, "%s: cannot allocate %zu bytes", what, bytes);
   }
   return PANTHER_OK;
@@ -818,27 +822,24 @@ int query_lengths(panther_ctx* c, Lane* lane, const int32_t* dq, int64_t nq, hip
   TRY(ctx_ensure(c, lane->b_qlen, bytes, "query lengths"));
   uint64_t* qlen = static_cast<uint64_t*>(lane->b_qlen.p);
   // without room for the scratch every query is answered by itself
-  if (once && nq > 1 && nq < ((int64_t)1 << 31) &&
-      ctx_ensure(c, lane->b_rep, sizeof(int32_t) * (size_t)nq, "repeated queries") ==
-          PANTHER_OK) {
-    const size_t words = sizeof(uint64_t) * (size_t)c->n;
-    const bool grown = !lane->b_seen.p || lane->b_seen.cap < words;
-    if (!grown || ctx_ensure(c, lane->b_seen, words, "repeated queries") == PANTHER_OK) {
-      if (grown || lane->seen_call == ~0u) {
-        HIPTRY(hipMemsetAsync(lane->b_seen.p, 0, lane->b_seen.cap, s), "repeated queries");
-        lane->seen_call = 0;
-      }
-      ++lane->seen_call;
-      launch_query_lengths_once(c->d_inv_ptr, dq, nq,
-                                static_cast<unsigned long long*>(lane->b_seen.p),
-                                lane->seen_call, static_cast<int32_t*>(lane->b_rep.p), qlen, s);
-    } else {
-      once = false;
+  once = once && nq > 1 && nq < ((int64_t)1 << 31) &&
+         ctx_ensure(c, lane->b_rep, sizeof(int32_t) * (size_t)nq, nullptr) == PANTHER_OK;
+  // (after b_rep, whose allocation may have given b_seen back)
+  const size_t words = sizeof(uint64_t) * (size_t)c->n;
+  const bool fresh = !lane->b_seen.p || lane->b_seen.cap < words || lane->seen_call == ~0u;
+  if (once && ctx_ensure(c, lane->b_seen, words, nullptr) == PANTHER_OK) {
+    if (fresh) {
+      lane->seen_call = ~0u;  // not cleared, should the clearing fail
+      HIPTRY(hipMemsetAsync(lane->b_seen.p, 0, lane->b_seen.cap, s), "repeated queries");
+      lane->seen_call = 0;
     }
+    ++lane->seen_call;
+    launch_query_lengths_once(c->d_inv_ptr, dq, nq,
+                              static_cast<unsigned long long*>(lane->b_seen.p), lane->seen_call,
+                              static_cast<int32_t*>(lane->b_rep.p), qlen, s);
   } else {
-    once = false;
+    launch_query_lengths(c->d_inv_ptr, dq, nq, qlen, s);
   }
-  if (!once) launch_query_lengths(c->d_inv_ptr, dq, nq, qlen, s);
   HIPTRY(hipGetLastError(), "query lengths");
   if (!to_host) {
     *len = nullptr;

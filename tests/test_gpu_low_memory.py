@@ -231,3 +231,27 @@ def test_smaller_graph_after_a_larger_one(oracle, inputs, wide):
           flush=True)
     assert held[1] - held[0] < 80 * MB
     assert held[1] > 122 * MB
+
+
+def test_batch_without_room_for_its_marks(oracle, inputs):
+    """The marks of repeated vertices (32 MiB at 4 M vertices) are optional: a
+    batch without them is answered, and leaves no message behind."""
+    from paper_1504_02577_amd.panther import Panther, panther_last_error
+
+    g = ring_graph(inputs, 1 << 22)
+    T, R = 5, 100_000
+    paths = oracle.walk(g, T, R, 3)
+    ptr, pid = oracle.index(g.n, paths)
+    busy = np.argsort(-np.diff(ptr))[:40]
+    P = Panther(0)
+    P.load_graph(g)
+    P.sample_paths(T, R, 3)
+    for room in (-56 * MB, None):  # 24 MiB with the 80 that only a load uses
+        leave_room(P, room)
+        for nq in (2, 61, 3000):
+            print(f"case: batch of {nq} in {room}", flush=True)
+            q = np.random.default_rng(nq).choice(busy, nq).astype(np.int32)
+            want = oracle.topk(g.n, paths, ptr, pid, q, 21)
+            assert all((a == b).all() for a, b in zip(P.topk(q, 21), want))
+            assert panther_last_error(P.h) == ""
+    P.close()
