@@ -97,7 +97,8 @@ __global__ void __launch_bounds__(kBlock, 2)
 k_knn_fp64(const float* __restrict__ theta, int32_t n, int32_t D, const float* __restrict__ qtheta,
            int32_t exclude_self, const int32_t* __restrict__ queries,
            const int32_t* __restrict__ rows, int64_t nq, int32_t kp, int32_t cap,
-           double* __restrict__ part_d, int32_t* __restrict__ part_v) {
+           double* __restrict__ part_d, int32_t* __restrict__ part_v, int32_t k,
+           int32_t* __restrict__ out_ids, double* __restrict__ out_dist) {
   extern __shared__ __align__(16) char lds[];
   double* qv = reinterpret_cast<double*>(lds);               // [D][kQT]
   double* bd = qv + (size_t)kQT * D;                         // [kQT][cap]
@@ -234,6 +235,14 @@ k_knn_fp64(const float* __restrict__ theta, int32_t n, int32_t D, const float* _
     if (qid[q] < 0) continue;
     int c = (int)cnt[q];  // <= cap
     wave_sort_pairs(bd + q * cap, bv + q * cap, c);
+    if (gridDim.y == 1) {  // every row seen: the answer itself
+      const int64_t qi = rows ? (int64_t)rows[q0 + q] : q0 + q;
+      for (int j = lane; j < k; j += kWave) {
+        out_ids[qi * k + j] = j < c ? bv[q * cap + j] : -1;
+        out_dist[qi * k + j] = j < c ? sqrt(bd[q * cap + j]) : INFINITY;
+      }
+      continue;
+    }
     if (c > kp) c = kp;
     const int64_t o = ((q0 + q) * gridDim.y + blockIdx.y) * kp;
     for (int j = lane; j < kp; j += kWave) {
@@ -499,11 +508,10 @@ int launch_knn_recompute(const float* theta, int32_t n, int32_t D, const float* 
 }
 
 namespace {
-// Queries of one launch of the FP64 form, and its workspace: per query S
-// slices of kp pairs.
-constexpr int64_t kFp64Batch = 32768;
+// Workspace of the FP64 form: per query S slices of kp pairs (one slice
+// writes the results itself).
 size_t fp64_bytes(int64_t nq, int64_t S, int kp) {
-  return (sizeof(double) + sizeof(int32_t)) * (size_t)nq * S * kp;
+  return S > 1 ? (sizeof(double) + sizeof(int32_t)) * (size_t)nq * S * kp : 0;
 }
 int pow2_at_least(int k) {
   int kp = 1;
@@ -526,16 +534,14 @@ int64_t fp64_slices(int64_t nq, int32_t n, int kp, int num_cus) {
 size_t knn_fp64_bytes(int64_t nq, int32_t n, int32_t k, int num_cus) {
   if (nq <= 0) return 0;
   const int kp = pow2_at_least(k);
-  nq = std::min(nq, kFp64Batch);
   return fp64_bytes(nq, fp64_slices(nq, n, kp, num_cus), kp);
 }
 
 // qtheta: the queries' feature rows (theta itself for one graph, the other
 // graph's for the cross-graph form, which excludes no row).  rows (may be
 // null): the call answers queries[rows[i]] into output row rows[i] for
-// i < nq, instead of queries[i] into row i.  work: at least
-// knn_fp64_bytes(nq, ...) bytes, or less: then fewer slices or queries go at
-// a time (at least one slice of one query must fit).
+// i < nq, instead of queries[i] into row i.  work: knn_fp64_bytes(nq, ...)
+// bytes (up to 12 MiB), or less, or none: then in fewer slices.
 int launch_knn_fp64(const float* theta, int32_t n, int32_t D, const float* qtheta,
                     bool exclude_self, const int32_t* queries, const int32_t* rows, int64_t nq,
                     int32_t k, int num_cus, void* work, size_t work_bytes, int32_t* out_ids,
@@ -546,29 +552,18 @@ int launch_knn_fp64(const float* theta, int32_t n, int32_t D, const float* qthet
   hipError_t e = hipFuncSetAttribute((const void*)k_knn_fp64,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return (int)e;
-  int64_t most = std::min(nq, kFp64Batch);
-  while (most > 1 && fp64_bytes(most, 1, kp) > work_bytes) most = (most + 1) / 2;
-  if (most > 0 && fp64_bytes(most, 1, kp) > work_bytes) return (int)hipErrorInvalidValue;
-  for (int64_t i = 0; i < nq; i += most) {
-    const int64_t m = std::min(most, nq - i);
-    int64_t S = fp64_slices(m, n, kp, num_cus);
-    while (S > 1 && fp64_bytes(m, S, kp) > work_bytes) --S;
-    const int64_t tiles = (m + kQT - 1) / kQT;
-    double* part_d = static_cast<double*>(work);
-    int32_t* part_v = reinterpret_cast<int32_t*>(part_d + m * S * kp);
-    // with a row list the batch is a part of the list, else of the queries
-    const int32_t* qs = rows ? queries : queries + i;
-    const int32_t* rs = rows ? rows + i : nullptr;
-    int32_t* ids = rows ? out_ids : out_ids + i * k;
-    double* dist = rows ? out_dist : out_dist + i * k;
-    k_knn_fp64<<<dim3((unsigned)tiles, (unsigned)S), kBlock, lds, s>>>(
-        theta, n, D, qtheta, exclude_self ? 1 : 0, qs, rs, m, kp, cap, part_d, part_v);
-    k_knn_merge<<<(unsigned)m, kBlock, 0, s>>>(part_d, part_v, (int32_t)(S * kp), kp, k, rs, ids,
-                                               dist);
-    e = hipGetLastError();
-    if (e != hipSuccess) return (int)e;
-  }
-  return 0;
+  if (nq <= 0) return 0;
+  int64_t S = fp64_slices(nq, n, kp, num_cus);
+  while (S > 1 && fp64_bytes(nq, S, kp) > work_bytes) --S;
+  double* part_d = static_cast<double*>(work);
+  int32_t* part_v = S > 1 ? reinterpret_cast<int32_t*>(part_d + nq * S * kp) : nullptr;
+  k_knn_fp64<<<dim3((unsigned)((nq + kQT - 1) / kQT), (unsigned)S), kBlock, lds, s>>>(
+      theta, n, D, qtheta, exclude_self ? 1 : 0, queries, rows, nq, kp, cap, part_d, part_v, k,
+      out_ids, out_dist);
+  if (S > 1)
+    k_knn_merge<<<(unsigned)nq, kBlock, 0, s>>>(part_d, part_v, (int32_t)(S * kp), kp, k, rows,
+                                                out_ids, out_dist);
+  return (int)hipGetLastError();
 }
 
 }  // namespace panther

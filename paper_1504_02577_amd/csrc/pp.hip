@@ -138,16 +138,23 @@ extern "C" int panther_pp_topk(panther_ctx* c, const int32_t* queries, int64_t n
   return PANTHER_OK;
 }
 
+// The FP64 form over the database context c.  Its workspace, which only makes
+// it faster, is as large as the lane may hold and the device has.
+static int run_fp64(panther_ctx* c, Lane* lane, const float* qtheta, bool exclude_self,
+                    const int32_t* dq, int64_t nq, int32_t D, int32_t k, int32_t* d_ids,
+                    double* d_dist, hipStream_t s) {
+  const size_t need = std::min(knn_fp64_bytes(nq, c->n, k, c->num_cus), lane->work_room);
+  if (need) (void)ctx_ensure(c, lane->b_fbw, need, nullptr);
+  const int e = launch_knn_fp64(c->d_theta, c->n, D, qtheta, exclude_self, dq, nullptr, nq, k,
+                                c->num_cus, lane->b_fbw.p, lane->b_fbw.cap, d_ids, d_dist, s);
+  HIPTRY((hipError_t)e, "pp fp64 knn");
+  return PANTHER_OK;
+}
+
 int run_pp(panther_ctx* c, Lane* lane, const int32_t* dq, int64_t nq, int32_t D, int32_t k,
            int32_t* d_ids, double* d_dist, hipStream_t s) {
-  if (c->pp_form == PANTHER_PP_FP64) {
-    const size_t need = knn_fp64_bytes(nq, c->n, k, c->num_cus);
-    TRY(ctx_ensure(c, lane->b_fbw, need, "pp fp64 knn"));
-    const int e = launch_knn_fp64(c->d_theta, c->n, D, c->d_theta, true, dq, nullptr, nq, k,
-                                  c->num_cus, lane->b_fbw.p, lane->b_fbw.cap, d_ids, d_dist, s);
-    HIPTRY((hipError_t)e, "pp fp64 knn");
-    return PANTHER_OK;
-  }
+  if (c->pp_form == PANTHER_PP_FP64)
+    return run_fp64(c, lane, c->d_theta, true, dq, nq, D, k, d_ids, d_dist, s);
   return run_pp_bf16(c, lane, dq, nq, D, k, d_ids, d_dist, s, nullptr);
 }
 
@@ -209,11 +216,7 @@ extern "C" int panther_pp_topk_cross(panther_ctx* qc, panther_ctx* dbc, const in
   }
   stage_begin(dbc, 4, s);
   if (dbc->pp_form == PANTHER_PP_FP64) {
-    const size_t need = knn_fp64_bytes(nq, dbc->n, k, dbc->num_cus);
-    TRY(ctx_ensure(dbc, lane->b_fbw, need, "pp fp64 cross knn"));
-    const int e = launch_knn_fp64(dbc->d_theta, dbc->n, D, qc->d_theta, false, dq, nullptr, nq, k,
-                                  dbc->num_cus, lane->b_fbw.p, lane->b_fbw.cap, d_ids, d_dist, s);
-    HIPTRY((hipError_t)e, "pp fp64 cross knn");
+    TRY(run_fp64(dbc, lane, qc->d_theta, false, dq, nq, D, k, d_ids, d_dist, s));
   } else {
     TRY(prepare_bf16(dbc, D, s));
     TRY(run_pp_bf16(dbc, lane, dq, nq, D, k, d_ids, d_dist, s, qc->d_theta));

@@ -1562,13 +1562,12 @@ int run_pp_bf16(panther_ctx* c, Lane* lane, const int32_t* dq, int64_t nq, int32
 }  // namespace panther
 
 // Device bytes of the lane scratch a Panther++ call of nq queries takes: in
-// the FP64 form its slices' results; in the BF16 form pools,
+// the FP64 form none that it needs; in the BF16 form pools,
 // statistics, query order and its sort, certificate, exact recompute of
 // every query, cross-graph query rows.
 size_t pp_lane_bytes(const panther_ctx* c, int64_t nq, int32_t k) {
   if (nq <= 0) return 0;
-  if (c->pp_form == PANTHER_PP_FP64)
-    return panther::knn_fp64_bytes(nq, c->n, k, c->num_cus);
+  if (c->pp_form == PANTHER_PP_FP64) return 0;
   const size_t n = (size_t)nq;
   // either tile width may be chosen: the larger need
   size_t b = 0;

@@ -49,6 +49,9 @@ struct Lane {
   // that stands for each query's vertex, and per vertex {call, position}
   DevBuf b_rep, b_seen;
   uint32_t seen_call = 0;
+  // most bytes of scratch a call may add that it could do without (a serving
+  // lane's share of the budget past what its batch needs)
+  size_t work_room = ~(size_t)0;
   bool have_stats = false;
   double max_rel_err = 0.0;
   double mean_pre_recall = 0.0;

@@ -255,3 +255,53 @@ def test_batch_without_room_for_its_marks(oracle, inputs):
             assert all((a == b).all() for a, b in zip(P.topk(q, 21), want))
             assert panther_last_error(P.h) == ""
     P.close()
+
+
+def test_fp64_search_needs_no_workspace(oracle, inputs):
+    """The FP64 form splits the rows when its workspace fits, and answers
+    without any: in a full device, and in a serving lane whose share holds a
+    request's rows (7.6 KiB) and little more."""
+    import torch
+    from paper_1504_02577_amd.panther import Panther, Server
+
+    g = inputs.rmat_graph(15)
+    T, R, seed, D = 5, 100_000, 3, 100
+    paths = oracle.walk(g, T, R, seed)
+    ptr, pid = oracle.index(g.n, paths)
+    theta = oracle.features(g.n, paths, ptr, pid, D)
+    P = Panther(0)
+    P.load_graph(g)
+    P.sample_paths(T, R, seed)
+    P.set_option("pp.form", 0)
+    rng = np.random.default_rng(1)
+    P.pp_topk(np.array([0], np.int32), D, 1)  # features
+    for room in (-(1 << 40), None):
+        leave_room(P, room)
+        for nq, k in ((1, 10), (9, 256), (61, 50)):
+            print(f"case: fp64 nq={nq} k={k} room={room}", flush=True)
+            q = rng.integers(0, g.n, nq).astype(np.int32)
+            out = (torch.empty((nq, k), dtype=torch.int32, device="cuda"),
+                   torch.empty((nq, k), dtype=torch.float64, device="cuda"))
+            torch.cuda.synchronize()
+            P.pp_topk(torch.from_numpy(q).cuda(), D, k, out=out)
+            wi, wd = oracle.knn(theta, q, k)
+            assert (out[0].cpu().numpy() == wi).all()
+            assert (out[1].cpu().numpy().view(np.uint64) == np.ascontiguousarray(wd).view(np.uint64)).all()
+    for budget in (8 << 10, 16 << 10, 1 << 20):
+        print(f"case: fp64 serving in {budget} bytes", flush=True)
+        srv = Server(P, mem_budget_bytes=budget, max_batch=16, lanes=1, D=D)
+        qs = rng.integers(0, g.n, 40).astype(np.int32)
+        wi, wd = oracle.knn(theta, qs, 256)
+        assert [srv.submit(1, int(x), 256, i) for i, x in enumerate(qs)] == [0] * 40
+        got = []
+        for _ in range(3000):
+            got += srv.poll(10_000)
+            if len(got) == 40:
+                break
+        for r in got:
+            assert r["status"] == 0 and (r["ids"] == wi[r["tag"]]).all()
+            assert (r["scores"] == wd[r["tag"]]).all()
+        m = srv.memory()
+        assert len(got) == 40 and m["peak_lane_bytes"] <= m["lane_share_bytes"]
+        assert srv.stop() == 0
+    P.close()
