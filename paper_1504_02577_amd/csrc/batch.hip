@@ -1588,8 +1588,9 @@ size_t batched_query_bytes(const BatchSizing& z, uint64_t L, int32_t kmax) {
   return bytes;
 }
 
-// Device bytes of a batched call's fixed buffers (plan minimum, queue).
-size_t batched_fixed_bytes() { return 4096 + sizeof(ItemRec) + 64 + sizeof(uint32_t) * 16 + 256; }
+// Device bytes of a batched call's fixed buffers (plan minimum, queue; the one
+// record that a batch of hubs keeps is among its queries' own).
+size_t batched_fixed_bytes() { return 4096 + 64 + sizeof(uint32_t) * 16 + 256; }
 
 // Device bytes the lane's query scratch holds now.
 size_t lane_device_bytes(const Lane* lane) {

@@ -1579,7 +1579,7 @@ size_t pp_lane_bytes(const panther_ctx* c, int64_t nq, int32_t k) {
   }
   b += sizeof(unsigned long long) * kStatWords;
   b += (2 * sizeof(uint32_t) + 2 * sizeof(int32_t)) * ((n + 63) / 64 * 64);
-  b += sort_pairs_bytes(nq);
+  if (nq > kSmallOrder) b += sort_pairs_bytes(nq);
   b += (2 * sizeof(int32_t) + sizeof(double)) * n;
   b += panther::knn_range_bytes(nq);
   b += (sizeof(uint16_t) * 64 + sizeof(float)) * n;
