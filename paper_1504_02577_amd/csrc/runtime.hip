@@ -720,6 +720,7 @@ extern "C" int panther_get_paths(panther_ctx* c, int32_t* out, int mem) {
   c->err.clear();
   if (!c->has_paths) return ctx_fail(c, PANTHER_ESTATE, "no paths sampled");
   if (!out) return ctx_fail(c, PANTHER_EINVAL, "null output");
+  if (hipSetDevice(c->device) != hipSuccess) return ctx_fail(c, PANTHER_EDEVICE, "hipSetDevice");
   const size_t w = sizeof(int32_t) * (size_t)(c->T + 1);
   if (mem == PANTHER_MEM_DEVICE) {
     launch_pack_paths(c->d_paths, c->stride, c->T + 1, c->R, out, c->stream);
