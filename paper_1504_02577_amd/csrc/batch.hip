@@ -1699,17 +1699,19 @@ int run_batched(panther_ctx* c, Lane* lane, const int32_t* dq, const uint64_t* q
       BatchConfig best_cfg{};
       float best = 1e30f;
       // Where tier B's largest table takes the longest list, a smaller one
-      // still sends lists to the hub pipeline: stage 1 then times the whole
-      // call, or it would credit those lists to the smaller table (2,378
-      // queries of 10^4 paths, a handful of long lists: 147 us against 122).
+      // still sends lists to the hub pipeline: stage 1 then times the prefix
+      // with its hubs, or it would credit those lists to the smaller table
+      // (2,378 queries of 10^4 paths, a handful of long lists: 147 us against
+      // 122).  (The prefix as before, not the whole call: that made the first
+      // call of 60,000 queries of tier B's lists, T = 20, 95 ms instead of 48.)
       bool whole = qlen && nq <= kStage2MaxQueries;
       const uint64_t widest = (uint64_t)layout_for(c, BatchConfig{}).TB / (2 * (uint64_t)c->T);
-      for (int64_t i = 0; i < nq && whole; ++i) whole = qlen[i] <= widest || qlen[i] == kRepeated;
+      for (int64_t i = 0; i < m && whole; ++i) whole = qlen[i] <= widest || qlen[i] == kRepeated;
       for (int blk : kBlocks)
         for (int wgs : kWgs) {
           const BatchConfig cfg{blk, wgs, 1, 0};
           float ms = 0.f;
-          if (!st) st = time_cfg(cfg, whole ? nq : m, whole, &ms);
+          if (!st) st = time_cfg(cfg, m, whole, &ms);
           if (!st && ms < best) {
             best = ms;
             best_cfg = cfg;
