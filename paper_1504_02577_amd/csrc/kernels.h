@@ -113,12 +113,13 @@ void launch_query_lengths(const uint64_t* inv_ptr, const int32_t* queries, int64
                           uint64_t* out, hipStream_t s);
 // The same with repeated queries marked: one position (below 2^31) of every
 // queried vertex stands for it, rep[i] is that position, and the others get
-// length kRepeated.  seen: a word per vertex, zero at first, and call a
-// number above every earlier one (the first is 1).
+// length kRepeated.  seen: a word per vertex (mask ~0), or mask + 1 words, a
+// power of two of at least 2 nq; zero at first, and call a number above every
+// earlier one (the first is 1).
 constexpr uint64_t kRepeated = ~0ull;
 void launch_query_lengths_once(const uint64_t* inv_ptr, const int32_t* queries, int64_t nq,
-                               unsigned long long* seen, uint32_t call, int32_t* rep,
-                               uint64_t* out, hipStream_t s);
+                               unsigned long long* seen, uint32_t mask, uint32_t call,
+                               int32_t* rep, uint64_t* out, hipStream_t s);
 // Output rows of repeated queries copied from those of rep[i].
 void launch_copy_rows(const int32_t* rep, int64_t nq, int32_t k, int32_t* ids, uint32_t* counts,
                       int32_t* len, hipStream_t s);

@@ -46,7 +46,7 @@ struct Lane {
   double stat_scanned = 0.0;  // (query, row) products of its pool pass / (queries * vertices)
   PinnedBuf h_qlen;  // path-list lengths of the last call's queries
   // repeated queries of a batch (query_lengths with `once`): the position
-  // that stands for each query's vertex, and per vertex {call, position}
+  // that stands for each query's vertex, and slots of {call, position}
   DevBuf b_rep, b_seen;
   uint32_t seen_call = 0;
   // most bytes of scratch a call may add that it could do without (a serving

@@ -825,10 +825,14 @@ int query_lengths(panther_ctx* c, Lane* lane, const int32_t* dq, int64_t nq, hip
   // without room for the scratch every query is answered by itself
   once = once && nq > 1 && nq < ((int64_t)1 << 31) &&
          ctx_ensure(c, lane->b_rep, sizeof(int32_t) * (size_t)nq, nullptr) == PANTHER_OK;
+  // marks: a word per vertex, or a hash of 2 to 4 words per query
+  uint64_t slots = 2;
+  while (slots < 2 * (uint64_t)nq) slots <<= 1;
+  const bool direct = slots >= (uint64_t)c->n;
+  const size_t seen_bytes = sizeof(uint64_t) * (size_t)(direct ? (uint64_t)c->n : slots);
   // (after b_rep, whose allocation may have given b_seen back)
-  const size_t words = sizeof(uint64_t) * (size_t)c->n;
-  const bool fresh = !lane->b_seen.p || lane->b_seen.cap < words || lane->seen_call == ~0u;
-  if (once && ctx_ensure(c, lane->b_seen, words, nullptr) == PANTHER_OK) {
+  const bool fresh = !lane->b_seen.p || lane->b_seen.cap < seen_bytes || lane->seen_call == ~0u;
+  if (once && ctx_ensure(c, lane->b_seen, seen_bytes, nullptr) == PANTHER_OK) {
     if (fresh) {
       lane->seen_call = ~0u;  // not cleared, should the clearing fail
       HIPTRY(hipMemsetAsync(lane->b_seen.p, 0, lane->b_seen.cap, s), "repeated queries");
@@ -836,7 +840,8 @@ int query_lengths(panther_ctx* c, Lane* lane, const int32_t* dq, int64_t nq, hip
     }
     ++lane->seen_call;
     launch_query_lengths_once(c->d_inv_ptr, dq, nq,
-                              static_cast<unsigned long long*>(lane->b_seen.p), lane->seen_call,
+                              static_cast<unsigned long long*>(lane->b_seen.p),
+                              direct ? ~0u : (uint32_t)(slots - 1), lane->seen_call,
                               static_cast<int32_t*>(lane->b_rep.p), qlen, s);
   } else {
     launch_query_lengths(c->d_inv_ptr, dq, nq, qlen, s);

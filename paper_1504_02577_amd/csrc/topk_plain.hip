@@ -101,15 +101,21 @@ k_topk_plain(const int32_t* __restrict__ qp, int32_t n, const uint64_t* __restri
 }
 
 // Path-list lengths of the queries.  With rep, a vertex repeated in the batch
-// is answered once: one of its positions, the first to reach seen[vertex],
+// is answered once: one of its positions, the first to claim a slot of seen,
 // stands for it (rep[i] == i), and the others get that position and the
 // length kRepeated (the planner leaves them out, and their rows are copied).
-// seen holds {call number, position} per vertex, so it needs no clearing and
-// the lengths no launch of their own.
+// seen holds {call number, position} words, so it needs no clearing and the
+// lengths no launch of their own.  It is indexed by vertex (mask ~0), or, where
+// the batch is small beside the graph, by a hash of at least twice as many
+// slots as queries: a slot of an earlier call is free, and as slots are never
+// freed within a call, a vertex ends at its claimed slot or at a free one.
+// (8 bytes for every vertex made the first call on an R-MAT 20 graph, which
+// clears them, 70 us longer.)
 __global__ void k_query_lengths(const uint64_t* __restrict__ inv_ptr,
                                 const int32_t* __restrict__ queries, int64_t nq,
-                                unsigned long long* __restrict__ seen, uint32_t call,
-                                int32_t* __restrict__ rep, uint64_t* __restrict__ out) {
+                                unsigned long long* __restrict__ seen, uint32_t mask,
+                                uint32_t call, int32_t* __restrict__ rep,
+                                uint64_t* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i >= nq) return;
   const int32_t q = queries[i];
@@ -119,12 +125,27 @@ __global__ void k_query_lengths(const uint64_t* __restrict__ inv_ptr,
     return;
   }
   const unsigned long long mine = ((unsigned long long)call << 32) | (uint32_t)i;
-  unsigned long long old = __hip_atomic_load(&seen[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  // an entry of this call stays; an older one is replaced by exactly one
-  if ((uint32_t)(old >> 32) != call) old = atomicCAS(&seen[q], old, mine);
-  const bool first = (uint32_t)(old >> 32) != call;
-  rep[i] = first ? (int32_t)i : (int32_t)(uint32_t)old;
-  out[i] = first ? L : kRepeated;
+  uint32_t h = mask == ~0u
+                   ? (uint32_t)q
+                   : (uint32_t)((uint64_t)(uint32_t)q * 0x9E3779B97F4A7C15ull >> 32) & mask;
+  int32_t first = (int32_t)i;
+  for (uint32_t probe = 0; probe <= mask; ++probe) {  // (half of the slots stay free)
+    unsigned long long old =
+        __hip_atomic_load(&seen[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((uint32_t)(old >> 32) != call) {
+      // a free slot goes to exactly one; the others see its entry
+      const unsigned long long prev = atomicCAS(&seen[h], old, mine);
+      if (prev == old) break;
+      old = prev;
+    }
+    if (queries[(uint32_t)old] == q) {
+      first = (int32_t)(uint32_t)old;
+      break;
+    }
+    h = (h + 1) & mask;
+  }
+  rep[i] = first;
+  out[i] = first == (int32_t)i ? L : kRepeated;
 }
 
 // Rows of repeated queries from the rows of the positions that stand for
@@ -173,15 +194,15 @@ void launch_zero_u32(uint32_t* p, uint64_t n, hipStream_t s) {
 
 void launch_query_lengths(const uint64_t* inv_ptr, const int32_t* queries, int64_t nq,
                           uint64_t* out, hipStream_t s) {
-  launch_query_lengths_once(inv_ptr, queries, nq, nullptr, 0u, nullptr, out, s);
+  launch_query_lengths_once(inv_ptr, queries, nq, nullptr, 0u, 0u, nullptr, out, s);
 }
 
 void launch_query_lengths_once(const uint64_t* inv_ptr, const int32_t* queries, int64_t nq,
-                               unsigned long long* seen, uint32_t call, int32_t* rep,
-                               uint64_t* out, hipStream_t s) {
+                               unsigned long long* seen, uint32_t mask, uint32_t call,
+                               int32_t* rep, uint64_t* out, hipStream_t s) {
   if (nq > 0)
     k_query_lengths<<<(unsigned)((nq + kBlock - 1) / kBlock), kBlock, 0, s>>>(
-        inv_ptr, queries, nq, seen, call, rep, out);
+        inv_ptr, queries, nq, seen, mask, call, rep, out);
 }
 
 void launch_copy_rows(const int32_t* rep, int64_t nq, int32_t k, int32_t* ids, uint32_t* counts,

@@ -109,8 +109,7 @@ def ring_graph(inputs, n):
 
 def test_sampling_takes_what_the_load_left(oracle, inputs):
     """2 M vertices leave 40 MiB that only a load uses, and the paths need 20
-    MiB more than there is beside it; then a query batch's outputs need what an
-    earlier batch's 16 MiB of marks hold."""
+    MiB more than there is beside it."""
     import torch
     from paper_1504_02577_amd.panther import Panther
 
@@ -133,14 +132,6 @@ def test_sampling_takes_what_the_load_left(oracle, inputs):
     assert (P.paths() == paths).all()
     got = P.index(g.n)
     assert (got[0] == ptr).all() and (got[1] == pid).all()
-    P.set_option("autotune", 0)
-    q = np.arange(1500, dtype=np.int32)
-    for room in (None, 6 * MB):
-        print(f"case: batch in {room}", flush=True)
-        leave_room(P, room)
-        k = 5 if room is None else 1024
-        want = oracle.topk(g.n, paths, ptr, pid, q, k)
-        assert all((a == b).all() for a, b in zip(P.topk(q, k), want))
     P.close()
 
 
@@ -233,27 +224,41 @@ def test_smaller_graph_after_a_larger_one(oracle, inputs, wide):
     assert held[1] > 122 * MB
 
 
-def test_batch_without_room_for_its_marks(oracle, inputs):
-    """The marks of repeated vertices (32 MiB at 4 M vertices) are optional: a
-    batch without them is answered, and leaves no message behind."""
+def test_marks_of_repeated_queries_are_optional(oracle, inputs):
+    """A batch of every vertex in other order, after topk_all has allocated all
+    but its marks (16 MiB at 2 M vertices): answered without them, with no
+    message left; and a later batch's outputs may take the memory of marks."""
+    import torch
     from paper_1504_02577_amd.panther import Panther, panther_last_error
 
-    g = ring_graph(inputs, 1 << 22)
-    T, R = 5, 100_000
+    n = 1 << 21
+    g = ring_graph(inputs, n)
+    T, R, k = 5, 100_000, 3
     paths = oracle.walk(g, T, R, 3)
     ptr, pid = oracle.index(g.n, paths)
-    busy = np.argsort(-np.diff(ptr))[:40]
     P = Panther(0)
     P.load_graph(g)
     P.sample_paths(T, R, 3)
-    for room in (-56 * MB, None):  # 24 MiB with the 80 that only a load uses
+    P.set_option("autotune", 0)
+    all_rows = P.topk_all(n, k)
+    q = np.random.default_rng(0).integers(0, n, n).astype(np.int32)
+    out = (torch.empty((n, k), dtype=torch.int32, device="cuda"),
+           torch.empty((n, k), dtype=torch.uint32, device="cuda"),
+           torch.empty((n,), dtype=torch.int32, device="cuda"))
+    dq = torch.from_numpy(q).cuda()
+    torch.cuda.synchronize()
+    for room in (-28 * MB, None):  # 12 MiB with the 40 that only a load uses
+        print(f"case: batch of {n} in {room}", flush=True)
         leave_room(P, room)
-        for nq in (2, 61, 3000):
-            print(f"case: batch of {nq} in {room}", flush=True)
-            q = np.random.default_rng(nq).choice(busy, nq).astype(np.int32)
-            want = oracle.topk(g.n, paths, ptr, pid, q, 21)
-            assert all((a == b).all() for a, b in zip(P.topk(q, 21), want))
-            assert panther_last_error(P.h) == ""
+        P.topk(dq, k, out=out)
+        torch.cuda.synchronize()
+        assert all((a.cpu().numpy() == b[q]).all() for a, b in zip(out, all_rows))
+        assert panther_last_error(P.h) == ""
+    print("case: outputs in the marks' memory", flush=True)
+    leave_room(P, 6 * MB)
+    q = np.arange(1500, dtype=np.int32)
+    want = oracle.topk(g.n, paths, ptr, pid, q, 1024)  # 12 MiB of them
+    assert all((a == b).all() for a, b in zip(P.topk(q, 1024), want))
     P.close()
 
 
