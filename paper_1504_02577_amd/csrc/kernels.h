@@ -114,7 +114,7 @@ void launch_query_lengths(const uint64_t* inv_ptr, const int32_t* queries, int64
 // The same with repeated queries marked: one position (below 2^31) of every
 // queried vertex stands for it, rep[i] is that position, and the others get
 // length kRepeated.  seen: a word per vertex (mask ~0), or mask + 1 words, a
-// power of two of at least 2 nq; zero at first, and call a number above every
+// power of two above nq; zero at first, and call a number above every
 // earlier one (the first is 1).
 constexpr uint64_t kRepeated = ~0ull;
 void launch_query_lengths_once(const uint64_t* inv_ptr, const int32_t* queries, int64_t nq,

@@ -825,10 +825,13 @@ int query_lengths(panther_ctx* c, Lane* lane, const int32_t* dq, int64_t nq, hip
   // without room for the scratch every query is answered by itself
   once = once && nq > 1 && nq < ((int64_t)1 << 31) &&
          ctx_ensure(c, lane->b_rep, sizeof(int32_t) * (size_t)nq, nullptr) == PANTHER_OK;
-  // marks: a word per vertex, or a hash of 2 to 4 words per query
-  uint64_t slots = 2;
-  while (slots < 2 * (uint64_t)nq) slots <<= 1;
-  const bool direct = slots >= (uint64_t)c->n;
+  // Marks: a word per vertex, or, for up to 1,024 queries, a hash of 32 words
+  // or more per query.  (The hash spares the first call on a graph the clearing
+  // of n words; at 10,000 queries and three slots each its longest chains of
+  // atomics made every call 4 per cent slower: 0.201 -> 0.208 ms.)
+  uint64_t slots = 32;
+  while (slots < 32 * (uint64_t)nq) slots <<= 1;
+  const bool direct = nq > 1024 || slots >= (uint64_t)c->n;
   const size_t seen_bytes = sizeof(uint64_t) * (size_t)(direct ? (uint64_t)c->n : slots);
   // (after b_rep, whose allocation may have given b_seen back)
   const bool fresh = !lane->b_seen.p || lane->b_seen.cap < seen_bytes || lane->seen_call == ~0u;

@@ -105,10 +105,10 @@ k_topk_plain(const int32_t* __restrict__ qp, int32_t n, const uint64_t* __restri
 // stands for it (rep[i] == i), and the others get that position and the
 // length kRepeated (the planner leaves them out, and their rows are copied).
 // seen holds {call number, position} words, so it needs no clearing and the
-// lengths no launch of their own.  It is indexed by vertex (mask ~0), or, where
-// the batch is small beside the graph, by a hash of at least twice as many
-// slots as queries: a slot of an earlier call is free, and as slots are never
-// freed within a call, a vertex ends at its claimed slot or at a free one.
+// lengths no launch of their own.  It is indexed by vertex (mask ~0), or, for
+// a small batch, by a hash of many more slots than queries: a slot of an
+// earlier call is free, and as slots are never freed within a call, a vertex
+// ends at its claimed slot or at a free one.
 // (8 bytes for every vertex made the first call on an R-MAT 20 graph, which
 // clears them, 70 us longer.)
 __global__ void k_query_lengths(const uint64_t* __restrict__ inv_ptr,
@@ -129,7 +129,7 @@ __global__ void k_query_lengths(const uint64_t* __restrict__ inv_ptr,
                    ? (uint32_t)q
                    : (uint32_t)((uint64_t)(uint32_t)q * 0x9E3779B97F4A7C15ull >> 32) & mask;
   int32_t first = (int32_t)i;
-  for (uint32_t probe = 0; probe <= mask; ++probe) {  // (half of the slots stay free)
+  for (uint32_t probe = 0; probe <= mask; ++probe) {  // (most slots stay free)
     unsigned long long old =
         __hip_atomic_load(&seen[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((uint32_t)(old >> 32) != call) {
