@@ -1758,28 +1758,19 @@ int run_batched(panther_ctx* c, Lane* lane, const int32_t* dq, const uint64_t* q
   if (b->untuned && qlen) {
     // A batch that is not tuned (a small one, a serving lane's, or any with
     // autotuning off): tier B's largest table where that spares the hub
-    // pipeline.  Where the longest list needs the pipeline anyway, the smallest
-    // table, which leaves tier M whole and tier B empty: what tier B would take
-    // costs less among the hubs than a CU for each of it.  Over 80 batches of
-    // R-MAT 18, 20 and 22 (61 to 100,000 queries, by degree, uniform with one
-    // hub, of tier B's lists in part or whole, of hubs alone; T = 5 and 20,
-    // k = 50) that takes 0.57 to 1.13 of the largest table's time, 0.94 at the
-    // median, and 0.56 to 1.10, 0.94 at the median, of the time with half of
-    // tier M among the hubs too (2,378 queries, one hub and tier B's lists: 0.26
-    // ms, 0.25 and here 0.20).  That half goes there only if nothing is left
-    // beside the hubs then, which spares the second stream (16 queries of 10^5
-    // paths on 1,000 vertices: 0.125 ms, 0.137 without).
-    const uint64_t T2 = 2 * (uint64_t)c->T;
-    const BatchConfig wide{}, small{512, 2, 1, 0};
-    const uint64_t LB = (uint64_t)layout_for(c, wide).TB / T2;
-    const uint64_t half = (uint64_t)layout_for(c, small).TB / T2 / 2;
-    bool hub = false, rest = false;
-    for (int64_t i = 0; i < nq && !(hub && rest); ++i) {
-      if (qlen[i] == kRepeated) continue;
-      hub = hub || qlen[i] > LB;
-      rest = rest || qlen[i] <= half;
-    }
-    b->cfg = !hub ? wide : (rest ? small : BatchConfig{512, 2, 2, 0});
+    // pipeline.  Where the longest list needs the pipeline anyway, two
+    // work-groups a CU with half the table: the lists that this sends to the
+    // hubs cost less there than a CU each.  Over 80 batches of R-MAT 18, 20 and
+    // 22 (61 to 100,000 queries, by degree, uniform with one hub, of tier B's
+    // lists in part or whole, of hubs alone; T = 5 and 20, k = 50) that takes
+    // 0.57 to 1.13 of the largest table's time, 0.94 at the median, and 0.56 to
+    // 1.10, 0.94 at the median, of the time with tier B empty (2,378 queries,
+    // one hub and tier B's lists: 0.26 ms, 0.25 and here 0.20).
+    const BatchConfig wide{};
+    const uint64_t LB = (uint64_t)layout_for(c, wide).TB / (2 * (uint64_t)c->T);
+    bool hub = false;
+    for (int64_t i = 0; i < nq && !hub; ++i) hub = qlen[i] > LB && qlen[i] != kRepeated;
+    b->cfg = hub ? BatchConfig{512, 2, 1, 0} : wide;
   }
   int st = plan(c, b, b->cfg, dq, qlen, dqlen, nq, k, d_ids, d_counts, d_len, theta, s, true,
                 &args);
