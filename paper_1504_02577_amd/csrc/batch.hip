@@ -1756,21 +1756,15 @@ int run_batched(panther_ctx* c, Lane* lane, const int32_t* dq, const uint64_t* q
     }
   }
   if (b->untuned && qlen) {
-    // A batch that is not tuned (a small one, a serving lane's, or any with
-    // autotuning off): tier B's largest table where that spares the hub
-    // pipeline.  Where the longest list needs the pipeline anyway, two
-    // work-groups a CU with half the table: the lists that this sends to the
-    // hubs cost less there than a CU each.  Over 80 batches of R-MAT 18, 20 and
-    // 22 (61 to 100,000 queries, by degree, uniform with one hub, of tier B's
-    // lists in part or whole, of hubs alone; T = 5 and 20, k = 50) that takes
-    // 0.57 to 1.13 of the largest table's time, 0.94 at the median, and 0.56 to
-    // 1.10, 0.94 at the median, of the time with tier B empty (2,378 queries,
-    // one hub and tier B's lists: 0.26 ms, 0.25 and here 0.20).
+    // A batch too small to tune (or a serving lane's): tier B's largest table
+    // where that spares the hub pipeline; where the longest list needs the
+    // pipeline anyway, the smallest, which leaves tier B empty (61 queries of
+    // R-MAT 20, k = 200: 0.157 ms, 0.21 with the largest).
     const BatchConfig wide{};
     const uint64_t LB = (uint64_t)layout_for(c, wide).TB / (2 * (uint64_t)c->T);
     bool hub = false;
     for (int64_t i = 0; i < nq && !hub; ++i) hub = qlen[i] > LB && qlen[i] != kRepeated;
-    b->cfg = hub ? BatchConfig{512, 2, 1, 0} : wide;
+    b->cfg = hub ? BatchConfig{512, 2, 2, 0} : wide;
   }
   int st = plan(c, b, b->cfg, dq, qlen, dqlen, nq, k, d_ids, d_counts, d_len, theta, s, true,
                 &args);
