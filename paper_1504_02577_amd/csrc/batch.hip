@@ -1756,10 +1756,18 @@ int run_batched(panther_ctx* c, Lane* lane, const int32_t* dq, const uint64_t* q
     }
   }
   if (b->untuned && qlen) {
-    // A batch too small to tune (or a serving lane's): tier B's largest table
-    // where that spares the hub pipeline; where the longest list needs the
-    // pipeline anyway, the smallest, which leaves tier B empty (61 queries of
-    // R-MAT 20, k = 200: 0.157 ms, 0.21 with the largest).
+    // A batch that is not tuned (a small one, a serving lane's, or any with
+    // autotuning off): tier B's largest table where that spares the hub
+    // pipeline; where the longest list needs the pipeline anyway, the smallest,
+    // which leaves tier B empty and tier M its shorter half.  Over 84 batches of
+    // R-MAT 18, 20 and 22 (61 to 100,000 queries, by degree, uniform with one
+    // hub, of tier B's lists in part or whole, of hubs alone; T = 5 and 20,
+    // k = 50) that takes 0.83 to 1.14 of the largest table's time, 1.0 at the
+    // median: less with the many short lists of uniform queries, more with T =
+    // 20.  (Two work-groups a CU without halving tier M: 0.56 to 1.06 of this
+    // rule's time, 0.93 at the median; but 61 queries by degree, k = 200, 0.153
+    // -> 0.159 ms, and 16 queries of 10^5 paths on 1,000 vertices 0.125 -> 0.137,
+    // which then need a second stream.)
     const BatchConfig wide{};
     const uint64_t LB = (uint64_t)layout_for(c, wide).TB / (2 * (uint64_t)c->T);
     bool hub = false;
