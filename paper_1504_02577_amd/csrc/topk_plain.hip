@@ -138,7 +138,7 @@ __global__ void k_query_lengths(const uint64_t* __restrict__ inv_ptr,
       if (prev == old) break;
       old = prev;
     }
-    if (queries[(uint32_t)old] == q) {
+    if (mask == ~0u || queries[(uint32_t)old] == q) {
       first = (int32_t)(uint32_t)old;
       break;
     }
