@@ -89,7 +89,11 @@ const char *panther_last_error(const panther_ctx *ctx);
  * ascending columns are searched by bisection, other rows scanned, so the
  * check costs O(m log d) on sorted input.  Without the flag the rows are
  * walked as given.  Replaces any previous graph and drops paths, index and
- * features; a rejected graph leaves the context without a graph.
+ * features; a rejected graph leaves the context without a graph.  The
+ * graph's storage and its preparation's (20 bytes per vertex) are kept for
+ * the next load; an allocation of the context that fails frees what it can
+ * do without (this scratch, then, where row sums need 64 bits, the guide
+ * records) and is tried again.
  * Errors: EINVAL (n < 1, m < 0, m >= 2^31, malformed CSR, an asymmetric CSR
  * under PANTHER_CHECK_SYMMETRIC, unknown flags, empty start set, row weight
  * sum >= 2^63), ENOMEM, EDEVICE. */

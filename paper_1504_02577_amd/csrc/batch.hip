@@ -791,7 +791,7 @@ struct BatchState {
   size_t dp_offs_cap = 0;
   char* dp_scan = nullptr;
   size_t dp_scan_cap = 0;
-  uint64_t* dp_small = nullptr;  // [0]: the pair count, [1, 133): digit starts
+  uint64_t* dp_small = nullptr;  // the pair count, then kDigits + 1 digit starts
   size_t dp_small_cap = 0;
   uint64_t* dp_hubL = nullptr;
   size_t dp_hubL_cap = 0;
@@ -1438,7 +1438,8 @@ static int plan(panther_ctx* c, BatchState* b, const BatchConfig& cfg, const int
   // length class, longest first (enough for load balance): a counting sort in
   // two passes, the LDS tiers' items written straight into the pinned upload
   // buffer.  (Hubs were ordered by exact length, which brought the repeats of
-  // a vertex together; they are answered once now.)
+  // a vertex together.  panther_topk_similar answers them once now; a serving
+  // lane still computes each, wherever in its class it comes.)
   std::array<size_t, kDigits + 1> start{};  // of each digit of plan_digit
   std::vector<std::pair<uint64_t, int32_t>> C;
   int st;

@@ -86,8 +86,8 @@ struct panther_ctx {
   uint64_t* d_pfx = nullptr;  // row prefixes from entry 1 on, when some W_v >= 2^32
   bool pfx64 = false;
   uint2* d_edge = nullptr;    // {prefix, column} when every W_v < 2^32
-  uint4* d_fat = nullptr;     // 64-byte guide records, same case
-  int4* d_start_rec = nullptr;  // {v, row start, degree, W} per start entry, same case
+  uint4* d_fat = nullptr;     // 64-byte guide records; with wider sums, if they fit
+  int4* d_start_rec = nullptr;  // {v, row start, degree, W} per start entry, W_v < 2^32
   int32_t* d_vstart = nullptr;
   int32_t nstart = 0;
   uint64_t max_w = 0;
@@ -180,7 +180,7 @@ int set_batch_option(panther_ctx* c, const std::string& key, int64_t value);
 // copies the forced batch options of lane 0 to another lane
 void copy_batch_options(panther_ctx* c, Lane* dst);
 void free_batch_state(Lane* lane);
-// drops the lane's captured graph and its repeat detection (new paths)
+// drops the lane's captured graph and its memory of the last launch (new paths)
 void forget_batch_graph(Lane* lane);
 void free_lane(Lane* lane);
 // Memory accounting of the serving loop's admission: the lane's tier and
