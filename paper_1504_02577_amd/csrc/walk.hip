@@ -63,10 +63,10 @@ __device__ __forceinline__ uint4 load_chunk(const uint4* p) {
 // line up four times, and with 2,048 lanes of a CU in flight the line could
 // leave the caches in between: the walk read 97 bytes per record from HBM, and
 // reads 66 now, starts included.)  What bounds it is the rate of scattered
-// requests, about 45 per nanosecond (4 GiB of 64-byte blocks, each read once
-// in scattered order, take 49; a table of 128 MB, which the Infinity Cache
-// holds, goes no faster): R-MAT 24, 10^8 paths of 5 steps, 17.4 -> 13.4 ms;
-// R-MAT 20, 10^7 paths, 1.89 -> 1.20 ms.  Every lane of the quad must be active.
+// requests, about 45 per nanosecond (a plain read of 4 GiB in scattered 64-byte
+// blocks reaches 49; a table of 128 MB, which the Infinity Cache holds, is no
+// faster): R-MAT 24, 10^8 paths of 5 steps, 17.4 -> 13.4 ms; R-MAT 20, 10^7
+// paths, 1.89 -> 1.20 ms.  Every lane of the quad must be active.
 template <bool NT>
 __device__ __forceinline__ void quad_records(const uint4* __restrict__ fat, uint32_t bucket,
                                              uint4 (&g)[4]) {
