@@ -91,8 +91,8 @@ __host__ __device__ constexpr int knn_scan_cap(int kp) { return kp < 64 ? 128 : 
 // for every load: 3.0 ms for the case below.)  The rows are split over grid.y
 // so that few queries fill the chip too: 301 queries x 262,144 rows of 100
 // coordinates took 43.1 ms on 19 work-groups that each scanned every row, and
-// take 1.35 (the arithmetic alone 0.41).  Two waves per SIMD (a few spilled
-// words) beat one with 284 registers, 1.70 ms.
+// take 1.35 (the arithmetic alone 0.41).  Two waves per SIMD (28 spilled
+// registers) beat one with 284 registers, 1.70 ms.
 __global__ void __launch_bounds__(kBlock, 2)
 k_knn_fp64(const float* __restrict__ theta, int32_t n, int32_t D, const float* __restrict__ qtheta,
            int32_t exclude_self, const int32_t* __restrict__ queries,
