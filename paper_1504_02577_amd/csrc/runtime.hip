@@ -205,11 +205,12 @@ static void free_graph(panther_ctx* c, bool release) {
 }
 
 // A graph buffer of at least `bytes`: the kept one unless it is too small, or
-// more than 64 MiB too large (what a graph holds, and whether there is room
-// for optional records, is hardly to depend on the graphs before it).
+// more than 64 MiB and a sixteenth too large (graphs of about one size share
+// their storage; else what a graph holds, and whether there is room for
+// optional records, is not to depend on the graphs before it).
 template <typename T>
 static int graph_alloc(panther_ctx* c, DevBuf& b, size_t bytes, const char* what, T** out) {
-  if (b.cap > bytes + ((size_t)64 << 20)) ctx_release(b);
+  if (b.cap > bytes + std::max(bytes / 16, (size_t)64 << 20)) ctx_release(b);
   const int st = ctx_ensure(c, b, std::max<size_t>(bytes, 16), what);
   *out = st ? nullptr : static_cast<T*>(b.p);
   return st;

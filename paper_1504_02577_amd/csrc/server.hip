@@ -242,7 +242,8 @@ static void lane_main(panther_server* sv, LaneWorker* w) {
       ctx_release(w->d_q);
       ctx_release(w->d_out);
     }
-    w->lane.work_room = sv->share - b.mem - lane_held(w);
+    const size_t taken = lane_held(w) + b.mem;
+    w->lane.work_room = sv->share > taken ? sv->share - taken : 0;
     run_batch(sv, w, b);
     const int64_t held = (int64_t)lane_held(w);
     for (int64_t cur = sv->peak_lane.load(); held > cur &&
